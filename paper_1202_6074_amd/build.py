@@ -23,7 +23,10 @@ HIP_FLAGS = [
     "-Wl,-rpath,/opt/rocm/lib",
     "-I" + os.path.join(ROOT, "include"),
 ]
-SOURCES = [os.path.join(CSRC, "kernels.hip"), os.path.join(CSRC, "kernels2d.hip"), os.path.join(CSRC, "capi.cpp")]
+# (object, source, extra flags): kernels.hip once for each storage mode (its
+# kernels, the long compilations, in parallel) and once for the dispatch
+SOURCES = ([(f"kernels_s{k}", "kernels.hip", [f"-DCM_STORAGE={k}"]) for k in range(4)] +
+           [("kernels", "kernels.hip", []), ("kernels2d", "kernels2d.hip", []), ("capi", "capi.cpp", [])])
 
 
 def _run(cmd):
@@ -34,14 +37,14 @@ def _run(cmd):
 
 
 def build_hip(out=LIB):
-    """Compile each source to an object in parallel, then link the shared library."""
+    """Compile the objects in parallel, then link the shared library."""
     from concurrent.futures import ThreadPoolExecutor
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     cflags = [f for f in HIP_FLAGS if f not in ("-shared",) and not f.startswith("-Wl,")]
-    objs = [os.path.join(objdir, os.path.basename(src) + ".o") for src in SOURCES]
+    objs = [os.path.join(objdir, name + ".o") for name, _, _ in SOURCES]
     with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
-        list(ex.map(lambda so: _run([HIPCC] + cflags + ["-c", "-o", so[1], so[0]]), zip(SOURCES, objs)))
+        list(ex.map(lambda o, s: _run([HIPCC] + cflags + s[2] + ["-c", "-o", o, os.path.join(CSRC, s[1])]), objs, SOURCES))
     tmp = out + ".tmp"
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-Wl,-rpath,/opt/rocm/lib", "-o", tmp] + objs)
     os.replace(tmp, out)

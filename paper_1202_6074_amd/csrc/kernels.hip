@@ -986,36 +986,6 @@ __global__ void __launch_bounds__(256) k_reduce_partial(const typename Store<S>:
     block_reduce(v, partial + 8 * b);
 }
 
-__global__ void __launch_bounds__(256) k_reduce_final(const double* __restrict__ partial, size_t nparts,
-                                                      double* __restrict__ out) {
-    double v[8] = {0, 0, 0, 0, 0, 0, 1.0e300, 0};
-    for (size_t b = threadIdx.x; b < nparts; b += blockDim.x) {
-        double w[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) w[k] = partial[8 * b + k];
-        combine(v, w);
-    }
-    block_reduce(v, out);
-}
-
-// ---------------------------------------------------------------- plain copy
-// Reference streaming kernel used to calibrate bandwidth and hardware byte
-// counters against a known size: one 16-byte vector per thread, non-temporal
-// load and store, 64-thread workgroups (the fastest plain copy form measured
-// on MI355X, 4 GiB each way, on two machines: 6.67 and 6.73 TB/s, against 6.52
-// and 6.49 with 256-thread workgroups, 6.35 with 512, 6.18 with 1024, 6.21-6.26
-// with an ordinary load; two or more vectors per thread and grid-stride loops
-// were slower still, 4.1-6.1 TB/s).
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-__global__ void __launch_bounds__(256) k_zero(unsigned int* __restrict__ dst, size_t n) {
-    const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < n) dst[k] = 0u;
-}
-__global__ void __launch_bounds__(256) k_copy(const u32x4* __restrict__ src, u32x4* __restrict__ dst, size_t n16) {
-    const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < n16) __builtin_nontemporal_store(__builtin_nontemporal_load(src + k), dst + k);
-}
-
 // ---------------------------------------------------------------- launch helpers
 // Rows of up to 256 cells get one workgroup of the next width in {64, 128,
 // 256} (so that the LDS gather applies); wider rows workgroups of 256.
@@ -1202,7 +1172,7 @@ static hipError_t step_inplace_w(const LaunchArgs& a, void* buf) {
     return a.force_field ? step_inplace_t<S, W, false, true>(a, buf) : step_inplace_t<S, W, false, false>(a, buf);
 }
 template <int S>
-static hipError_t step_inplace_s(const LaunchArgs& a, void* buf) {
+hipError_t step_inplace_s(const LaunchArgs& a, void* buf) {
     if (a.g.aa != 1 && a.g.aa != 2) return hipErrorInvalidValue;
     return split_wall_rows(a, [&](const LaunchArgs& b, bool w) {
         return w ? step_inplace_w<S, true>(b, buf) : step_inplace_w<S, false>(b, buf);
@@ -1246,7 +1216,7 @@ static hipError_t step_les(const LaunchArgs& a, const void* src, void* dst) {
     return a.cs_smag > 0.0 ? step_ff<S, W, true>(a, src, dst) : step_ff<S, W, false>(a, src, dst);
 }
 template <int S>
-static hipError_t step_w(const LaunchArgs& a, const void* src, void* dst) {
+hipError_t step_w(const LaunchArgs& a, const void* src, void* dst) {
     if (a.flags & 4u) {
         if (a.walls || !a.stress_prev || !a.stress_next) return hipErrorInvalidValue;   // checked by the caller
         return a.force_field ? step_sgs_t<S, true>(a, src, dst) : step_sgs_t<S, false>(a, src, dst);
@@ -1346,6 +1316,61 @@ static hipError_t reduce_t(const LaunchArgs& a, const void* src, double* partial
     return launch_reduce_final(partial, (size_t)grid.x * grid.y * grid.z, out, a.stream);
 }
 
+template <int S>
+hipError_t adjoint_s(const LaunchArgs& a, const void* state, const void* lam_in, void* lam_out, void* grad_F) {
+    return a.force_field ? adjoint_t<S, true>(a, state, lam_in, lam_out, grad_F)
+                         : adjoint_t<S, false>(a, state, lam_in, lam_out, grad_F);
+}
+template <int S>
+hipError_t seed_s(const LaunchArgs& a, const void* state, void* lam_out, void* grad_F) {
+    return a.force_field ? seed_t<S, true>(a, state, lam_out, grad_F) : seed_t<S, false>(a, state, lam_out, grad_F);
+}
+template <int S>
+hipError_t init_s(const LaunchArgs& a, void* dst, const void* rho, const void* u, int dt) {
+    if (a.walls) return a.force_field ? init_t<S, true, true>(a, dst, rho, u, dt) : init_t<S, true, false>(a, dst, rho, u, dt);
+    return a.force_field ? init_t<S, false, true>(a, dst, rho, u, dt) : init_t<S, false, false>(a, dst, rho, u, dt);
+}
+template <int S>
+hipError_t setpop_s(const LaunchArgs& a, void* dst, const void* f, int dt) {
+    return a.walls ? setpop_t<S, true>(a, dst, f, dt) : setpop_t<S, false>(a, dst, f, dt);
+}
+template <int S>
+hipError_t read_s(const LaunchArgs& a, const void* src, void* o0, void* o1, int dt, int mode) {
+    if (a.walls) return a.force_field ? read_t<S, true, true>(a, src, o0, o1, dt, mode) : read_t<S, true, false>(a, src, o0, o1, dt, mode);
+    return a.force_field ? read_t<S, false, true>(a, src, o0, o1, dt, mode) : read_t<S, false, false>(a, src, o0, o1, dt, mode);
+}
+template <int S>
+hipError_t reduce_s(const LaunchArgs& a, const void* src, double* partial, double* out, size_t mb) {
+    if (a.walls) return a.force_field ? reduce_t<S, true, true>(a, src, partial, out, mb) : reduce_t<S, true, false>(a, src, partial, out, mb);
+    return a.force_field ? reduce_t<S, false, true>(a, src, partial, out, mb) : reduce_t<S, false, false>(a, src, partial, out, mb);
+}
+
+// The launchers of one storage mode S. This file is compiled once for each mode
+// with CM_STORAGE = S, which emits the kernels of that mode (the four objects
+// build in parallel), and once without it for what follows, the dispatch over
+// the modes and the kernels that do not depend on them.
+#define CM_STORAGE_LAUNCHERS(KIND, S)                                                                        \
+    KIND template hipError_t step_w<S>(const LaunchArgs&, const void*, void*);                               \
+    KIND template hipError_t step_inplace_s<S>(const LaunchArgs&, void*);                                    \
+    KIND template hipError_t init_s<S>(const LaunchArgs&, void*, const void*, const void*, int);             \
+    KIND template hipError_t setpop_s<S>(const LaunchArgs&, void*, const void*, int);                        \
+    KIND template hipError_t read_s<S>(const LaunchArgs&, const void*, void*, void*, int, int);              \
+    KIND template hipError_t adjoint_s<S>(const LaunchArgs&, const void*, const void*, void*, void*);        \
+    KIND template hipError_t seed_s<S>(const LaunchArgs&, const void*, void*, void*);                        \
+    KIND template hipError_t reduce_s<S>(const LaunchArgs&, const void*, double*, double*, size_t);
+#define CM_DEFINE
+#ifdef CM_STORAGE
+CM_STORAGE_LAUNCHERS(CM_DEFINE, CM_STORAGE)
+#else
+CM_STORAGE_LAUNCHERS(extern, 0)
+CM_STORAGE_LAUNCHERS(extern, 1)
+CM_STORAGE_LAUNCHERS(extern, 2)
+CM_STORAGE_LAUNCHERS(extern, 3)
+#endif
+
+}  // namespace cm
+
+#ifndef CM_STORAGE
 #define CM_DISPATCH_S(fn, ...)                                  \
     switch (a.storage) {                                         \
         case 0: return fn<0>(__VA_ARGS__);                       \
@@ -1355,30 +1380,39 @@ static hipError_t reduce_t(const LaunchArgs& a, const void* src, double* partial
         default: return hipErrorInvalidValue;                    \
     }
 
-template <int S>
-static hipError_t init_s(const LaunchArgs& a, void* dst, const void* rho, const void* u, int dt) {
-    if (a.walls) return a.force_field ? init_t<S, true, true>(a, dst, rho, u, dt) : init_t<S, true, false>(a, dst, rho, u, dt);
-    return a.force_field ? init_t<S, false, true>(a, dst, rho, u, dt) : init_t<S, false, false>(a, dst, rho, u, dt);
-}
-template <int S>
-static hipError_t setpop_s(const LaunchArgs& a, void* dst, const void* f, int dt) {
-    return a.walls ? setpop_t<S, true>(a, dst, f, dt) : setpop_t<S, false>(a, dst, f, dt);
-}
-template <int S>
-static hipError_t read_s(const LaunchArgs& a, const void* src, void* o0, void* o1, int dt, int mode) {
-    if (a.walls) return a.force_field ? read_t<S, true, true>(a, src, o0, o1, dt, mode) : read_t<S, true, false>(a, src, o0, o1, dt, mode);
-    return a.force_field ? read_t<S, false, true>(a, src, o0, o1, dt, mode) : read_t<S, false, false>(a, src, o0, o1, dt, mode);
-}
-template <int S>
-static hipError_t reduce_s(const LaunchArgs& a, const void* src, double* partial, double* out, size_t mb) {
-    if (a.walls) return a.force_field ? reduce_t<S, true, true>(a, src, partial, out, mb) : reduce_t<S, true, false>(a, src, partial, out, mb);
-    return a.force_field ? reduce_t<S, false, true>(a, src, partial, out, mb) : reduce_t<S, false, false>(a, src, partial, out, mb);
+namespace cm {
+// Second pass of the FP64 reductions: one workgroup combines the partials.
+__global__ void __launch_bounds__(256) k_reduce_final(const double* __restrict__ partial, size_t nparts,
+                                                      double* __restrict__ out) {
+    double v[8] = {0, 0, 0, 0, 0, 0, 1.0e300, 0};
+    for (size_t b = threadIdx.x; b < nparts; b += blockDim.x) {
+        double w[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w[k] = partial[8 * b + k];
+        combine(v, w);
+    }
+    block_reduce(v, out);
 }
 
-}  // namespace cm
+// ---------------------------------------------------------------- plain copy
+// Reference streaming kernel used to calibrate bandwidth and hardware byte
+// counters against a known size: one 16-byte vector per thread, non-temporal
+// load and store, 64-thread workgroups (the fastest plain copy form measured
+// on MI355X, 4 GiB each way, on two machines: 6.67 and 6.73 TB/s, against 6.52
+// and 6.49 with 256-thread workgroups, 6.35 with 512, 6.18 with 1024, 6.21-6.26
+// with an ordinary load; two or more vectors per thread and grid-stride loops
+// were slower still, 4.1-6.1 TB/s).
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+__global__ void __launch_bounds__(256) k_zero(unsigned int* __restrict__ dst, size_t n) {
+    const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < n) dst[k] = 0u;
+}
+__global__ void __launch_bounds__(256) k_copy(const u32x4* __restrict__ src, u32x4* __restrict__ dst, size_t n16) {
+    const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < n16) __builtin_nontemporal_store(__builtin_nontemporal_load(src + k), dst + k);
+}
 
 // Host-callable launchers (C++ linkage, used by the C ABI layer).
-namespace cm {
 hipError_t launch_step(const LaunchArgs& a, const void* src, void* dst) { CM_DISPATCH_S(step_w, a, src, dst) }
 hipError_t launch_init_equilibrium(const LaunchArgs& a, void* dst, const void* rho, const void* u, int dt) {
     CM_DISPATCH_S(init_s, a, dst, rho, u, dt)
@@ -1391,26 +1425,10 @@ hipError_t launch_read(const LaunchArgs& a, const void* src, void* out0, void* o
     CM_DISPATCH_S(read_s, a, src, out0, out1, dt, mode)
 }
 hipError_t launch_adjoint(const LaunchArgs& a, const void* state, const void* lam_in, void* lam_out, void* grad_F) {
-    switch (a.storage) {
-        case 0: return a.force_field ? adjoint_t<0, true>(a, state, lam_in, lam_out, grad_F)
-                                     : adjoint_t<0, false>(a, state, lam_in, lam_out, grad_F);
-        case 1: return a.force_field ? adjoint_t<1, true>(a, state, lam_in, lam_out, grad_F)
-                                     : adjoint_t<1, false>(a, state, lam_in, lam_out, grad_F);
-        case 2: return a.force_field ? adjoint_t<2, true>(a, state, lam_in, lam_out, grad_F)
-                                     : adjoint_t<2, false>(a, state, lam_in, lam_out, grad_F);
-        case 3: return a.force_field ? adjoint_t<3, true>(a, state, lam_in, lam_out, grad_F)
-                                     : adjoint_t<3, false>(a, state, lam_in, lam_out, grad_F);
-        default: return hipErrorInvalidValue;
-    }
+    CM_DISPATCH_S(adjoint_s, a, state, lam_in, lam_out, grad_F)
 }
 hipError_t launch_energy_seed(const LaunchArgs& a, const void* state, void* lam_out, void* grad_F) {
-    switch (a.storage) {
-        case 0: return a.force_field ? seed_t<0, true>(a, state, lam_out, grad_F) : seed_t<0, false>(a, state, lam_out, grad_F);
-        case 1: return a.force_field ? seed_t<1, true>(a, state, lam_out, grad_F) : seed_t<1, false>(a, state, lam_out, grad_F);
-        case 2: return a.force_field ? seed_t<2, true>(a, state, lam_out, grad_F) : seed_t<2, false>(a, state, lam_out, grad_F);
-        case 3: return a.force_field ? seed_t<3, true>(a, state, lam_out, grad_F) : seed_t<3, false>(a, state, lam_out, grad_F);
-        default: return hipErrorInvalidValue;
-    }
+    CM_DISPATCH_S(seed_s, a, state, lam_out, grad_F)
 }
 hipError_t launch_reduce(const LaunchArgs& a, const void* src, double* partial, double* out, size_t max_blocks) {
     CM_DISPATCH_S(reduce_s, a, src, partial, out, max_blocks)
@@ -1473,3 +1491,4 @@ size_t reduce_partials(const Geom& g) {
     return (size_t)grid.x * grid.y * grid.z;
 }
 }  // namespace cm
+#endif   // CM_STORAGE
