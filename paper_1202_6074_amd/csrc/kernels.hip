@@ -312,31 +312,46 @@ __device__ __forceinline__ void gather_any(const typename Store<S>::T* src, cons
     else gather<S, WALLS, 2>(src, g, x, y, z, L, h);
 }
 
-// Gather of the two-buffer pull scheme for periodic rows when one workgroup
-// covers a whole grid row (nx <= blockDim.x, lanes x >= nx idle): every
-// population row is read aligned at x, so each wave reads whole cache lines and
-// nothing twice, and the values that cross to x + 1 or x - 1 (the 18 rows with
-// e_x != 0) are exchanged through LDS. Against per-lane shifted loads, the
-// access pattern alone (trivial arithmetic, 256^3 FP32) runs 7 % faster.
+// Gather of the two-buffer pull scheme when one workgroup covers a whole grid
+// row (nx <= blockDim.x = XW, lanes x >= nx idle): every population row is read
+// aligned at x, so each wave reads whole cache lines and nothing twice, and the
+// values that cross to x + 1 or x - 1 (the 18 rows with e_x != 0) are exchanged
+// through LDS. Against per-lane shifted loads, the access pattern alone
+// (trivial arithmetic, 256^3 FP32) runs 7 % faster. XW, the LDS row length, is
+// the workgroup's width: with 256 for all, the 18 KB of an FP32 workgroup left
+// room for eight 64-lane workgroups, eight waves, on a CU (64 x 64 x 128 FP32
+// channel: 22.7 us a step, with the wall rows' own launch 33.0; now 21.0).
+// WALLS: the populations that arrive from a wall are the opposite ones of the
+// cell itself, row 26 - i at x, so the rows next to a wall read other rows and
+// take their values without the shift; y is the same for the whole workgroup, so
+// these are scalar selects and need no launch of their own. (The wall term
+// itself is added by the caller.)
 // Every lane of the workgroup must call this (it contains a barrier); idle
 // lanes load a valid address and fill LDS columns nobody reads. pin() is
 // called after all population loads are issued and before the barrier.
-template <int S, bool SB, typename Pin>
-__device__ __forceinline__ void gather_xlds(const typename Store<S>::T* src, const Geom g, int x, bool act, int y,
+template <int S, bool SB, bool WALLS, int XW, typename Pin>
+__device__ __forceinline__ void gather_xlds(const typename Store<S>::T* __restrict__ src, const Geom g, int x, bool act, int y,
                                             int z, typename Store<S>::T (&out)[27], Pin&& pin) {
     using T = typename Store<S>::T;
-    __shared__ T sm[18][256];
+    __shared__ T sm[18][XW];
     const int ys[3] = {y == g.ny - 1 ? 0 : y + 1, y, y == 0 ? g.ny - 1 : y - 1};
     const int zs[3] = {z == g.nz - 1 ? 0 : z + 1, z, z == 0 ? g.nz - 1 : z - 1};
+    // from a wall: e_y = +1 on the lowest row, e_y = -1 on the highest
+    auto bounce = [&](int i) {
+        const int iy = (i / 3) % 3;
+        return WALLS && ((iy == 2 && y == 0) || (iy == 0 && y == g.ny - 1));
+    };
     const uint32_t rb = (uint32_t)g.nx * (uint32_t)sizeof(T);
     const uint32_t xt = (uint32_t)(act ? x : 0) * (uint32_t)sizeof(T);   // idle lanes read x = 0
     T raw[27];
 #pragma unroll
     for (int i = 0; i < 27; ++i) {
         const int ix = i % 3, iy = (i / 3) % 3, iz = i / 9;
-        const T* grp = src + row_base(g, i - ix, ys[iy], zs[iz]);
-        if constexpr (SB) raw[i] = load_raw<S>(at_row(grp, xt + (uint32_t)ix * rb));
-        else raw[i] = load_raw<S>((const T*)((const char*)grp + xt + (uint32_t)ix * rb));
+        const bool w = bounce(i);
+        const T* grp = src + row_base(g, w ? 24 - (i - ix) : i - ix, w ? y : ys[iy], w ? z : zs[iz]);
+        const uint32_t o = xt + (uint32_t)(w ? 2 - ix : ix) * rb;
+        if constexpr (SB) raw[i] = load_raw<S>(at_row(grp, o));
+        else raw[i] = load_raw<S>((const T*)((const char*)grp + o));
     }
 #pragma unroll
     for (int i = 0; i < 27; ++i)
@@ -352,8 +367,46 @@ __device__ __forceinline__ void gather_xlds(const typename Store<S>::T* src, con
 #pragma unroll
     for (int i = 0; i < 27; ++i) {
         const int ix = i % 3;   // e_x = ix - 1: the value comes from x - e_x
-        out[i] = ix == 1 ? raw[i] : sm[(i / 3) * 2 + ix / 2][ix == 0 ? xp : xm];
+        out[i] = ix == 1 ? raw[i] : sm[(i / 3) * 2 + ix / 2][bounce(i) ? x : (ix == 0 ? xp : xm)];
     }
+}
+
+// The wall terms of the populations that arrived from a wall, on a row next to
+// one (y uniform; the same rounded addition as in gather).
+template <typename R>
+__device__ __forceinline__ void add_wall_terms(const Geom& g, int y, const Launch<R>& L, R (&h)[27]) {
+    if (y == 0) {
+#pragma unroll
+        for (int i = 0; i < 27; ++i)
+            if ((i / 3) % 3 == 2) h[i] = add_rn(h[i], L.wt_lo[i]);
+    }
+    if (y == g.ny - 1) {
+#pragma unroll
+        for (int i = 0; i < 27; ++i)
+            if ((i / 3) % 3 == 0) h[i] = add_rn(h[i], L.wt_hi[i]);
+    }
+}
+
+// The z-line sums that collide_lines starts from, of the stored values t
+// gathered at a cell of row y.
+template <int S, bool WALLS, typename R = typename Store<S>::R>
+__device__ __forceinline__ void stored_line_sums(const typename Store<S>::T (&t)[27], const Geom& g, int y,
+                                                 const Launch<R>& L, R (&h)[27], R (&ls)[9], R (&ld)[9]) {
+    if constexpr (S == 3) {
+        // straight from the FP16 values (no conversions), but on the rows that
+        // take wall terms; the sums round the same
+        if (!(WALLS && (y == 0 || y == g.ny - 1))) {
+#pragma unroll
+            for (int l = 0; l < 9; ++l)
+                mix_line<0>(__builtin_bit_cast(uint16_t, t[l]), __builtin_bit_cast(uint16_t, t[l + 9]),
+                            __builtin_bit_cast(uint16_t, t[l + 18]), ls[l], ld[l], h[l]);
+            return;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 27; ++i) h[i] = from_store<S>(t[i], i, L.P.rho0);
+    if constexpr (WALLS) add_wall_terms(g, y, L, h);
+    zline_sums(h, ls, ld);
 }
 
 template <typename R, bool FFIELD>
@@ -420,14 +473,14 @@ __device__ __forceinline__ void finish_cell(typename Store<S>::T* __restrict__ d
 }
 
 // SGS: the sub-grid stress acts as a force (rs_prev read, rs_next written).
-// XL: one workgroup covers each grid row (nx <= blockDim.x, no walls in the
-// launch), so the x-shifted values go through LDS (gather_xlds); otherwise
-// each lane loads its shifted values itself (gather), looping over x when the
-// grid has one workgroup per row (g.rowloop).
+// XL: the width of the workgroup that covers each grid row (nx <= blockDim.x =
+// XL), so that the x-shifted values go through LDS (gather_xlds); 0: each lane
+// loads its shifted values itself (gather), looping over x when the grid has
+// one workgroup per row (g.rowloop).
 // FP16 storage is bound by instruction issue: five waves per SIMD (at most 96
 // vector registers, which it fits without spilling) measured 3 % faster; the
 // other modes gained nothing or spilled.
-template <int S, bool WALLS, bool LES, bool FFIELD, bool VAR, bool SGS = false, bool XL = true>
+template <int S, bool WALLS, bool LES, bool FFIELD, bool VAR, bool SGS = false, int XL = 256>
 __global__ void __launch_bounds__(256, (S == 3 && !SGS) ? 5 : 1) k_step(const typename Store<S>::T* __restrict__ src,
                                               typename Store<S>::T* __restrict__ dst,
                                               const typename Store<S>::R* __restrict__ force, const Geom g,
@@ -444,8 +497,7 @@ __global__ void __launch_bounds__(256, (S == 3 && !SGS) ? 5 : 1) k_step(const ty
     block_coords(g.xcd, bx, y, z);
     y = g.ybase + y * g.ystride;
     z += g.zbase;
-    if constexpr (XL) {
-        static_assert(!WALLS, "the LDS gather is for periodic rows");
+    if constexpr (XL != 0) {
         const int x = threadIdx.x;
         const bool act = x < g.nx;
         // the stress and force loads go out with the population loads, in the
@@ -454,7 +506,7 @@ __global__ void __launch_bounds__(256, (S == 3 && !SGS) ? 5 : 1) k_step(const ty
         if constexpr (SGS) sgs_load<R, SB>(rs_prev, g, act ? x : 0, y, z, sv);
         row_force<R, FFIELD, SB>(force, g, L, act ? x : 0, y, z, F);
         typename Store<S>::T t[27];
-        gather_xlds<S, SB>(src, g, x, act, y, z, t, [&]() {
+        gather_xlds<S, SB, WALLS, XL>(src, g, x, act, y, z, t, [&]() {
             if constexpr (FFIELD) {
 #pragma unroll
                 for (int d = 0; d < 3; ++d) asm volatile("" : "+v"(F[d]));
@@ -465,17 +517,7 @@ __global__ void __launch_bounds__(256, (S == 3 && !SGS) ? 5 : 1) k_step(const ty
             }
         });
         R h[27], ls[9], ld[9];
-        if constexpr (S == 3) {
-            // the z-line sums straight from the FP16 values (no conversions)
-#pragma unroll
-            for (int l = 0; l < 9; ++l)
-                mix_line<0>(__builtin_bit_cast(uint16_t, t[l]), __builtin_bit_cast(uint16_t, t[l + 9]),
-                            __builtin_bit_cast(uint16_t, t[l + 18]), ls[l], ld[l], h[l]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 27; ++i) h[i] = from_store<S>(t[i], i, L.P.rho0);
-            zline_sums(h, ls, ld);
-        }
+        stored_line_sums<S, WALLS>(t, g, y, L, h, ls, ld);
         R acc[3];
         if constexpr (SGS) sgs_combine(sv, acc);
         if (act) finish_cell<S, LES, VAR, SGS, SB>(dst, g, L, x, y, z, h, ls, ld, F, acc, rs_next);
@@ -987,17 +1029,20 @@ __global__ void __launch_bounds__(256) k_reduce_partial(const typename Store<S>:
 }
 
 // ---------------------------------------------------------------- launch helpers
-// Rows of up to 256 cells get one workgroup of the next width in {64, 128,
-// 256} (so that the LDS gather applies); wider rows workgroups of 256.
+// Rows of up to 256 cells get one workgroup of the next multiple of 64 lanes
+// (so that the LDS gather applies); wider rows workgroups of 256.
 static dim3 grid_for_step(const Geom& g, int& bx) {
-    bx = g.nx <= 64 ? 64 : (g.nx <= 128 ? 128 : 256);
+    bx = g.nx <= 256 ? (g.nx + 63) / 64 * 64 : 256;
     return dim3(g.rowloop ? 1 : (g.nx + bx - 1) / bx, g.yrows, g.nz);
 }
 
-// With walls, only the rows y = 0 and y = ny - 1 need the bounce-back code:
-// the interior rows run the periodic kernel (its y +- 1 never wraps there) and
-// the two wall rows a kernel of their own, so that the wall terms and extra
-// row pointers do not burden the registers of every workgroup.
+// With walls, only the rows y = 0 and y = ny - 1 need the bounce-back code.
+// Where lanes gather for themselves (wide rows, in-place streaming) the interior
+// rows run the periodic kernel (its y +- 1 never wraps there) and the two wall
+// rows a kernel of their own, so that the wall terms and extra row pointers do
+// not burden the registers of every workgroup. The LDS-exchange kernel takes all
+// rows in one launch (gather_xlds): the second launch cost 11 us of a 33 us step
+// at 64 x 64 x 128 and 12 of 89 us at 128^3 FP32.
 template <typename F>
 static hipError_t split_wall_rows(const LaunchArgs& a, F&& launch) {
     if (!a.walls) return launch(a, false);
@@ -1058,10 +1103,20 @@ static Launch<R> make_launch(const LaunchArgs& a) {
     return L;
 }
 
-// The LDS gather needs one workgroup per grid row (a single chunk of x) and
-// periodic rows; the wall rows and wider rows take the per-lane gather, and so
-// does every row when the caller asks for it (g.lanegather, a tuning hint).
-static bool one_block_per_row(const Geom& g, const dim3& grid, int bx) { return grid.x == 1 && g.nx <= bx && !g.lanegather; }
+// The LDS gather needs one workgroup per grid row (a single chunk of x); wider
+// rows take the per-lane gather, and so does every row when the caller asks for
+// it (g.lanegather, a tuning hint).
+static bool one_block_per_row(const Geom& g) { return g.nx <= 256 && !g.lanegather; }
+
+// Calls f with the row width XL of the LDS-exchange kernel as a compile-time
+// constant: the workgroup's width for this row length (grid_for_step).
+template <typename F>
+static void with_row_width(int bx, F&& f) {
+    if (bx <= 64) f(std::integral_constant<int, 64>());
+    else if (bx <= 128) f(std::integral_constant<int, 128>());
+    else if (bx <= 192) f(std::integral_constant<int, 192>());
+    else f(std::integral_constant<int, 256>());
+}
 
 // FP16 rows for the two-cells-per-lane kernel: an even number of 258 to 512
 // cells (one workgroup of at most 256 lanes per row; rows of up to 256 cells
@@ -1135,17 +1190,18 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
             return hipGetLastError();
         }
     }
-    if constexpr (!W) {
-        if (one_block_per_row(a.g, grid, bx)) {
-            return launch_z_chunks(a.g, grid, sizeof(T) == 4, [&](const dim3& gq, const Geom& gg) {
-                if (var) k_step<S, W, LES, FF, true, false, true><<<gq, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L);
-                else k_step<S, W, LES, FF, false, false, true><<<gq, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L);
+    if (one_block_per_row(a.g)) {
+        return launch_z_chunks(a.g, grid, sizeof(T) == 4, [&](const dim3& gq, const Geom& gg) {
+            with_row_width(bx, [&](auto xl) {
+                constexpr int XL = decltype(xl)::value;
+                if (var) k_step<S, W, LES, FF, true, false, XL><<<gq, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L);
+                else k_step<S, W, LES, FF, false, false, XL><<<gq, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L);
             });
-        }
+        });
     }
     const unsigned cap = sizeof(T) == 4 && a.g.nx > 256 && a.g.nx <= 512 ? kLdsFourPerCu : 0u;
-    if (var) k_step<S, W, LES, FF, true, false, false><<<grid, bx, cap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
-    else k_step<S, W, LES, FF, false, false, false><<<grid, bx, cap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
+    if (var) k_step<S, W, LES, FF, true, false, 0><<<grid, bx, cap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
+    else k_step<S, W, LES, FF, false, false, 0><<<grid, bx, cap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
     return hipGetLastError();
 }
 
@@ -1187,7 +1243,7 @@ static hipError_t step_sgs_t(const LaunchArgs& a, const void* src, void* dst) {
     int bx;
     const dim3 grid = grid_for_step(a.g, bx);
     const bool var = (a.flags & 3u) != 0;
-    const bool xl = one_block_per_row(a.g, grid, bx);
+    const bool xl = one_block_per_row(a.g);
     hipStream_t st = (hipStream_t)a.stream;
     const Launch<R> L = make_launch<R>(a);
     const R* rp = (const R*)a.stress_prev;
@@ -1199,10 +1255,14 @@ static hipError_t step_sgs_t(const LaunchArgs& a, const void* src, void* dst) {
     // FP32 rows of one workgroup in chunks of planes, as the step without the
     // stress force (256^3: 769.4 -> 761.2 us)
     return launch_z_chunks(g, grid, sizeof(T) == 4 && xl, [&](const dim3& gq, const Geom& gg) {
-        if (var && xl) k_step<S, false, false, FF, true, true, true><<<gq, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L, rp, rn);
-        else if (var) k_step<S, false, false, FF, true, true, false><<<gq, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L, rp, rn);
-        else if (xl) k_step<S, false, false, FF, false, true, true><<<gq, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L, rp, rn);
-        else k_step<S, false, false, FF, false, true, false><<<gq, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L, rp, rn);
+        if (xl) {
+            with_row_width(bx, [&](auto w) {
+                constexpr int XL = decltype(w)::value;
+                if (var) k_step<S, false, false, FF, true, true, XL><<<gq, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L, rp, rn);
+                else k_step<S, false, false, FF, false, true, XL><<<gq, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L, rp, rn);
+            });
+        } else if (var) k_step<S, false, false, FF, true, true, 0><<<gq, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L, rp, rn);
+        else k_step<S, false, false, FF, false, true, 0><<<gq, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L, rp, rn);
     });
 
 }
@@ -1221,6 +1281,7 @@ hipError_t step_w(const LaunchArgs& a, const void* src, void* dst) {
         if (a.walls || !a.stress_prev || !a.stress_next) return hipErrorInvalidValue;   // checked by the caller
         return a.force_field ? step_sgs_t<S, true>(a, src, dst) : step_sgs_t<S, false>(a, src, dst);
     }
+    if (one_block_per_row(a.g)) return a.walls ? step_les<S, true>(a, src, dst) : step_les<S, false>(a, src, dst);
     return split_wall_rows(a, [&](const LaunchArgs& b, bool w) {
         return w ? step_les<S, true>(b, src, dst) : step_les<S, false>(b, src, dst);
     });
