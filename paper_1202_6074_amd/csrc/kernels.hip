@@ -443,6 +443,28 @@ __device__ __forceinline__ void row_force(const R* __restrict__ force, const Geo
 }
 
 // h[0..8], ls, ld: the z-line sums of the gathered populations (zline_sums).
+// The collision, and the store of the sub-grid stress (SGS).
+template <int S, bool LES, bool VAR, bool SGS, bool SB = false>
+__device__ __forceinline__ void collide_cell(const Geom g, const Launch<typename Store<S>::R>& L, int x, int y, int z,
+                                             typename Store<S>::R (&h)[27], const typename Store<S>::R (&ls)[9],
+                                             const typename Store<S>::R (&ld)[9], const typename Store<S>::R (&F)[3],
+                                             const typename Store<S>::R (&acc)[3],
+                                             typename Store<S>::R* __restrict__ rs_next) {
+    using R = typename Store<S>::R;
+    R rho, ux, uy, uz;
+    if constexpr (SGS) {
+        R st[6];
+        collide_lines<R, false, VAR, true, S == 3>(h, ls, ld, F[0], F[1], F[2], L.P, rho, ux, uy, uz, acc, st);
+        const size_t row = (size_t)g.nx * ((size_t)y + (size_t)g.ny * z);   // uniform
+        const uint32_t xb = (uint32_t)x * (uint32_t)sizeof(R);
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+            __builtin_nontemporal_store(st[k], row_at<SB>(rs_next + (size_t)k * g.N + row, xb));
+    } else {
+        (void)acc; (void)rs_next; (void)x; (void)y; (void)z;
+        collide_lines<R, LES, VAR, false, S == 3>(h, ls, ld, F[0], F[1], F[2], L.P, rho, ux, uy, uz);
+    }
+}
 template <int S, bool LES, bool VAR, bool SGS, bool SB = false>
 __device__ __forceinline__ void finish_cell(typename Store<S>::T* __restrict__ dst, const Geom g,
                                             const Launch<typename Store<S>::R>& L, int x, int y, int z,
@@ -450,22 +472,8 @@ __device__ __forceinline__ void finish_cell(typename Store<S>::T* __restrict__ d
                                             const typename Store<S>::R (&ld)[9], const typename Store<S>::R (&F)[3],
                                             const typename Store<S>::R (&acc)[3],
                                             typename Store<S>::R* __restrict__ rs_next) {
-    using R = typename Store<S>::R;
     using T = typename Store<S>::T;
-    const size_t row = (size_t)g.nx * ((size_t)y + (size_t)g.ny * z);   // uniform
-    const uint32_t xb = (uint32_t)x * (uint32_t)sizeof(R);
-    const R Fx = F[0], Fy = F[1], Fz = F[2];
-    R rho, ux, uy, uz;
-    if constexpr (SGS) {
-        R st[6];
-        collide_lines<R, false, VAR, true, S == 3>(h, ls, ld, Fx, Fy, Fz, L.P, rho, ux, uy, uz, acc, st);
-#pragma unroll
-        for (int k = 0; k < 6; ++k)
-            __builtin_nontemporal_store(st[k], row_at<SB>(rs_next + (size_t)k * g.N + row, xb));
-    } else {
-        (void)acc; (void)rs_next;
-        collide_lines<R, LES, VAR, false, S == 3>(h, ls, ld, Fx, Fy, Fz, L.P, rho, ux, uy, uz);
-    }
+    collide_cell<S, LES, VAR, SGS, SB>(g, L, x, y, z, h, ls, ld, F, acc, rs_next);
     const uint32_t xt = (uint32_t)x * (uint32_t)sizeof(T);
 #pragma unroll
     for (int i = 0; i < 27; ++i)
@@ -546,6 +554,134 @@ __global__ void __launch_bounds__(256, (S == 3 && !SGS) ? 5 : 1) k_step(const ty
             zline_sums(h, ls, ld);
             finish_cell<S, LES, VAR, SGS>(dst, g, L, x, y, z, h, ls, ld, F, acc, rs_next);
         }
+    }
+}
+
+// ---------------------------------------------------------------- step, whole rows through LDS
+// Direct copy of 16 bytes a lane from global memory to LDS: lane l of a wave
+// writes at `lds` + 16 l (lds the same for the whole wave), without a vector
+// register in between. Complete after wait_lds_copies, for the wave's own
+// copies; a barrier after it makes them visible to the workgroup.
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+template <typename P>
+__device__ __forceinline__ void copy16_to_lds(P src, void* lds) {
+    constexpr int kNonTemporal = 2;   // cache policy bit of the instruction
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                     (__attribute__((address_space(3))) void*)lds, 16, 0, kNonTemporal);
+}
+__device__ __forceinline__ void wait_lds_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Elements of LDS that hold a group of three adjacent rows of nx values with up
+// to one 16-byte vector of misalignment, in whole vectors.
+template <typename T>
+__host__ __device__ constexpr uint32_t group_stride(uint32_t nx) {
+    constexpr uint32_t V = 16 / sizeof(T);
+    return (3u * nx + 2u * V - 1u) / V * V;
+}
+
+// Stores a block of n values at D, held in LDS from element o on (o the
+// misalignment of D, so that LDS and memory vectors coincide): whole vectors
+// non-temporal, the values of the vectors at the ends one by one.
+template <typename T>
+__device__ __forceinline__ void store_block(T* D, uint32_t o, uint32_t n, const T* sm, uint32_t tid, uint32_t bd) {
+    constexpr uint32_t V = 16 / sizeof(T);
+    T* const D0 = D - o;   // the block's first vector
+    const uint32_t end = o + n, c1 = end / V;
+    for (uint32_t c = tid + (o ? 1u : 0u); c < c1; c += bd)
+        __builtin_nontemporal_store(((const u32x4*)sm)[c], at_row((u32x4*)D0, c * 16u));
+    if (o && tid >= o && tid < V) D0[tid] = sm[tid];
+    const uint32_t tail = c1 * V + tid;
+    if (tail < end) D0[tail] = sm[tail];
+}
+
+// The step on rows that do not start on cache lines (or are wider than 256
+// cells): one workgroup per grid row, lane = cell, and the row's populations go
+// through LDS in both directions. In memory the three populations of a source
+// row that differ only in e_x are one contiguous block of 3 nx values, and the
+// 27 rows that the cell row writes are one block of 27 nx; both are moved as
+// 16-byte vectors of 16-byte-aligned addresses whatever nx is, the reads
+// straight into LDS and without passing through registers. What a lane reads
+// from LDS is shifted by e_x, what it writes is its own column.
+// Bound by HBM; per-lane accesses to such rows touch three lines instead of two
+// per wave in most rows and write partial lines, which non-temporal stores send
+// to memory one by one.
+// A vector at either end of a block can hold values outside it. Reading them
+// is harmless (an aligned vector with one valid byte lies in a mapped page; the
+// values are not used); they are not written: the ends of the row's block are
+// stored value by value.
+// DIRECT: rows that do start on cache lines: each lane stores its own values (no
+// partial lines to avoid, and one barrier less).
+template <int S, bool WALLS, bool LES, bool FFIELD, bool VAR, bool SGS, bool DIRECT>
+__global__ void __launch_bounds__(512) k_step_row(const typename Store<S>::T* __restrict__ src,
+                                                  typename Store<S>::T* __restrict__ dst,
+                                                  const typename Store<S>::R* __restrict__ force, const Geom g,
+                                                  const Launch<typename Store<S>::R> L,
+                                                  const typename Store<S>::R* __restrict__ rs_prev = nullptr,
+                                                  typename Store<S>::R* __restrict__ rs_next = nullptr) {
+    using R = typename Store<S>::R;
+    using T = typename Store<S>::T;
+    constexpr uint32_t V = 16 / sizeof(T);
+    extern __shared__ __align__(16) unsigned char lds_bytes[];
+    T* const sm = (T*)lds_bytes;
+    int bx, y, z;
+    block_coords(g.xcd, bx, y, z);
+    z += g.zbase;
+    const uint32_t tid = threadIdx.x, bd = blockDim.x, nx = (uint32_t)g.nx;
+    const uint32_t wave0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid & ~63u));
+    const bool act = tid < nx;
+    const uint32_t x = act ? tid : 0u;   // idle lanes compute cell 0 and store nothing
+    const int ys[3] = {y == g.ny - 1 ? 0 : y + 1, y, y == 0 ? g.ny - 1 : y - 1};
+    const int zs[3] = {z == g.nz - 1 ? 0 : z + 1, z, z == 0 ? g.nz - 1 : z - 1};
+    // group q = (e_x = -1, 0, 1) of (e_y, e_z); from a wall the opposite group of
+    // the own row, its three populations in reverse order and not shifted
+    auto bounce = [&](int q) { return WALLS && ((q % 3 == 2 && y == 0) || (q % 3 == 0 && y == g.ny - 1)); };
+    const uint32_t gs = group_stride<T>(nx);
+    uint32_t off[9];   // misalignment of each group, in elements
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        const bool w = bounce(q);
+        const T* A = src + row_base(g, w ? 24 - 3 * q : 3 * q, w ? y : ys[q % 3], w ? z : zs[q / 3]);
+        off[q] = (uint32_t)((uintptr_t)A & 15u) / (uint32_t)sizeof(T);
+        const u32x4* base = (const u32x4*)((uintptr_t)A & ~(uintptr_t)15);
+        const uint32_t n = (off[q] + 3u * nx + V - 1u) / V;
+        for (uint32_t k = 0; k < n; k += bd)   // one pass, two for FP64
+            if (tid + k < n) copy16_to_lds(at_row(base, (tid + k) * 16u), lds_bytes + 16u * (q * (gs / V) + k + wave0));
+    }
+    R sv[SGS ? 18 : 1], F[3];
+    if constexpr (SGS) sgs_load<R, false>(rs_prev, g, (int)x, y, z, sv);
+    row_force<R, FFIELD, false>(force, g, L, (int)x, y, z, F);
+    wait_lds_copies();
+    __syncthreads();
+    const uint32_t xs[3] = {x + 1u >= nx ? 0u : x + 1u, nx + x, 2u * nx + (x == 0u ? nx - 1u : x - 1u)};   // x - e_x
+    T t[27];
+#pragma unroll
+    for (int i = 0; i < 27; ++i) {
+        const int ix = i % 3, q = i / 3;
+        t[i] = sm[q * gs + off[q] + (bounce(q) ? x + (uint32_t)(2 - ix) * nx : xs[ix])];
+    }
+    R h[27], ls[9], ld[9];
+    stored_line_sums<S, WALLS>(t, g, y, L, h, ls, ld);
+    R acc[3];
+    if constexpr (SGS) sgs_combine(sv, acc);
+    if constexpr (DIRECT) {
+        if (act) finish_cell<S, LES, VAR, SGS, S == 3>(dst, g, L, (int)x, y, z, h, ls, ld, F, acc, rs_next);
+    } else {
+        // (unguarded, the collision of the idle lanes cost 15 vector registers)
+        if (act) collide_cell<S, LES, VAR, SGS>(g, L, (int)x, y, z, h, ls, ld, F, acc, rs_next);
+        __syncthreads();   // every lane has read its values: the LDS takes the results
+        T* const D = dst + row_base(g, 0, y, z);
+        const uint32_t o = (uint32_t)((uintptr_t)D & 15u) / (uint32_t)sizeof(T);
+        if (act) {
+            uint32_t at = o + x;   // stepped row by row: 27 addresses held at once spilled
+#pragma unroll
+            for (int i = 0; i < 27; ++i) {
+                sm[at] = to_store<S>(h[i], i, L.P.rho0);
+                at += nx;
+                asm volatile("" : "+v"(at));
+            }
+        }
+        __syncthreads();
+        store_block<T>(D, o, 27u * nx, sm, tid, bd);
     }
 }
 
@@ -1030,9 +1166,11 @@ __global__ void __launch_bounds__(256) k_reduce_partial(const typename Store<S>:
 
 // ---------------------------------------------------------------- launch helpers
 // Rows of up to 256 cells get one workgroup of the next multiple of 64 lanes
-// (so that the LDS gather applies); wider rows workgroups of 256.
+// (so that the LDS gather applies); wider rows the fewest workgroups of at most
+// 256 lanes, of even width (300 cells: two of 192 lanes, not 256 and 44 of 256).
 static dim3 grid_for_step(const Geom& g, int& bx) {
-    bx = g.nx <= 256 ? (g.nx + 63) / 64 * 64 : 256;
+    const int n = (g.nx + 255) / 256;
+    bx = ((g.nx + n - 1) / n + 63) / 64 * 64;
     return dim3(g.rowloop ? 1 : (g.nx + bx - 1) / bx, g.yrows, g.nz);
 }
 
@@ -1108,6 +1246,32 @@ static Launch<R> make_launch(const LaunchArgs& a) {
 // it (g.lanegather, a tuning hint).
 static bool one_block_per_row(const Geom& g) { return g.nx <= 256 && !g.lanegather; }
 
+// Rows for the kernel that moves whole rows through LDS (es: storage bytes of
+// one value). Rows of up to 256 cells that start on cache lines, es nx a
+// multiple of 128 bytes, stay with the LDS-exchange kernel, whose single barrier
+// costs less (us per step, LDS exchange / whole rows: 256^3 FP32 587 / 609,
+// 192^3 FP16 130 / 137); so do lattices whose two buffers fit the 32 MB of the
+// eight L2s, where partial lines are merged before they reach memory and the
+// extra barriers show (40^3 FP32 6.2 / 7.7, 45 x 60 x 80 FP16 9.5 / 10.4; beyond
+// it 70^3 FP32 22.1 / 19.4, 100^3 53.6 / 43.4, 250 x 200 x 200 454 / 374,
+// 187 x 151 x 133 FP16 131 / 81, 201 x 200 x 200 FP64 660 / 618). Rows of 257
+// to 512 cells: all that the two-cell FP16 kernel does not take (per-lane
+// gather / whole rows: 300 x 200 x 200 FP32 747 / 467, 320 574 / 469,
+// 384 x 384 x 200 1,205 / 1,142, 512 x 512 x 128 1,298 / 1,275), but not FP64,
+// whose LDS would leave two workgroups on a CU. Rows shorter than 16 cells fill
+// too few lanes and vectors to gain.
+static bool whole_rows(const Geom& g, size_t es) {
+    if (g.lanegather || g.rowloop || g.nx < 16 || g.nx > 512) return false;
+    if (g.nx > 256) return es != 8;
+    return (size_t)g.nx * es % 128 != 0 && 27 * (size_t)g.N * es >= ((size_t)16 << 20);
+}
+
+// Its workgroup, one lane per cell, and LDS: the nine groups of three rows (the
+// block of 27 result rows that takes their place is smaller).
+static int row_lanes(const Geom& g) { return (g.nx + 63) / 64 * 64; }
+template <typename T>
+static unsigned row_lds(const Geom& g) { return 9u * group_stride<T>((uint32_t)g.nx) * (unsigned)sizeof(T); }
+
 // Calls f with the row width XL of the LDS-exchange kernel as a compile-time
 // constant: the workgroup's width for this row length (grid_for_step).
 template <typename F>
@@ -1130,16 +1294,14 @@ static bool pair_rows(const Geom& g, const void* src, const void* dst, const voi
 
 // Occupancy caps by LDS reservation: with 60,000 bytes of the CU's 160 KB of
 // LDS reserved per workgroup, at most two workgroups share a CU; with 40,960
-// bytes, four (three for a kernel that holds 9 KB of its own). The reserved
-// LDS itself is not used. Measured at 256^3 and 512^3, fewer resident rows per
-// CU made the DRAM traffic of these kernels more efficient: the in-place pair
-// of kernels with 4-byte populations on rows of at most 512 cells 3-6 % faster
-// at two workgroups per CU (FP16: slower; rows of 1024 cells: not faster), the
-// per-lane gather with 4-byte populations on rows of 257-512 cells 1-2 %
-// faster at four, the two-cells-per-lane FP16 kernel about 1 % faster at
-// three. The LDS-exchange step kernels are fastest at their full occupancy
-// (six to seven workgroups).
-constexpr unsigned kLdsTwoPerCu = 60000, kLdsFourPerCu = 40960, kLdsPairCap = 40960;
+// bytes, three for a kernel that holds 9 KB of its own. The reserved LDS itself
+// is not used. Measured at 256^3 and 512^3, fewer resident rows per CU made the
+// DRAM traffic of these kernels more efficient: the in-place pair of kernels
+// with 4-byte populations on rows of at most 512 cells 3-6 % faster at two
+// workgroups per CU (FP16: slower; rows of 1024 cells: not faster), the
+// two-cells-per-lane FP16 kernel about 1 % faster at three. The LDS-exchange
+// step kernels are fastest at their full occupancy (six to seven workgroups).
+constexpr unsigned kLdsTwoPerCu = 60000, kLdsPairCap = 40960;
 
 // A step over many z-planes runs as launches of at most kZChunk planes each:
 // the end of each launch brings the eight XCDs back to the same planes, where
@@ -1182,13 +1344,33 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
     if constexpr (!W && S == 3) {
         if (pair_rows(a.g, src, dst, a.force_field)) {
             const dim3 gp(1, a.g.yrows, a.g.nz);
-            const int bp = 256;   // one lane per pair of a row of 258-512 cells
-            // with its own 9 KB of LDS, at most three workgroups per CU
-            // (measured 0.8 and 1.3 % faster at 512^3 on two machines)
-            if (var) k_step_f16pair<LES, FF, true><<<gp, bp, kLdsPairCap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
-            else k_step_f16pair<LES, FF, false><<<gp, bp, kLdsPairCap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
+            // one lane per pair; at most three workgroups per CU (with the
+            // kernel's own 9 KB of LDS) for the longest rows only (512 x 512 x
+            // 128: 688 us per step without, 663 with the cap; 400 x 200 x 200:
+            // 335 and 343, in 256 lanes for all widths and the cap 381)
+            const int bp = (a.g.nx / 2 + 63) / 64 * 64;
+            const unsigned pcap = a.g.nx > 448 ? kLdsPairCap : 0u;
+            if (var) k_step_f16pair<LES, FF, true><<<gp, bp, pcap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
+            else k_step_f16pair<LES, FF, false><<<gp, bp, pcap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
             return hipGetLastError();
         }
+    }
+    if (whole_rows(a.g, sizeof(T))) {
+        // rows that start on cache lines (wider than 256 cells: the others of
+        // that kind take the LDS exchange): each lane stores its own values
+        // (us per step, through LDS / directly: 384 x 384 x 200 FP32 1,158 /
+        // 1,142, 512 x 512 x 128 1,377 / 1,275; 250 x 200 x 200 374 / 433)
+        const bool direct = (size_t)a.g.nx * sizeof(T) % 128 == 0;
+        return launch_z_chunks(a.g, dim3(1, a.g.ny, a.g.nz), sizeof(T) == 4, [&](const dim3& gq, const Geom& gg) {
+            auto launch = [&](auto v, auto d) {
+                k_step_row<S, W, LES, FF, decltype(v)::value, false, decltype(d)::value>
+                    <<<gq, row_lanes(gg), row_lds<T>(gg), st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L);
+            };
+            if (var && direct) launch(std::true_type(), std::true_type());
+            else if (var) launch(std::true_type(), std::false_type());
+            else if (direct) launch(std::false_type(), std::true_type());
+            else launch(std::false_type(), std::false_type());
+        });
     }
     if (one_block_per_row(a.g)) {
         return launch_z_chunks(a.g, grid, sizeof(T) == 4, [&](const dim3& gq, const Geom& gg) {
@@ -1199,9 +1381,8 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
             });
         });
     }
-    const unsigned cap = sizeof(T) == 4 && a.g.nx > 256 && a.g.nx <= 512 ? kLdsFourPerCu : 0u;
-    if (var) k_step<S, W, LES, FF, true, false, 0><<<grid, bx, cap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
-    else k_step<S, W, LES, FF, false, false, 0><<<grid, bx, cap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
+    if (var) k_step<S, W, LES, FF, true, false, 0><<<grid, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
+    else k_step<S, W, LES, FF, false, false, 0><<<grid, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
     return hipGetLastError();
 }
 
@@ -1254,6 +1435,19 @@ static hipError_t step_sgs_t(const LaunchArgs& a, const void* src, void* dst) {
     if (a.xcd_default && g.xcd >= 2) g.xcd = 0;
     // FP32 rows of one workgroup in chunks of planes, as the step without the
     // stress force (256^3: 769.4 -> 761.2 us)
+    if (whole_rows(g, sizeof(T))) {
+        const bool direct = (size_t)g.nx * sizeof(T) % 128 == 0;
+        return launch_z_chunks(g, dim3(1, g.ny, g.nz), sizeof(T) == 4, [&](const dim3& gq, const Geom& gg) {
+            auto launch = [&](auto v, auto d) {
+                k_step_row<S, false, false, FF, decltype(v)::value, true, decltype(d)::value>
+                    <<<gq, row_lanes(gg), row_lds<T>(gg), st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L, rp, rn);
+            };
+            if (var && direct) launch(std::true_type(), std::true_type());
+            else if (var) launch(std::true_type(), std::false_type());
+            else if (direct) launch(std::false_type(), std::true_type());
+            else launch(std::false_type(), std::false_type());
+        });
+    }
     return launch_z_chunks(g, grid, sizeof(T) == 4 && xl, [&](const dim3& gq, const Geom& gg) {
         if (xl) {
             with_row_width(bx, [&](auto w) {
@@ -1281,7 +1475,8 @@ hipError_t step_w(const LaunchArgs& a, const void* src, void* dst) {
         if (a.walls || !a.stress_prev || !a.stress_next) return hipErrorInvalidValue;   // checked by the caller
         return a.force_field ? step_sgs_t<S, true>(a, src, dst) : step_sgs_t<S, false>(a, src, dst);
     }
-    if (one_block_per_row(a.g)) return a.walls ? step_les<S, true>(a, src, dst) : step_les<S, false>(a, src, dst);
+    if (whole_rows(a.g, sizeof(typename Store<S>::T)) || one_block_per_row(a.g))
+        return a.walls ? step_les<S, true>(a, src, dst) : step_les<S, false>(a, src, dst);
     return split_wall_rows(a, [&](const LaunchArgs& b, bool w) {
         return w ? step_les<S, true>(b, src, dst) : step_les<S, false>(b, src, dst);
     });
@@ -1463,7 +1658,6 @@ __global__ void __launch_bounds__(256) k_reduce_final(const double* __restrict__
 // and 6.49 with 256-thread workgroups, 6.35 with 512, 6.18 with 1024, 6.21-6.26
 // with an ordinary load; two or more vectors per thread and grid-stride loops
 // were slower still, 4.1-6.1 TB/s).
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 __global__ void __launch_bounds__(256) k_zero(unsigned int* __restrict__ dst, size_t n) {
     const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k < n) dst[k] = 0u;

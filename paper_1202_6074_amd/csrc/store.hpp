@@ -22,18 +22,25 @@ template <> struct Store<3> { using T = _Float16; using R = float;  static const
 // xcd = 1: XCD k takes the k-th contiguous eighth of the blocks (in x, y, z
 // order), so that rows that share data (x-halo cache lines, neighbouring
 // stress rows) are read through one L2; xcd = R >= 2: runs of R consecutive
-// blocks go to the XCDs in turn (8 R blocks per round). Orders whose block
-// count does not divide fall back to the plain one. Any bijection is correct;
-// this one only changes which L2 serves a block and when.
+// blocks go to the XCDs in turn (8 R blocks per round; the blocks after the last
+// full round in the plain order). Any bijection is correct; this one only
+// changes which L2 serves a block and when.
 __device__ __forceinline__ void block_coords(int xcd, int& bx, int& y, int& z) {
+    if (xcd == 0) {
+        bx = (int)blockIdx.x;
+        y = (int)blockIdx.y;
+        z = (int)blockIdx.z;
+        return;
+    }
     const uint32_t gx = gridDim.x, gy = gridDim.y, gz = gridDim.z;
     uint32_t lin = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
     const uint32_t total = gx * gy * gz;
-    if (xcd == 1 && (total & 7u) == 0u) {
-        lin = (lin & 7u) * (total >> 3) + (lin >> 3);
-    } else if (xcd >= 2 && total % (8u * (uint32_t)xcd) == 0u) {
+    if (xcd == 1) {
+        const uint32_t k = lin & 7u, rest = total & 7u;   // the first `rest` eighths are one longer
+        lin = k * (total >> 3) + (k < rest ? k : rest) + (lin >> 3);
+    } else {
         const uint32_t run = (uint32_t)xcd, round = lin / (8u * run), k = lin % (8u * run);
-        lin = round * 8u * run + (k & 7u) * run + (k >> 3);
+        if ((round + 1u) * 8u * run <= total) lin = round * 8u * run + (k & 7u) * run + (k >> 3);
     }
     bx = (int)(lin % gx);
     const uint32_t r = lin / gx;

@@ -54,3 +54,27 @@ def test_row_widths(storage, nx):
     for flags in ({}, {"factorized": True, "reduced_compressibility": True}, {"sgs_force": True}):
         a, b = _states((nx, 4, 3), storage, False, 3, (0, 32), flags=flags)
         assert torch.equal(a, b)
+
+
+# lattices of more than 16 MB a buffer, where rows that do not start on cache
+# lines go through LDS whole: rows of an odd length, one vector more or less
+# than whole workgroups, rows whose blocks start on every misalignment of a
+# 16-byte vector, and the widths of 257 to 512 cells (aligned and not)
+@pytest.mark.parametrize("storage", ["f64", "f32", "f32s", "f16s"])
+@pytest.mark.parametrize("nx", [17, 63, 65, 130, 187, 255, 257, 300, 320, 511, 512])
+@pytest.mark.parametrize("walls", [False, True])
+def test_whole_rows_through_lds(storage, nx, walls):
+    torch = _torch()
+    ny = -(-(17 << 20) // (27 * nx * 5 * {"f64": 8, "f32": 4, "f32s": 4, "f16s": 2}[storage]))
+    for force, les, flags in ((True, True, {}), (False, False, {"factorized": True, "reduced_compressibility": True})):
+        a, b = _states((nx, ny, 5), storage, walls, 2, (0, 32), force, les, flags)
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("nx", [130, 187, 300, 384])
+def test_whole_rows_with_the_sub_grid_force(storage, nx):
+    torch = _torch()
+    ny = -(-(17 << 20) // (27 * nx * 5 * {"f64": 8, "f32": 4, "f16s": 2}[storage]))
+    a, b = _states((nx, ny, 5), storage, False, 3, (0, 32), flags={"sgs_force": True})
+    assert torch.equal(a, b)
