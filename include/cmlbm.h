@@ -289,8 +289,7 @@ cmlbm_status cmlbm_reduce(cmlbm_handle h, double out[8]);
  * out: DEVICE array of 8 doubles, overwritten with the same quantities as
  * cmlbm_reduce's out (non-finite cells are counted in out[5]; the status does
  * not report them, since nothing is read back). The results equal
- * cmlbm_reduce's up to FP64 rounding (the cells are summed in another
- * order), and are themselves deterministic.
+ * cmlbm_reduce's up to FP64 rounding, and are themselves deterministic.
  * Scratch: a static device array of CMLBM_REDUCE_NOALLOC_SCRATCH_BYTES that
  * each device holds from the first call on it until the process ends; the
  * partial-sum kernel launches at most 1024 workgroups, each combining several

@@ -2,10 +2,10 @@
 // alternation and error reporting. Device work lives in kernels.hip.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <string>
 
@@ -17,8 +17,8 @@ struct cmlbm_lattice {
     void* buf[2];
     int cur;             // index of the buffer holding the current state
     size_t bytes_each;
-    double* scratch;     // reduction partials followed by 8 result slots
-    size_t nparts;
+    double* scratch;     // reduction partials
+    double* result;      // host memory that the device writes the 8 reduced values to (ResultSlots)
     void* stress[2];     // sub-grid stress buffers (caller-owned); stress[k] pairs with buf[k]
     size_t stress_bytes;
     int device;          // device current at creation (the handle's work runs there)
@@ -102,6 +102,43 @@ int default_xcd_order(int lattice, int storage, int nx, bool rowloop, bool walls
     }
     return lattice == CMLBM_D3Q27 && four_byte && !rowloop && !walls && nx > 128 ? kXcdRun : 0;
 }
+
+// Host memory that devices write reduced values to: 64 slots of 8 doubles in one
+// page, allocated with the first handle and held until the process ends (an
+// allocation for each handle made its creation 0.1 ms longer); handles beyond
+// the 64th get memory of their own.
+class ResultSlots {
+public:
+    hipError_t take(double** out) {
+        std::lock_guard<std::mutex> lock(mu_);
+        if (!page_) {
+            const hipError_t e = hipHostMalloc((void**)&page_, 64 * kBytes, hipHostMallocPortable);
+            if (e != hipSuccess) return e;
+        }
+        for (int k = 0; k < 64; ++k)
+            if (!(used_ >> k & 1u)) {
+                used_ |= (uint64_t)1 << k;
+                *out = page_ + 8 * k;
+                return hipSuccess;
+            }
+        return hipHostMalloc((void**)out, kBytes, hipHostMallocPortable);
+    }
+    hipError_t give_back(double* p) {
+        std::lock_guard<std::mutex> lock(mu_);
+        if (page_ && p >= page_ && p < page_ + 8 * 64) {
+            used_ &= ~((uint64_t)1 << ((p - page_) / 8));
+            return hipSuccess;
+        }
+        return hipHostFree(p);
+    }
+
+private:
+    static constexpr size_t kBytes = 8 * sizeof(double);
+    std::mutex mu_;
+    double* page_ = nullptr;
+    uint64_t used_ = 0;
+};
+ResultSlots g_results;
 
 cmlbm_status check_handle(cmlbm_handle h) {
     if (!h) return fail(CMLBM_EINVAL, "null handle");
@@ -233,11 +270,14 @@ cmlbm_status cmlbm_create(const cmlbm_desc* d, void* buf_a, void* buf_b, size_t 
     h->buf[1] = buf_b;
     h->cur = 0;
     h->bytes_each = bytes_each;
-    h->nparts = cm::reduce_partials(a.g);
-    hipError_t e = hipMalloc((void**)&h->scratch, sizeof(double) * (8 * h->nparts + 8));
+    hipError_t e = hipMalloc((void**)&h->scratch, sizeof(double) * 8 * cm::kReduceBlocks);
+    if (e == hipSuccess) {
+        e = g_results.take(&h->result);
+        if (e != hipSuccess) (void)hipFree(h->scratch);
+    }
     if (e != hipSuccess) {
         delete h;
-        return hip_fail(e, "hipMalloc(reduction scratch)");
+        return hip_fail(e, "allocation of the reduction scratch");
     }
     *out = h;
     return CMLBM_OK;
@@ -250,6 +290,8 @@ cmlbm_status cmlbm_destroy(cmlbm_handle h) {
         // the scratch may still be in use by work queued on the stream
         e = hipStreamSynchronize((hipStream_t)h->a.stream);
         hipError_t e2 = hipFree(h->scratch);
+        if (e == hipSuccess) e = e2;
+        e2 = g_results.give_back(h->result);   // no queued work writes to it any more
         if (e == hipSuccess) e = e2;
     }
     delete h;
@@ -391,12 +433,12 @@ cmlbm_status cmlbm_reduce(cmlbm_handle h, double out[8]) {
     if (!out) return fail(CMLBM_EINVAL, "out must be non-null");
     if (cmlbm_status s = check_sgs_ready(h)) return s;
     bind_stress(h);
-    double* res = h->scratch + 8 * h->nparts;
-    hipError_t e = h->a.lattice ? cm2::launch_reduce(h->a, h->buf[h->cur], h->scratch, res)
-                                : cm::launch_reduce(h->a, h->buf[h->cur], h->scratch, res);
-    if (e == hipSuccess) e = hipMemcpyAsync(out, res, 8 * sizeof(double), hipMemcpyDeviceToHost, (hipStream_t)h->a.stream);
+    // the last kernel writes the values to host memory: no copy to wait for
+    hipError_t e = h->a.lattice ? cm2::launch_reduce(h->a, h->buf[h->cur], h->scratch, h->result)
+                                : cm::launch_reduce(h->a, h->buf[h->cur], h->scratch, h->result);
     if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)h->a.stream);
     if (e != hipSuccess) return hip_fail(e, "reduce");
+    std::memcpy(out, h->result, 8 * sizeof(double));
     if (out[5] > 0) {
         char msg[96];
         std::snprintf(msg, sizeof msg, "%.0f cells with non-finite rho or u", out[5]);
@@ -412,14 +454,10 @@ cmlbm_status cmlbm_reduce_noalloc(cmlbm_handle h, double* out) {
     double* scratch = nullptr;
     hipError_t e = cm::static_reduce_scratch(h->device, &scratch);
     if (e != hipSuccess) return hip_fail(e, "reduce_noalloc: address of the static scratch");
-    // the partial kernel launches at most kStaticReduceBlocks workgroups, so
-    // every lattice fits; the check guards the array's size against changes
-    const size_t nparts = std::min(h->nparts, cm::kStaticReduceBlocks);
-    if (nparts > cm::kStaticReduceBlocks) return fail(CMLBM_EINVAL, "reduce_noalloc: partials exceed the static scratch");
     bind_stress(h);
     // partials in the static scratch, the final combination straight into out
-    e = h->a.lattice ? cm2::launch_reduce(h->a, h->buf[h->cur], scratch, out, cm::kStaticReduceBlocks)
-                     : cm::launch_reduce(h->a, h->buf[h->cur], scratch, out, cm::kStaticReduceBlocks);
+    e = h->a.lattice ? cm2::launch_reduce(h->a, h->buf[h->cur], scratch, out)
+                     : cm::launch_reduce(h->a, h->buf[h->cur], scratch, out);
     return e == hipSuccess ? CMLBM_OK : hip_fail(e, "reduce_noalloc");
 }
 

@@ -303,13 +303,15 @@ __device__ __forceinline__ void gather(const typename Store<S>::T* src, const Ge
     }
 }
 
-// Gather in the mode the geometry's streaming state asks for (read-out kernels).
+// Gather in the mode the geometry's streaming state asks for (read-out kernels;
+// ordinary loads of the x-shifted rows, whose lines the neighbouring wave reads
+// too: reductions of 512 x 512 x 128 FP16 531 us non-temporal, 458 ordinary).
 template <int S, bool WALLS, typename R = typename Store<S>::R>
 __device__ __forceinline__ void gather_any(const typename Store<S>::T* src, const Geom g, int x, int y, int z,
                                            const Launch<R>& L, R (&h)[27]) {
-    if (g.aa == 0) gather<S, WALLS, 0>(src, g, x, y, z, L, h);
-    else if (g.aa == 1) gather<S, WALLS, 1>(src, g, x, y, z, L, h);
-    else gather<S, WALLS, 2>(src, g, x, y, z, L, h);
+    if (g.aa == 0) gather<S, WALLS, 0, false>(src, g, x, y, z, L, h);
+    else if (g.aa == 1) gather<S, WALLS, 1, false>(src, g, x, y, z, L, h);
+    else gather<S, WALLS, 2, false>(src, g, x, y, z, L, h);
 }
 
 // Gather of the two-buffer pull scheme when one workgroup covers a whole grid
@@ -387,6 +389,15 @@ __device__ __forceinline__ void add_wall_terms(const Geom& g, int y, const Launc
     }
 }
 
+// The deviations h of the stored values t gathered at a cell of row y.
+template <int S, bool WALLS, typename R = typename Store<S>::R>
+__device__ __forceinline__ void stored_devs(const typename Store<S>::T (&t)[27], const Geom& g, int y, const Launch<R>& L,
+                                            R (&h)[27]) {
+#pragma unroll
+    for (int i = 0; i < 27; ++i) h[i] = from_store<S>(t[i], i, L.P.rho0);
+    if constexpr (WALLS) add_wall_terms(g, y, L, h);
+}
+
 // The z-line sums that collide_lines starts from, of the stored values t
 // gathered at a cell of row y.
 template <int S, bool WALLS, typename R = typename Store<S>::R>
@@ -403,10 +414,92 @@ __device__ __forceinline__ void stored_line_sums(const typename Store<S>::T (&t)
             return;
         }
     }
-#pragma unroll
-    for (int i = 0; i < 27; ++i) h[i] = from_store<S>(t[i], i, L.P.rho0);
-    if constexpr (WALLS) add_wall_terms(g, y, L, h);
+    stored_devs<S, WALLS>(t, g, y, L, h);
     zline_sums(h, ls, ld);
+}
+
+// ---------------------------------------------------------------- whole rows through LDS
+// Direct copy of 16 bytes a lane from global memory to LDS: lane l of a wave
+// writes at `lds` + 16 l (lds the same for the whole wave), without a vector
+// register in between. Complete after wait_lds_copies, for the wave's own
+// copies; a barrier after it makes them visible to the workgroup.
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+template <typename P>
+__device__ __forceinline__ void copy16_to_lds(P src, void* lds) {
+    constexpr int kNonTemporal = 2;   // cache policy bit of the instruction
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                     (__attribute__((address_space(3))) void*)lds, 16, 0, kNonTemporal);
+}
+__device__ __forceinline__ void wait_lds_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Elements of LDS that hold a group of three adjacent rows of nx values with up
+// to one 16-byte vector of misalignment, in whole vectors.
+template <typename T>
+__host__ __device__ constexpr uint32_t group_stride(uint32_t nx) {
+    constexpr uint32_t V = 16 / sizeof(T);
+    return (3u * nx + 2u * V - 1u) / V * V;
+}
+
+// Stores a block of n values at D, held in LDS from element o on (o the
+// misalignment of D, so that LDS and memory vectors coincide): whole vectors
+// non-temporal, the values of the vectors at the ends one by one (a block
+// shorter than a vector has only those).
+template <typename T>
+__device__ __forceinline__ void store_block(T* D, uint32_t o, uint32_t n, const T* sm, uint32_t tid, uint32_t bd) {
+    constexpr uint32_t V = 16 / sizeof(T);
+    T* const D0 = D - o;   // the block's first vector
+    const uint32_t end = o + n, c1 = end / V;
+    for (uint32_t c = tid + (o ? 1u : 0u); c < c1; c += bd)
+        __builtin_nontemporal_store(((const u32x4*)sm)[c], at_row((u32x4*)D0, c * 16u));
+    if (o && tid >= o && tid < V && tid < end) D0[tid] = sm[tid];
+    const uint32_t tail = c1 * V + tid;
+    if (tail < end && (c1 || !o)) D0[tail] = sm[tail];
+}
+
+// Gather of the two-buffer pull scheme for a workgroup that holds a whole grid
+// row, lane = cell, at any alignment: in memory the three populations of a source
+// row that differ only in e_x are one contiguous block of 3 nx values; the nine
+// blocks are copied straight into LDS (`sm`, 9 group_stride values) as 16-byte
+// vectors of 16-byte-aligned addresses, and each lane reads its 27 values there,
+// shifted by e_x. other() is called between the copies and the wait for them. A
+// vector at either end of a block can hold values outside it, which are not
+// used: an aligned vector with one valid byte lies in a mapped page.
+// t: the stored values as the step kernels' other gathers give them. Idle lanes
+// (x = 0) take part; every lane of the workgroup must call this.
+template <int S, bool WALLS, typename Other>
+__device__ __forceinline__ void gather_rows(const typename Store<S>::T* __restrict__ src, const Geom& g, uint32_t x, int y,
+                                            int z, typename Store<S>::T* sm, typename Store<S>::T (&t)[27], Other&& other) {
+    using T = typename Store<S>::T;
+    constexpr uint32_t V = 16 / sizeof(T);
+    const uint32_t tid = threadIdx.x, bd = blockDim.x, nx = (uint32_t)g.nx;
+    const uint32_t wave0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid & ~63u));
+    const int ys[3] = {y == g.ny - 1 ? 0 : y + 1, y, y == 0 ? g.ny - 1 : y - 1};
+    const int zs[3] = {z == g.nz - 1 ? 0 : z + 1, z, z == 0 ? g.nz - 1 : z - 1};
+    // group q = (e_x = -1, 0, 1) of (e_y, e_z); from a wall the opposite group of
+    // the own row, its three populations in reverse order and not shifted
+    auto bounce = [&](int q) { return WALLS && ((q % 3 == 2 && y == 0) || (q % 3 == 0 && y == g.ny - 1)); };
+    const uint32_t gs = group_stride<T>(nx);
+    uint32_t off[9];   // misalignment of each group, in elements
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        const bool w = bounce(q);
+        const T* A = src + row_base(g, w ? 24 - 3 * q : 3 * q, w ? y : ys[q % 3], w ? z : zs[q / 3]);
+        off[q] = (uint32_t)((uintptr_t)A & 15u) / (uint32_t)sizeof(T);
+        const u32x4* base = (const u32x4*)((uintptr_t)A & ~(uintptr_t)15);
+        const uint32_t n = (off[q] + 3u * nx + V - 1u) / V;
+        for (uint32_t k = 0; k < n; k += bd)   // one pass, two for FP64
+            if (tid + k < n)
+                copy16_to_lds(at_row(base, (tid + k) * 16u), (unsigned char*)sm + 16u * (q * (gs / V) + k + wave0));
+    }
+    other();
+    wait_lds_copies();
+    __syncthreads();
+    const uint32_t xs[3] = {x + 1u >= nx ? 0u : x + 1u, nx + x, 2u * nx + (x == 0u ? nx - 1u : x - 1u)};   // x - e_x
+#pragma unroll
+    for (int i = 0; i < 27; ++i) {
+        const int ix = i % 3, q = i / 3;
+        t[i] = sm[q * gs + off[q] + (bounce(q) ? x + (uint32_t)(2 - ix) * nx : xs[ix])];
+    }
 }
 
 template <typename R, bool FFIELD>
@@ -558,57 +651,14 @@ __global__ void __launch_bounds__(256, (S == 3 && !SGS) ? 5 : 1) k_step(const ty
 }
 
 // ---------------------------------------------------------------- step, whole rows through LDS
-// Direct copy of 16 bytes a lane from global memory to LDS: lane l of a wave
-// writes at `lds` + 16 l (lds the same for the whole wave), without a vector
-// register in between. Complete after wait_lds_copies, for the wave's own
-// copies; a barrier after it makes them visible to the workgroup.
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-template <typename P>
-__device__ __forceinline__ void copy16_to_lds(P src, void* lds) {
-    constexpr int kNonTemporal = 2;   // cache policy bit of the instruction
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                     (__attribute__((address_space(3))) void*)lds, 16, 0, kNonTemporal);
-}
-__device__ __forceinline__ void wait_lds_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// Elements of LDS that hold a group of three adjacent rows of nx values with up
-// to one 16-byte vector of misalignment, in whole vectors.
-template <typename T>
-__host__ __device__ constexpr uint32_t group_stride(uint32_t nx) {
-    constexpr uint32_t V = 16 / sizeof(T);
-    return (3u * nx + 2u * V - 1u) / V * V;
-}
-
-// Stores a block of n values at D, held in LDS from element o on (o the
-// misalignment of D, so that LDS and memory vectors coincide): whole vectors
-// non-temporal, the values of the vectors at the ends one by one.
-template <typename T>
-__device__ __forceinline__ void store_block(T* D, uint32_t o, uint32_t n, const T* sm, uint32_t tid, uint32_t bd) {
-    constexpr uint32_t V = 16 / sizeof(T);
-    T* const D0 = D - o;   // the block's first vector
-    const uint32_t end = o + n, c1 = end / V;
-    for (uint32_t c = tid + (o ? 1u : 0u); c < c1; c += bd)
-        __builtin_nontemporal_store(((const u32x4*)sm)[c], at_row((u32x4*)D0, c * 16u));
-    if (o && tid >= o && tid < V) D0[tid] = sm[tid];
-    const uint32_t tail = c1 * V + tid;
-    if (tail < end) D0[tail] = sm[tail];
-}
-
 // The step on rows that do not start on cache lines (or are wider than 256
-// cells): one workgroup per grid row, lane = cell, and the row's populations go
-// through LDS in both directions. In memory the three populations of a source
-// row that differ only in e_x are one contiguous block of 3 nx values, and the
-// 27 rows that the cell row writes are one block of 27 nx; both are moved as
-// 16-byte vectors of 16-byte-aligned addresses whatever nx is, the reads
-// straight into LDS and without passing through registers. What a lane reads
-// from LDS is shifted by e_x, what it writes is its own column.
+// cells): one workgroup per grid row, and the row's populations go through LDS
+// in both directions, in (gather_rows) as nine blocks of 3 nx values, out as
+// the one block of 27 nx values that the 27 rows of a cell row are.
 // Bound by HBM; per-lane accesses to such rows touch three lines instead of two
 // per wave in most rows and write partial lines, which non-temporal stores send
-// to memory one by one.
-// A vector at either end of a block can hold values outside it. Reading them
-// is harmless (an aligned vector with one valid byte lies in a mapped page; the
-// values are not used); they are not written: the ends of the row's block are
-// stored value by value.
+// to memory one by one. Vectors through registers instead of straight into LDS:
+// 383 us per step at 250 x 200 x 200 FP32, against 367-374.
 // DIRECT: rows that do start on cache lines: each lane stores its own values (no
 // partial lines to avoid, and one barrier less).
 template <int S, bool WALLS, bool LES, bool FFIELD, bool VAR, bool SGS, bool DIRECT>
@@ -620,45 +670,20 @@ __global__ void __launch_bounds__(512) k_step_row(const typename Store<S>::T* __
                                                   typename Store<S>::R* __restrict__ rs_next = nullptr) {
     using R = typename Store<S>::R;
     using T = typename Store<S>::T;
-    constexpr uint32_t V = 16 / sizeof(T);
     extern __shared__ __align__(16) unsigned char lds_bytes[];
     T* const sm = (T*)lds_bytes;
     int bx, y, z;
     block_coords(g.xcd, bx, y, z);
     z += g.zbase;
-    const uint32_t tid = threadIdx.x, bd = blockDim.x, nx = (uint32_t)g.nx;
-    const uint32_t wave0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid & ~63u));
+    const uint32_t tid = threadIdx.x, nx = (uint32_t)g.nx;
     const bool act = tid < nx;
-    const uint32_t x = act ? tid : 0u;   // idle lanes compute cell 0 and store nothing
-    const int ys[3] = {y == g.ny - 1 ? 0 : y + 1, y, y == 0 ? g.ny - 1 : y - 1};
-    const int zs[3] = {z == g.nz - 1 ? 0 : z + 1, z, z == 0 ? g.nz - 1 : z - 1};
-    // group q = (e_x = -1, 0, 1) of (e_y, e_z); from a wall the opposite group of
-    // the own row, its three populations in reverse order and not shifted
-    auto bounce = [&](int q) { return WALLS && ((q % 3 == 2 && y == 0) || (q % 3 == 0 && y == g.ny - 1)); };
-    const uint32_t gs = group_stride<T>(nx);
-    uint32_t off[9];   // misalignment of each group, in elements
-#pragma unroll
-    for (int q = 0; q < 9; ++q) {
-        const bool w = bounce(q);
-        const T* A = src + row_base(g, w ? 24 - 3 * q : 3 * q, w ? y : ys[q % 3], w ? z : zs[q / 3]);
-        off[q] = (uint32_t)((uintptr_t)A & 15u) / (uint32_t)sizeof(T);
-        const u32x4* base = (const u32x4*)((uintptr_t)A & ~(uintptr_t)15);
-        const uint32_t n = (off[q] + 3u * nx + V - 1u) / V;
-        for (uint32_t k = 0; k < n; k += bd)   // one pass, two for FP64
-            if (tid + k < n) copy16_to_lds(at_row(base, (tid + k) * 16u), lds_bytes + 16u * (q * (gs / V) + k + wave0));
-    }
+    const uint32_t x = act ? tid : 0u;
     R sv[SGS ? 18 : 1], F[3];
-    if constexpr (SGS) sgs_load<R, false>(rs_prev, g, (int)x, y, z, sv);
-    row_force<R, FFIELD, false>(force, g, L, (int)x, y, z, F);
-    wait_lds_copies();
-    __syncthreads();
-    const uint32_t xs[3] = {x + 1u >= nx ? 0u : x + 1u, nx + x, 2u * nx + (x == 0u ? nx - 1u : x - 1u)};   // x - e_x
     T t[27];
-#pragma unroll
-    for (int i = 0; i < 27; ++i) {
-        const int ix = i % 3, q = i / 3;
-        t[i] = sm[q * gs + off[q] + (bounce(q) ? x + (uint32_t)(2 - ix) * nx : xs[ix])];
-    }
+    gather_rows<S, WALLS>(src, g, x, y, z, sm, t, [&]() {
+        if constexpr (SGS) sgs_load<R, false>(rs_prev, g, (int)x, y, z, sv);
+        row_force<R, FFIELD, false>(force, g, L, (int)x, y, z, F);
+    });
     R h[27], ls[9], ld[9];
     stored_line_sums<S, WALLS>(t, g, y, L, h, ls, ld);
     R acc[3];
@@ -681,7 +706,7 @@ __global__ void __launch_bounds__(512) k_step_row(const typename Store<S>::T* __
             }
         }
         __syncthreads();
-        store_block<T>(D, o, 27u * nx, sm, tid, bd);
+        store_block<T>(D, o, 27u * nx, sm, tid, blockDim.x);
     }
 }
 
@@ -909,63 +934,141 @@ __device__ __forceinline__ void scatter(typename Store<S>::T* __restrict__ dst, 
     }
 }
 
-template <int S, bool WALLS, bool FFIELD>
-__global__ void __launch_bounds__(256) k_init_equilibrium(typename Store<S>::T* __restrict__ dst,
+// The same for a workgroup that holds a whole grid row (lane = cell, h of lanes
+// with `act`), through LDS: scattered by the lanes, the populations with e_x != 0
+// write rows shifted by one value, partial lines at every wave's ends and, where
+// rows do not start on cache lines, everywhere. Here the three populations that
+// go to one target row, a contiguous block, are put together in LDS (`sm`, 3
+// group_stride values) and stored in whole vectors, the targets of one e_z at
+// a time. Before / after, us: start of 256^3 FP32 449 / 411, of
+// 300 x 181 x 90 FP32-shifted 274 / 124, of 187 x 151 x 133 FP16 134 / 69;
+// set_populations (FP64 values) of 300 x 181 x 90 443 / 301.
+template <int S, bool WALLS, typename R = typename Store<S>::R>
+__device__ __forceinline__ void push_rows(typename Store<S>::T* __restrict__ dst, const Geom g, uint32_t x, bool act,
+                                          int y, int z, const Launch<R>& L, const R (&h)[27],
+                                          typename Store<S>::T* sm) {
+    using T = typename Store<S>::T;
+    const uint32_t nx = (uint32_t)g.nx, gs = group_stride<T>(nx);
+    const int ys[3] = {y == g.ny - 1 ? 0 : y + 1, y, y == 0 ? g.ny - 1 : y - 1};
+    const int zs[3] = {z == g.nz - 1 ? 0 : z + 1, z, z == 0 ? g.nz - 1 : z - 1};
+    const bool own = g.aa != 0;   // in place: every population stays in the cell's own rows
+    const uint32_t xs[3] = {own ? x : (x + 1u >= nx ? 0u : x + 1u), nx + x,
+                            2u * nx + (own ? x : (x == 0u ? nx - 1u : x - 1u))};
+#pragma unroll
+    for (int iz = 0; iz < 3; ++iz) {
+        T* D[3];
+        uint32_t o[3];
+#pragma unroll
+        for (int iy = 0; iy < 3; ++iy) {
+            const int q = 3 * iz + iy;
+            const bool lo = WALLS && iy == 2 && y == 0, hi = WALLS && iy == 0 && y == g.ny - 1;
+            const bool bounce = (lo || hi) && !own;
+            D[iy] = dst + row_base(g, bounce ? 24 - 3 * q : 3 * q, own || bounce ? y : ys[iy], own || bounce ? z : zs[iz]);
+            o[iy] = (uint32_t)((uintptr_t)D[iy] & 15u) / (uint32_t)sizeof(T);
+            if (act) {
+#pragma unroll
+                for (int ix = 0; ix < 3; ++ix) {
+                    const int i = 3 * q + ix;
+                    R v = h[i];
+                    if (lo || hi) v = sub_rn(v, lo ? L.wt_lo[i] : L.wt_hi[i]);
+                    // w_i = w_{26-i}: the shift of the stored value is the same
+                    sm[iy * gs + o[iy] + (bounce ? (uint32_t)(2 - ix) * nx + x : xs[ix])] = to_store<S>(v, i, L.P.rho0);
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int iy = 0; iy < 3; ++iy) store_block<T>(D[iy], o[iy], 3u * nx, sm + iy * gs, threadIdx.x, blockDim.x);
+        if (iz < 2) __syncthreads();
+    }
+}
+
+// Writes h of cell (x, y, z): ROWS, through LDS by the workgroup that covers the
+// row, else by each lane for itself.
+template <int S, bool WALLS, bool ROWS, typename R = typename Store<S>::R>
+__device__ __forceinline__ void put_state(typename Store<S>::T* __restrict__ dst, const Geom g, int x, bool act, int y, int z,
+                                          const Launch<R>& L, const R (&h)[27]) {
+    if constexpr (ROWS) {
+        extern __shared__ __align__(16) unsigned char lds_bytes[];
+        push_rows<S, WALLS>(dst, g, (uint32_t)x, act, y, z, L, h, (typename Store<S>::T*)lds_bytes);
+    } else {
+        if (act) scatter<S, WALLS>(dst, g, x, y, z, L, h);
+    }
+}
+
+template <int S, bool WALLS, bool FFIELD, bool ROWS>
+__global__ void __launch_bounds__(ROWS ? 512 : 256) k_init_equilibrium(typename Store<S>::T* __restrict__ dst,
                                                           const typename Store<S>::R* __restrict__ force,
                                                           const void* __restrict__ rho_in, const void* __restrict__ u_in,
                                                           int dt, const Geom g, const Launch<typename Store<S>::R> L) {
     using R = typename Store<S>::R;
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     const int y = blockIdx.y, z = blockIdx.z;
-    if (x >= g.nx) return;
-    const int c = x + g.nx * (y + g.ny * z);
-    const R rho = rho_in ? static_cast<R>(as_double(rho_in, dt, c)) : L.P.rho0;
-    const R ux = static_cast<R>(as_double(u_in, dt, c));
-    const R uy = static_cast<R>(as_double(u_in, dt, (size_t)g.N + c));
-    const R uz = static_cast<R>(as_double(u_in, dt, 2 * (size_t)g.N + c));
-    R Fx, Fy, Fz;
-    cell_force<R, FFIELD>(force, g, c, L, Fx, Fy, Fz);
+    const bool act = x < g.nx;
     R h[27];
-    equilibrium(h, rho, ux, uy, uz, Fx, Fy, Fz, L.P.rho0, L.P.rc != 0);
-    scatter<S, WALLS>(dst, g, x, y, z, L, h);
+    if (act) {
+        const int c = x + g.nx * (y + g.ny * z);
+        const R rho = rho_in ? static_cast<R>(as_double(rho_in, dt, c)) : L.P.rho0;
+        const R ux = static_cast<R>(as_double(u_in, dt, c));
+        const R uy = static_cast<R>(as_double(u_in, dt, (size_t)g.N + c));
+        const R uz = static_cast<R>(as_double(u_in, dt, 2 * (size_t)g.N + c));
+        R Fx, Fy, Fz;
+        cell_force<R, FFIELD>(force, g, c, L, Fx, Fy, Fz);
+        equilibrium(h, rho, ux, uy, uz, Fx, Fy, Fz, L.P.rho0, L.P.rc != 0);
+    }
+    put_state<S, WALLS, ROWS>(dst, g, x, act, y, z, L, h);
 }
 
-template <int S, bool WALLS>
-__global__ void __launch_bounds__(256) k_set_populations(typename Store<S>::T* __restrict__ dst,
+template <int S, bool WALLS, bool ROWS>
+__global__ void __launch_bounds__(ROWS ? 512 : 256) k_set_populations(typename Store<S>::T* __restrict__ dst,
                                                          const void* __restrict__ f, int dt, const Geom g,
                                                          const Launch<typename Store<S>::R> L) {
     using R = typename Store<S>::R;
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     const int y = blockIdx.y, z = blockIdx.z;
-    if (x >= g.nx) return;
-    const int c = x + g.nx * (y + g.ny * z);
+    const bool act = x < g.nx;
     R h[27];
+    if (act) {
+        const int c = x + g.nx * (y + g.ny * z);
 #pragma unroll
-    for (int i = 0; i < 27; ++i)
-        h[i] = static_cast<R>(as_double(f, dt, (size_t)i * g.N + c) - (double)L.P.rho0 * (double)w27<double>(i));
-    scatter<S, WALLS>(dst, g, x, y, z, L, h);
+        for (int i = 0; i < 27; ++i)
+            h[i] = static_cast<R>(as_double(f, dt, (size_t)i * g.N + c) - (double)L.P.rho0 * (double)w27<double>(i));
+    }
+    put_state<S, WALLS, ROWS>(dst, g, x, act, y, z, L, h);
 }
 
 // ---------------------------------------------------------------- read-out
-// mode 0: canonical populations into out0 (27 planes); mode 1: rho into out0
-// (1 plane) and u into out1 (3 planes)
-template <int S, bool WALLS, bool FFIELD>
-__global__ void __launch_bounds__(256) k_read(const typename Store<S>::T* __restrict__ src,
-                                              const typename Store<S>::R* __restrict__ force, void* __restrict__ out0,
-                                              void* __restrict__ out1, int dt, int mode, const Geom g,
+// Canonical populations into out0 (27 planes), or, with MOMENTS, rho into out0
+// (1 plane) and u into out1 (3 planes), as OUT values. ROWS: the workgroup
+// covers the row and gathers through LDS. NT: non-temporal stores, for rows of
+// whole 32-byte sectors; others share sectors between waves (us, ordinary /
+// non-temporal: populations of 300 x 181 x 90 FP32 484 / 428, of 201 x 160 x 100
+// FP64 313 / 343).
+template <int S, bool WALLS, bool FFIELD, bool MOMENTS, bool ROWS, bool NT, typename OUT>
+__global__ void __launch_bounds__(ROWS ? 512 : 256) k_read(const typename Store<S>::T* __restrict__ src,
+                                              const typename Store<S>::R* __restrict__ force, OUT* __restrict__ out0,
+                                              OUT* __restrict__ out1, const Geom g,
                                               const Launch<typename Store<S>::R> L) {
     using R = typename Store<S>::R;
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     const int y = blockIdx.y, z = blockIdx.z;
-    if (x >= g.nx) return;
-    const int c = x + g.nx * (y + g.ny * z);
     R h[27];
-    gather_any<S, WALLS>(src, g, x, y, z, L, h);
-    auto put = [&](void* out, size_t k, double v) {
-        if (dt == 0) static_cast<double*>(out)[k] = v;
-        else static_cast<float*>(out)[k] = static_cast<float>(v);
+    if constexpr (ROWS) {
+        extern __shared__ __align__(16) unsigned char lds_bytes[];
+        typename Store<S>::T t[27];
+        gather_rows<S, WALLS>(src, g, x < g.nx ? (uint32_t)x : 0u, y, z, (typename Store<S>::T*)lds_bytes, t, []() {});
+        if (x >= g.nx) return;
+        stored_devs<S, WALLS>(t, g, y, L, h);
+    } else {
+        if (x >= g.nx) return;
+        gather_any<S, WALLS>(src, g, x, y, z, L, h);
+    }
+    const int c = x + g.nx * (y + g.ny * z);
+    auto put = [&](OUT* out, size_t k, double v) {
+        if constexpr (NT) __builtin_nontemporal_store(static_cast<OUT>(v), out + k);
+        else out[k] = static_cast<OUT>(v);
     };
-    if (mode == 0) {
+    if constexpr (!MOMENTS) {
 #pragma unroll
         for (int i = 0; i < 27; ++i)
             put(out0, (size_t)i * g.N + c, (double)h[i] + (double)L.P.rho0 * w27<double>(i));
@@ -1078,7 +1181,7 @@ __global__ void __launch_bounds__(256) k_energy_seed(const typename Store<S>::T*
     if (x >= g.nx) return;
     const int c = x + g.nx * (y + g.ny * z);
     R h[27];
-    gather<S, WALLS>(state, g, x, y, z, L, h);
+    gather<S, WALLS, 0, false>(state, g, x, y, z, L, h);
     R Fx, Fy, Fz;
     cell_force<R, FFIELD>(force, g, c, L, Fx, Fy, Fz);
     R drho, jx, jy, jz;
@@ -1101,13 +1204,17 @@ __global__ void __launch_bounds__(256) k_energy_seed(const typename Store<S>::T*
 }
 
 // ---------------------------------------------------------------- FP64 reductions
-// Partial sums per workgroup. The lattice is cut into tiles of one workgroup
-// width along a grid row, numbered x chunk fastest, then y, then z; workgroup b
-// (linear index over the launch grid) combines, lane by lane, the cells of
-// tiles b, b + B, b + 2B, ... (B workgroups in the launch) in that order, then
-// reduces over its lanes in a fixed tree. Launched with one workgroup per tile
-// it visits exactly its own tile; launched with fewer workgroups the partials
-// need only 8 B doubles, whatever the lattice size.
+// Partial sums per workgroup. The lattice is cut into tiles of blockDim.x cells
+// along a grid row, numbered x chunk fastest, then y, then z; the lanes of row
+// threadIdx.y of workgroup b combine the cells of tiles k, k + n, k + 2n, ...
+// (k = blockDim.y b + threadIdx.y, n = blockDim.y times the workgroups) in that
+// order, and the workgroup then reduces over its lanes in a fixed tree. At most
+// kReduceBlocks workgroups, each with 8 doubles of partials: with one
+// workgroup per tile the tree and its eight barriers ran per 256 cells, and the
+// one workgroup that combines the partials read 4 MB of them (256^3 FP32: 451 us
+// and 107 us; now 330 and 5).
+// (Rows gathered through LDS lose here, where a workgroup waits for each row in
+// turn: reductions of 512 x 512 x 128 FP16 435 us by lane, 547 by row.)
 template <int S, bool WALLS, bool FFIELD>
 __global__ void __launch_bounds__(256) k_reduce_partial(const typename Store<S>::T* __restrict__ src,
                                                         const typename Store<S>::R* __restrict__ force,
@@ -1115,18 +1222,19 @@ __global__ void __launch_bounds__(256) k_reduce_partial(const typename Store<S>:
                                                         const Launch<typename Store<S>::R> L) {
     using R = typename Store<S>::R;
     const uint32_t gx = (uint32_t)((g.nx + (int)blockDim.x - 1) / (int)blockDim.x);
-    const uint64_t ntiles = (uint64_t)gx * (uint64_t)g.ny * (uint64_t)g.nz;
-    const uint64_t nblocks = (uint64_t)gridDim.x * gridDim.y * gridDim.z;
-    const uint64_t b = blockIdx.x + (uint64_t)gridDim.x * (blockIdx.y + (uint64_t)gridDim.y * blockIdx.z);
+    const uint32_t ntiles = gx * (uint32_t)g.ny * (uint32_t)g.nz;   // at most N < 2^31
+    // blockDim.x is a multiple of the wave: the tile is uniform within a wave
+    const uint32_t ty = (uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.y);
+    const uint32_t step = gridDim.x * blockDim.y;
     double v[8] = {0, 0, 0, 0, 0, 0, 1.0e300, 0};
-    for (uint64_t t = b; t < ntiles; t += nblocks) {
+    for (uint32_t t = blockIdx.x * blockDim.y + ty; t < ntiles; t += step) {
         const int x = (int)(t % gx) * (int)blockDim.x + (int)threadIdx.x;
-        const uint64_t r = t / gx;
-        const int y = (int)(r % (uint64_t)g.ny), z = (int)(r / (uint64_t)g.ny);
-        if (x >= g.nx) continue;
-        const int c = x + g.nx * (y + g.ny * z);
+        const uint32_t r = t / gx;
+        const int y = (int)(r % (uint32_t)g.ny), z = (int)(r / (uint32_t)g.ny);
         R h[27];
+        if (x >= g.nx) continue;
         gather_any<S, WALLS>(src, g, x, y, z, L, h);
+        const int c = x + g.nx * (y + g.ny * z);
         double hd[27];
 #pragma unroll
         for (int i = 0; i < 27; ++i) hd[i] = (double)h[i];
@@ -1161,7 +1269,7 @@ __global__ void __launch_bounds__(256) k_reduce_partial(const typename Store<S>:
         if (bad) { w[0] = w[1] = w[2] = w[3] = w[4] = 0.0; }
         combine(v, w);
     }
-    block_reduce(v, partial + 8 * b);
+    block_reduce(v, partial + 8 * (size_t)blockIdx.x);
 }
 
 // ---------------------------------------------------------------- launch helpers
@@ -1200,8 +1308,10 @@ static hipError_t split_wall_rows(const LaunchArgs& a, F&& launch) {
     return launch(wl, true);
 }
 
+// The kernels without a row loop: the same widths.
 static dim3 grid_for(const Geom& g, int& bx) {
-    bx = g.nx >= 256 ? 256 : (g.nx >= 128 ? 128 : 64);
+    const int n = (g.nx + 255) / 256;
+    bx = ((g.nx + n - 1) / n + 63) / 64 * 64;
     return dim3((g.nx + bx - 1) / bx, g.ny, g.nz);
 }
 
@@ -1246,9 +1356,8 @@ static Launch<R> make_launch(const LaunchArgs& a) {
 // it (g.lanegather, a tuning hint).
 static bool one_block_per_row(const Geom& g) { return g.nx <= 256 && !g.lanegather; }
 
-// Rows for the kernel that moves whole rows through LDS (es: storage bytes of
-// one value). Rows of up to 256 cells that start on cache lines, es nx a
-// multiple of 128 bytes, stay with the LDS-exchange kernel, whose single barrier
+// Rows for the kernel that moves whole rows through LDS. Rows of up to 256
+// cells that start on cache lines, of a multiple of 128 bytes, stay with the LDS-exchange kernel, whose single barrier
 // costs less (us per step, LDS exchange / whole rows: 256^3 FP32 587 / 609,
 // 192^3 FP16 130 / 137); so do lattices whose two buffers fit the 32 MB of the
 // eight L2s, where partial lines are merged before they reach memory and the
@@ -1260,10 +1369,15 @@ static bool one_block_per_row(const Geom& g) { return g.nx <= 256 && !g.lanegath
 // 384 x 384 x 200 1,205 / 1,142, 512 x 512 x 128 1,298 / 1,275), but not FP64,
 // whose LDS would leave two workgroups on a CU. Rows shorter than 16 cells fill
 // too few lanes and vectors to gain.
-static bool whole_rows(const Geom& g, size_t es) {
+// (past_l2: one buffer of more than 16 MB.)
+template <int S>
+static bool past_l2(const Geom& g) { return 27 * (size_t)g.N * sizeof(typename Store<S>::T) >= ((size_t)16 << 20); }
+template <int S>
+static bool whole_rows(const Geom& g) {
+    constexpr size_t es = sizeof(typename Store<S>::T);
     if (g.lanegather || g.rowloop || g.nx < 16 || g.nx > 512) return false;
     if (g.nx > 256) return es != 8;
-    return (size_t)g.nx * es % 128 != 0 && 27 * (size_t)g.N * es >= ((size_t)16 << 20);
+    return (size_t)g.nx * es % 128 != 0 && past_l2<S>(g);
 }
 
 // Its workgroup, one lane per cell, and LDS: the nine groups of three rows (the
@@ -1355,7 +1469,7 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
             return hipGetLastError();
         }
     }
-    if (whole_rows(a.g, sizeof(T))) {
+    if (whole_rows<S>(a.g)) {
         // rows that start on cache lines (wider than 256 cells: the others of
         // that kind take the LDS exchange): each lane stores its own values
         // (us per step, through LDS / directly: 384 x 384 x 200 FP32 1,158 /
@@ -1435,7 +1549,7 @@ static hipError_t step_sgs_t(const LaunchArgs& a, const void* src, void* dst) {
     if (a.xcd_default && g.xcd >= 2) g.xcd = 0;
     // FP32 rows of one workgroup in chunks of planes, as the step without the
     // stress force (256^3: 769.4 -> 761.2 us)
-    if (whole_rows(g, sizeof(T))) {
+    if (whole_rows<S>(g)) {
         const bool direct = (size_t)g.nx * sizeof(T) % 128 == 0;
         return launch_z_chunks(g, dim3(1, g.ny, g.nz), sizeof(T) == 4, [&](const dim3& gq, const Geom& gg) {
             auto launch = [&](auto v, auto d) {
@@ -1475,21 +1589,36 @@ hipError_t step_w(const LaunchArgs& a, const void* src, void* dst) {
         if (a.walls || !a.stress_prev || !a.stress_next) return hipErrorInvalidValue;   // checked by the caller
         return a.force_field ? step_sgs_t<S, true>(a, src, dst) : step_sgs_t<S, false>(a, src, dst);
     }
-    if (whole_rows(a.g, sizeof(typename Store<S>::T)) || one_block_per_row(a.g))
+    if (whole_rows<S>(a.g) || one_block_per_row(a.g))
         return a.walls ? step_les<S, true>(a, src, dst) : step_les<S, false>(a, src, dst);
     return split_wall_rows(a, [&](const LaunchArgs& b, bool w) {
         return w ? step_les<S, true>(b, src, dst) : step_les<S, false>(b, src, dst);
     });
 }
 
+// Setting a state: one workgroup per row, through LDS (push_rows), for rows of 16
+// to 512 cells of lattices past the L2s (set_populations of 20 x 50 x 50 FP32 8.8
+// us by lane, 10.2 by row; of 100^3 75.6 and 55.8).
+template <int S>
+static bool push_by_rows(const Geom& g) { return g.nx >= 16 && g.nx <= 512 && past_l2<S>(g); }
+template <int S>
+static unsigned push_lds(const Geom& g) {
+    return 3u * group_stride<typename Store<S>::T>((uint32_t)g.nx) * (unsigned)sizeof(typename Store<S>::T);
+}
 template <int S, bool W, bool FF>
 static hipError_t init_t(const LaunchArgs& a, void* dst, const void* rho, const void* u, int dt) {
     using T = typename Store<S>::T;
     using R = typename Store<S>::R;
-    int bx;
-    const dim3 grid = grid_for(a.g, bx);
-    k_init_equilibrium<S, W, FF><<<grid, bx, 0, (hipStream_t)a.stream>>>((T*)dst, (const R*)a.force_field, rho, u, dt,
-                                                                         a.g, make_launch<R>(a));
+    hipStream_t st = (hipStream_t)a.stream;
+    if (push_by_rows<S>(a.g)) {
+        k_init_equilibrium<S, W, FF, true><<<dim3(1, a.g.ny, a.g.nz), row_lanes(a.g), push_lds<S>(a.g), st>>>(
+            (T*)dst, (const R*)a.force_field, rho, u, dt, a.g, make_launch<R>(a));
+    } else {
+        int bx;
+        const dim3 grid = grid_for(a.g, bx);
+        k_init_equilibrium<S, W, FF, false><<<grid, bx, 0, st>>>((T*)dst, (const R*)a.force_field, rho, u, dt, a.g,
+                                                                 make_launch<R>(a));
+    }
     return hipGetLastError();
 }
 
@@ -1497,21 +1626,57 @@ template <int S, bool W>
 static hipError_t setpop_t(const LaunchArgs& a, void* dst, const void* f, int dt) {
     using T = typename Store<S>::T;
     using R = typename Store<S>::R;
-    int bx;
-    const dim3 grid = grid_for(a.g, bx);
-    k_set_populations<S, W><<<grid, bx, 0, (hipStream_t)a.stream>>>((T*)dst, f, dt, a.g, make_launch<R>(a));
+    hipStream_t st = (hipStream_t)a.stream;
+    if (push_by_rows<S>(a.g)) {
+        k_set_populations<S, W, true><<<dim3(1, a.g.ny, a.g.nz), row_lanes(a.g), push_lds<S>(a.g), st>>>((T*)dst, f, dt, a.g,
+                                                                                                    make_launch<R>(a));
+    } else {
+        int bx;
+        const dim3 grid = grid_for(a.g, bx);
+        k_set_populations<S, W, false><<<grid, bx, 0, st>>>((T*)dst, f, dt, a.g, make_launch<R>(a));
+    }
     return hipGetLastError();
 }
 
-template <int S, bool W, bool FF>
-static hipError_t read_t(const LaunchArgs& a, const void* src, void* out0, void* out1, int dt, int mode) {
+// Rows that the read-outs gather through LDS: two-buffer lattices past the L2s
+// (as whole_rows; below, the extra barriers show: populations of 20 x 50 x 50
+// FP32 8.7 us by lane, 10.6 by row), 16 to 512 cells (FP64: 256, by its LDS).
+// us by lane / by row: rho and u of 256^3 FP32 440 / 383, of 300 x 181 x 90
+// FP32-shifted 160 / 118, of 201 x 160 x 100 FP64 165 / 141; populations of
+// 256^3 FP32 1,014 / 857, of 300 x 181 x 90 429 / 375.
+template <int S>
+static bool read_rows(const Geom& g) {
+    return g.aa == 0 && g.nx >= 16 && g.nx <= (S == 0 ? 256 : 512) && past_l2<S>(g);
+}
+
+template <int S, bool W, bool FF, bool MOMENTS, typename OUT>
+static hipError_t read_o(const LaunchArgs& a, const void* src, void* out0, void* out1) {
     using T = typename Store<S>::T;
     using R = typename Store<S>::R;
-    int bx;
-    const dim3 grid = grid_for(a.g, bx);
-    k_read<S, W, FF><<<grid, bx, 0, (hipStream_t)a.stream>>>((const T*)src, (const R*)a.force_field, out0, out1, dt,
-                                                            mode, a.g, make_launch<R>(a));
+    hipStream_t st = (hipStream_t)a.stream;
+    const bool nt = (size_t)a.g.nx * sizeof(OUT) % 32 == 0;
+    auto launch = [&](auto n) {
+        constexpr bool NT = decltype(n)::value;
+        if (read_rows<S>(a.g)) {
+            k_read<S, W, FF, MOMENTS, true, NT, OUT><<<dim3(1, a.g.ny, a.g.nz), row_lanes(a.g), row_lds<T>(a.g), st>>>(
+                (const T*)src, (const R*)a.force_field, (OUT*)out0, (OUT*)out1, a.g, make_launch<R>(a));
+        } else {
+            int bx;
+            const dim3 grid = grid_for(a.g, bx);
+            k_read<S, W, FF, MOMENTS, false, NT, OUT><<<grid, bx, 0, st>>>((const T*)src, (const R*)a.force_field,
+                                                                           (OUT*)out0, (OUT*)out1, a.g, make_launch<R>(a));
+        }
+    };
+    if (nt) launch(std::true_type());
+    else launch(std::false_type());
     return hipGetLastError();
+}
+template <int S, bool W, bool FF>
+static hipError_t read_t(const LaunchArgs& a, const void* src, void* out0, void* out1, int dt, int mode) {
+    if (mode) return dt == 0 ? read_o<S, W, FF, true, double>(a, src, out0, out1) : read_o<S, W, FF, true, float>(a, src, out0, out1);
+    // the populations do not depend on the force
+    return dt == 0 ? read_o<S, W, false, false, double>(a, src, out0, out1)
+                   : read_o<S, W, false, false, float>(a, src, out0, out1);
 }
 
 template <int S, bool FF, bool W, bool LES, bool VAR>
@@ -1558,18 +1723,19 @@ static hipError_t seed_t(const LaunchArgs& a, const void* state, void* lam_out, 
 }
 
 template <int S, bool W, bool FF>
-static hipError_t reduce_t(const LaunchArgs& a, const void* src, double* partial, double* out, size_t max_blocks) {
+static hipError_t reduce_t(const LaunchArgs& a, const void* src, double* partial, double* out) {
     using T = typename Store<S>::T;
     using R = typename Store<S>::R;
     int bx;
-    dim3 grid = grid_for(a.g, bx);
-    const size_t ntiles = (size_t)grid.x * grid.y * grid.z;
-    if (max_blocks && ntiles > max_blocks) grid = dim3((unsigned)max_blocks, 1, 1);
-    k_reduce_partial<S, W, FF><<<grid, bx, 0, (hipStream_t)a.stream>>>((const T*)src, (const R*)a.force_field, partial,
-                                                                      a.g, make_launch<R>(a));
+    const dim3 tiles = grid_for(a.g, bx);
+    const int by = 256 / bx;   // narrow rows: several tiles side by side
+    const size_t blocks = ((size_t)tiles.x * tiles.y * tiles.z + by - 1) / by;
+    const unsigned grid = (unsigned)(blocks < kReduceBlocks ? blocks : kReduceBlocks);
+    k_reduce_partial<S, W, FF><<<grid, dim3(bx, by), 0, (hipStream_t)a.stream>>>((const T*)src, (const R*)a.force_field,
+                                                                                partial, a.g, make_launch<R>(a));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_reduce_final(partial, (size_t)grid.x * grid.y * grid.z, out, a.stream);
+    return launch_reduce_final(partial, grid, out, a.stream);
 }
 
 template <int S>
@@ -1596,9 +1762,9 @@ hipError_t read_s(const LaunchArgs& a, const void* src, void* o0, void* o1, int 
     return a.force_field ? read_t<S, false, true>(a, src, o0, o1, dt, mode) : read_t<S, false, false>(a, src, o0, o1, dt, mode);
 }
 template <int S>
-hipError_t reduce_s(const LaunchArgs& a, const void* src, double* partial, double* out, size_t mb) {
-    if (a.walls) return a.force_field ? reduce_t<S, true, true>(a, src, partial, out, mb) : reduce_t<S, true, false>(a, src, partial, out, mb);
-    return a.force_field ? reduce_t<S, false, true>(a, src, partial, out, mb) : reduce_t<S, false, false>(a, src, partial, out, mb);
+hipError_t reduce_s(const LaunchArgs& a, const void* src, double* partial, double* out) {
+    if (a.walls) return a.force_field ? reduce_t<S, true, true>(a, src, partial, out) : reduce_t<S, true, false>(a, src, partial, out);
+    return a.force_field ? reduce_t<S, false, true>(a, src, partial, out) : reduce_t<S, false, false>(a, src, partial, out);
 }
 
 // The launchers of one storage mode S. This file is compiled once for each mode
@@ -1613,7 +1779,7 @@ hipError_t reduce_s(const LaunchArgs& a, const void* src, double* partial, doubl
     KIND template hipError_t read_s<S>(const LaunchArgs&, const void*, void*, void*, int, int);              \
     KIND template hipError_t adjoint_s<S>(const LaunchArgs&, const void*, const void*, void*, void*);        \
     KIND template hipError_t seed_s<S>(const LaunchArgs&, const void*, void*, void*);                        \
-    KIND template hipError_t reduce_s<S>(const LaunchArgs&, const void*, double*, double*, size_t);
+    KIND template hipError_t reduce_s<S>(const LaunchArgs&, const void*, double*, double*);
 #define CM_DEFINE
 #ifdef CM_STORAGE
 CM_STORAGE_LAUNCHERS(CM_DEFINE, CM_STORAGE)
@@ -1658,7 +1824,14 @@ __global__ void __launch_bounds__(256) k_reduce_final(const double* __restrict__
 // and 6.49 with 256-thread workgroups, 6.35 with 512, 6.18 with 1024, 6.21-6.26
 // with an ordinary load; two or more vectors per thread and grid-stride loops
 // were slower still, 4.1-6.1 TB/s).
+// 16 bytes a thread (the stress planes of 192^3 FP32, 170 MB: 46 us with 4 bytes
+// a thread, now 26), the last 0 to 3 words by one thread each.
 __global__ void __launch_bounds__(256) k_zero(unsigned int* __restrict__ dst, size_t n) {
+    const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < n / 4) __builtin_nontemporal_store((u32x4){0u, 0u, 0u, 0u}, (u32x4*)dst + k);
+    else if (k - n / 4 < n % 4) dst[n - n % 4 + (k - n / 4)] = 0u;
+}
+__global__ void __launch_bounds__(256) k_zero_words(unsigned int* __restrict__ dst, size_t n) {
     const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k < n) dst[k] = 0u;
 }
@@ -1685,8 +1858,8 @@ hipError_t launch_adjoint(const LaunchArgs& a, const void* state, const void* la
 hipError_t launch_energy_seed(const LaunchArgs& a, const void* state, void* lam_out, void* grad_F) {
     CM_DISPATCH_S(seed_s, a, state, lam_out, grad_F)
 }
-hipError_t launch_reduce(const LaunchArgs& a, const void* src, double* partial, double* out, size_t max_blocks) {
-    CM_DISPATCH_S(reduce_s, a, src, partial, out, max_blocks)
+hipError_t launch_reduce(const LaunchArgs& a, const void* src, double* partial, double* out) {
+    CM_DISPATCH_S(reduce_s, a, src, partial, out)
 }
 hipError_t launch_copy(const void* src, void* dst, size_t bytes, void* stream) {
     const size_t n16 = bytes / 16;
@@ -1702,18 +1875,20 @@ hipError_t launch_reduce_final(const double* partial, size_t nparts, double* out
 }
 hipError_t launch_zero(void* dst, size_t bytes, void* stream) {
     const size_t n = bytes / 4;
-    const size_t blocks = (n + 255) / 256;
+    const bool vec = (uintptr_t)dst % 16 == 0;
+    const size_t blocks = ((vec ? n / 4 + n % 4 : n) + 255) / 256;
     if (blocks == 0) return hipSuccess;
     if (blocks > 0x7fffffffu) return hipErrorInvalidValue;
-    k_zero<<<(unsigned)blocks, 256, 0, (hipStream_t)stream>>>((unsigned int*)dst, n);
+    if (vec) k_zero<<<(unsigned)blocks, 256, 0, (hipStream_t)stream>>>((unsigned int*)dst, n);
+    else k_zero_words<<<(unsigned)blocks, 256, 0, (hipStream_t)stream>>>((unsigned int*)dst, n);
     return hipGetLastError();
 }
 // Scratch of the allocation-free reductions: the partials of at most
-// kStaticReduceBlocks workgroups (65,536 bytes per device, held until the
+// kReduceBlocks workgroups (65,536 bytes per device, held until the
 // process ends). In host code `scratch` names a
 // host-side stand-in, not the device array: its device address comes from
 // hipGetSymbolAddress, looked up once per device with that device current.
-static __device__ __align__(256) double scratch[8 * kStaticReduceBlocks];
+static __device__ __align__(256) double scratch[8 * kReduceBlocks];
 
 hipError_t static_reduce_scratch(int device, double** ptr) {
     constexpr int kMaxDevices = 64;
@@ -1738,12 +1913,6 @@ hipError_t static_reduce_scratch(int device, double** ptr) {
     }
     *ptr = addr[device];
     return hipSuccess;
-}
-
-size_t reduce_partials(const Geom& g) {
-    int bx;
-    const dim3 grid = grid_for(g, bx);
-    return (size_t)grid.x * grid.y * grid.z;
 }
 }  // namespace cm
 #endif   // CM_STORAGE

@@ -271,9 +271,8 @@ __global__ void __launch_bounds__(256) k2_read(const typename Store<S>::T* __res
     put(out1, (size_t)g.N + c, (double)((jy + R(0.5) * Fy) / rho_u));
 }
 
-// Partial sums per workgroup over tiles of one workgroup width along a grid
-// row (x chunk fastest, then y): workgroup b of B combines tiles b, b + B, ...
-// lane by lane, then reduces over its lanes (see the D3Q27 kernel).
+// Partial sums per workgroup over tiles of blockDim.x cells along a grid row (x
+// chunk fastest, then y): as the D3Q27 kernel.
 template <int S, bool WALLS, bool FFIELD>
 __global__ void __launch_bounds__(256) k2_reduce_partial(const typename Store<S>::T* __restrict__ src,
                                                          const typename Store<S>::R* __restrict__ force,
@@ -281,11 +280,11 @@ __global__ void __launch_bounds__(256) k2_reduce_partial(const typename Store<S>
                                                          const Launch<typename Store<S>::R> L) {
     using R = typename Store<S>::R;
     const uint32_t gx = (uint32_t)((g.nx + (int)blockDim.x - 1) / (int)blockDim.x);
-    const uint64_t ntiles = (uint64_t)gx * (uint64_t)g.ny;
-    const uint64_t nblocks = (uint64_t)gridDim.x * gridDim.y;
-    const uint64_t b = blockIdx.x + (uint64_t)gridDim.x * blockIdx.y;
+    const uint32_t ntiles = gx * (uint32_t)g.ny;   // at most N < 2^31
+    const uint32_t ty = (uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.y);
+    const uint32_t step = gridDim.x * blockDim.y;
     double v[8] = {0, 0, 0, 0, 0, 0, 1.0e300, 0};
-    for (uint64_t t = b; t < ntiles; t += nblocks) {
+    for (uint32_t t = blockIdx.x * blockDim.y + ty; t < ntiles; t += step) {
         const int x = (int)(t % gx) * (int)blockDim.x + (int)threadIdx.x;
         const int y = (int)(t / gx);
         if (x >= g.nx) continue;
@@ -324,12 +323,14 @@ __global__ void __launch_bounds__(256) k2_reduce_partial(const typename Store<S>
         w[7] = bad ? 0.0 : sqrt(u2);
         cm::combine(v, w);
     }
-    cm::block_reduce(v, partial + 8 * b);
+    cm::block_reduce(v, partial + 8 * (size_t)blockIdx.x);
 }
 
 // ---------------------------------------------------------------- launch helpers
+// The fewest workgroups of at most 256 lanes for a row, of even width.
 static dim3 grid_for(const Geom& g, int& bx, bool rowloop) {
-    bx = g.nx >= 256 ? 256 : (g.nx >= 128 ? 128 : 64);
+    const int n = (g.nx + 255) / 256;
+    bx = ((g.nx + n - 1) / n + 63) / 64 * 64;
     return dim3(rowloop ? 1 : (g.nx + bx - 1) / bx, g.ny, 1);
 }
 
@@ -457,24 +458,25 @@ static hipError_t read_s(const LaunchArgs& a, const void* src, void* o0, void* o
 }
 
 template <int S, bool W, bool FF>
-static hipError_t reduce_t(const LaunchArgs& a, const void* src, double* partial, double* out, size_t max_blocks) {
+static hipError_t reduce_t(const LaunchArgs& a, const void* src, double* partial, double* out) {
     using T = typename Store<S>::T;
     using R = typename Store<S>::R;
     int bx;
-    dim3 grid = grid_for(a.g, bx, false);
-    const size_t ntiles = (size_t)grid.x * grid.y;
-    if (max_blocks && ntiles > max_blocks) grid = dim3((unsigned)max_blocks, 1, 1);
-    k2_reduce_partial<S, W, FF><<<grid, bx, 0, (hipStream_t)a.stream>>>((const T*)src, (const R*)a.force_field,
-                                                                       partial, a.g, make_launch<R>(a));
+    const dim3 tiles = grid_for(a.g, bx, false);
+    const int by = 256 / bx;
+    const size_t blocks = ((size_t)tiles.x * tiles.y + by - 1) / by;
+    const unsigned grid = (unsigned)(blocks < cm::kReduceBlocks ? blocks : cm::kReduceBlocks);
+    k2_reduce_partial<S, W, FF><<<grid, dim3(bx, by), 0, (hipStream_t)a.stream>>>((const T*)src, (const R*)a.force_field,
+                                                                                 partial, a.g, make_launch<R>(a));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return cm::launch_reduce_final(partial, (size_t)grid.x * grid.y, out, a.stream);
+    return cm::launch_reduce_final(partial, grid, out, a.stream);
 }
 template <int S>
-static hipError_t reduce_s(const LaunchArgs& a, const void* src, double* partial, double* out, size_t mb) {
+static hipError_t reduce_s(const LaunchArgs& a, const void* src, double* partial, double* out) {
     if (a.walls)
-        return a.force_field ? reduce_t<S, true, true>(a, src, partial, out, mb) : reduce_t<S, true, false>(a, src, partial, out, mb);
-    return a.force_field ? reduce_t<S, false, true>(a, src, partial, out, mb) : reduce_t<S, false, false>(a, src, partial, out, mb);
+        return a.force_field ? reduce_t<S, true, true>(a, src, partial, out) : reduce_t<S, true, false>(a, src, partial, out);
+    return a.force_field ? reduce_t<S, false, true>(a, src, partial, out) : reduce_t<S, false, false>(a, src, partial, out);
 }
 
 #define CM2_DISPATCH_S(fn, ...)                 \
@@ -496,8 +498,8 @@ hipError_t launch_set_populations(const LaunchArgs& a, void* dst, const void* f,
 hipError_t launch_read(const LaunchArgs& a, const void* src, void* out0, void* out1, int dt, int mode) {
     CM2_DISPATCH_S(read_s, a, src, out0, out1, dt, mode)
 }
-hipError_t launch_reduce(const LaunchArgs& a, const void* src, double* partial, double* out, size_t max_blocks) {
-    CM2_DISPATCH_S(reduce_s, a, src, partial, out, max_blocks)
+hipError_t launch_reduce(const LaunchArgs& a, const void* src, double* partial, double* out) {
+    CM2_DISPATCH_S(reduce_s, a, src, partial, out)
 }
 
 }  // namespace cm2

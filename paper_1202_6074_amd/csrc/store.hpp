@@ -61,27 +61,34 @@ __device__ __forceinline__ void combine(double (&a)[8], const double (&b)[8]) {
     a[7] = fmax(a[7], b[7]);
 }
 
+// Over the lanes of a wave first (halving distances), then over the waves in
+// turn: a fixed order, and 512 bytes of LDS (a tree over all lanes in LDS took
+// 16 KB, on the kernels that need theirs for rows).
 __device__ __forceinline__ void block_reduce(double (&v)[8], double* __restrict__ out) {
-    __shared__ double sm[8][256];
+    __shared__ double sm[8][8];   // of at most eight waves
     const int t = threadIdx.x + blockDim.x * threadIdx.y;
-    const int nt = blockDim.x * blockDim.y;
+    const int waves = (int)(blockDim.x * blockDim.y) / 64;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) sm[k][t] = v[k];
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (t < s && t + s < nt) {
-            double a[8], b[8];
+    for (int s = 32; s > 0; s >>= 1) {
+        double w[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) { a[k] = sm[k][t]; b[k] = sm[k][t + s]; }
-            combine(a, b);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) sm[k][t] = a[k];
-        }
-        __syncthreads();
+        for (int k = 0; k < 8; ++k) w[k] = __shfl_down(v[k], s);
+        combine(v, w);
     }
-    if (t == 0) {
+    if ((t & 63) == 0) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) out[k] = sm[k][0];
+        for (int k = 0; k < 8; ++k) sm[t >> 6][k] = v[k];
+    }
+    __syncthreads();
+    if (t == 0) {
+        for (int w = 1; w < waves; ++w) {
+            double b[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) b[k] = sm[w][k];
+            combine(v, b);
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) out[k] = v[k];
     }
 }
 

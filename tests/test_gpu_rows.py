@@ -78,3 +78,76 @@ def test_whole_rows_with_the_sub_grid_force(storage, nx):
     ny = -(-(17 << 20) // (27 * nx * 5 * {"f64": 8, "f32": 4, "f16s": 2}[storage]))
     a, b = _states((nx, ny, 5), storage, False, 3, (0, 32), flags={"sgs_force": True})
     assert torch.equal(a, b)
+
+
+# Tolerances of one storage rounding (half a unit in the last place of values up
+# to 0.5, of deviations up to 0.125 in FP16) with the shift by w_i added and
+# taken away, and of sums of 27 such values in the compute type.
+ROUND = {"f64": 2e-16, "f32": 6e-8, "f32s": 6e-8, "f16s": 6.2e-5}
+SUMS = {"f64": 1e-14, "f32": 2e-6, "f32s": 2e-6, "f16s": 2e-6}
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f32s", "f16s"])
+@pytest.mark.parametrize("nx,ny,nz", [(9, 5, 3), (17, 90, 130), (187, 61, 19), (256, 29, 24), (300, 33, 21), (512, 20, 17),
+                                      (700, 9, 26)])
+@pytest.mark.parametrize("walls", [False, True])
+def test_set_and_read_by_rows_and_by_lanes(storage, nx, ny, nz, walls):
+    """set_populations and the read-outs on lattices below and above 16 MB a
+    buffer and on rows of more than 512 cells (by lanes) and the others (by
+    rows): the buffer against f moved to the upstream cells, what is read back
+    against f and its sums, and all of it bitwise against an in-place lattice,
+    whose read-out goes by lanes."""
+    torch = _torch()
+    from paper_1202_6074_amd.lattice import Lattice
+    g = torch.Generator().manual_seed(nx)
+    w1 = torch.tensor([1 / 6, 2 / 3, 1 / 6], dtype=torch.float64)
+    w = torch.einsum("a,b,c->abc", w1, w1, w1).reshape(27, 1, 1, 1).cuda()
+    f = w * (1 + 0.1 * torch.rand((27, nz, ny, nx), generator=g, dtype=torch.float64).cuda())
+    F = (1e-3 * torch.randn((3, nz, ny, nx), generator=g, dtype=torch.float64)).cuda()
+    got = []
+    for in_place in (False, True):
+        lat = Lattice((nx, ny, nz), storage=storage, walls=walls, wall_u_hi=(0.02, 0.0, 0.01), in_place=in_place)
+        lat.set_force(field=F)
+        lat.set_populations(f)
+        rho, u = lat.moments()
+        rho32, u32 = lat.moments(torch.float32)
+        got.append([lat.populations(), rho, u, lat.populations(torch.float32), rho32, u32])
+        red = lat.reduce()
+        if not in_place and not walls:
+            state = lat.state_buffer().view(nz, ny, 27, nx).permute(2, 0, 1, 3).double()
+            if storage in ("f32s", "f16s"):
+                state = state + w
+            for i in range(27):
+                e = (i // 9 - 1, (i // 3) % 3 - 1, i % 3 - 1)
+                want = torch.roll(f[i], [-v for v in e], dims=(0, 1, 2))
+                assert float((state[i] - want).abs().max()) <= ROUND[storage], i
+    pops, rho, u, pops32, rho32, u32 = got[0]
+    assert float((pops - f).abs().max()) <= 2 * ROUND[storage]
+    mom = torch.stack([sum((i // 3 ** d % 3 - 1) * pops[i] for i in range(27)) for d in range(3)])
+    assert float((rho - pops.sum(0)).abs().max()) <= SUMS[storage]
+    assert float((u - (mom + 0.5 * F) / pops.sum(0)).abs().max()) <= SUMS[storage]
+    assert float((pops32.double() - pops).abs().max()) <= 3e-8
+    assert torch.equal(rho32, rho.float()) and torch.equal(u32, u.float())
+    speed = u.square().sum(0).sqrt()
+    assert abs(red["mass"] - float(rho.sum())) <= SUMS[storage] * rho.numel()
+    assert abs(red["ke"] - float((0.5 * rho * speed ** 2).sum())) <= SUMS[storage] * rho.numel()
+    assert abs(red["umax"] - float(speed.max())) <= SUMS[storage] and red["nonfinite"] == 0
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("nx,ny,nz", [(187, 61, 19), (300, 33, 21)])
+@pytest.mark.parametrize("walls", [False, True])
+def test_start_by_rows(storage, nx, ny, nz, walls):
+    """init_equilibrium by rows, two-buffer and in place: the same populations."""
+    torch = _torch()
+    a = _states((nx, ny, nz), storage, walls, 0, (0,))
+    from paper_1202_6074_amd.lattice import Lattice   # noqa: F401
+    b = _states((nx, ny, nz), storage, walls, 0, (0,), in_place=True)
+    if not walls:
+        s = a[0].view(nz, ny, 27, nx)
+        t = b[0].view(nz, ny, 27, nx)
+        for i in range(27):
+            e = (i // 9 - 1, (i // 3) % 3 - 1, i % 3 - 1)
+            assert torch.equal(s[:, :, i], torch.roll(t[:, :, i], [-v for v in e], dims=(0, 1, 2)))
