@@ -227,6 +227,22 @@ __device__ __forceinline__ uint32_t pack_f16(float a, float b) {
 }
 
 
+// The wall terms of the populations that arrived from a wall, on a row next to
+// one (y uniform).
+template <typename R>
+__device__ __forceinline__ void add_wall_terms(const Geom& g, int y, const Launch<R>& L, R (&h)[27]) {
+    if (y == 0) {
+#pragma unroll
+        for (int i = 0; i < 27; ++i)
+            if ((i / 3) % 3 == 2) h[i] = add_rn(h[i], L.wt_lo[i]);
+    }
+    if (y == g.ny - 1) {
+#pragma unroll
+        for (int i = 0; i < 27; ++i)
+            if ((i / 3) % 3 == 0) h[i] = add_rn(h[i], L.wt_hi[i]);
+    }
+}
+
 // Gather of fbar(n) at cell (x, y, z).
 // MODE 0 (two-buffer pull scheme): the buffer holds fbar~(n-1), population i
 //   of the upstream cell x - e_i in plane i, or, when that is a wall, plane
@@ -246,6 +262,11 @@ __device__ __forceinline__ uint32_t pack_f16(float a, float b) {
 // +4 % for FP32 at 512^3); the step kernel takes ordinary loads there, and
 // gather_xlds when one workgroup covers a row. The read-out kernels keep the
 // default.
+// WALLS: a group from a wall reads other rows and is not shifted; y is uniform, so
+// these are scalar selects, and the wall terms are added at the end (a branch
+// for each population kept the loads from being in flight together: the adjoint
+// of 128^3 FP32 with the eddy viscosity between walls 175 us, now 119, periodic
+// 118).
 template <int S, bool WALLS, int MODE = 0, bool NTX = true, bool SB = false, typename R = typename Store<S>::R>
 __device__ __forceinline__ void gather(const typename Store<S>::T* src, const Geom g, int x, int y, int z,
                                        const Launch<R>& L, R (&h)[27]) {
@@ -253,15 +274,8 @@ __device__ __forceinline__ void gather(const typename Store<S>::T* src, const Ge
     if constexpr (MODE == 1) {
         const uint32_t xt = (uint32_t)x * (uint32_t)sizeof(T);
 #pragma unroll
-        for (int i = 0; i < 27; ++i) {
-            h[i] = load_dev<S, MODE != 2>(row_at<SB>(src + row_base(g, i, y, z), xt), i, L.P.rho0);
-            if constexpr (WALLS) {
-                const int iy = (i / 3) % 3;
-                const bool from_lo = (iy == 2) && (y == 0);
-                const bool from_hi = (iy == 0) && (y == g.ny - 1);
-                if (from_lo || from_hi) h[i] = add_rn(h[i], from_lo ? L.wt_lo[i] : L.wt_hi[i]);
-            }
-        }
+        for (int i = 0; i < 27; ++i) h[i] = load_dev<S>(row_at<SB>(src + row_base(g, i, y, z), xt), i, L.P.rho0);
+        if constexpr (WALLS) add_wall_terms(g, y, L, h);
         return;
     }
     const uint32_t xo[3] = {(uint32_t)(x == g.nx - 1 ? 0 : x + 1) * (uint32_t)sizeof(T), (uint32_t)x * (uint32_t)sizeof(T),
@@ -273,34 +287,22 @@ __device__ __forceinline__ void gather(const typename Store<S>::T* src, const Ge
     // rows (ey, ez) needs one uniform pointer, and the row-in-group offset is
     // folded into the three per-lane offsets (scalar-register pressure).
     const uint32_t rb = (uint32_t)g.nx * (uint32_t)sizeof(T);
-    uint32_t vo[3];
-#pragma unroll
-    for (int ix = 0; ix < 3; ++ix) vo[ix] = xo[ix] + (uint32_t)(MODE == 2 ? 2 - ix : ix) * rb;
 #pragma unroll
     for (int i = 0; i < 27; ++i) {
-        const int ix = i % 3, iy = (i / 3) % 3, iz = i / 9;
-        if constexpr (WALLS) {
-            const bool from_lo = (iy == 2) && (y == 0);
-            const bool from_hi = (iy == 0) && (y == g.ny - 1);
-            if (from_lo || from_hi) {
-                const int o = MODE == 2 ? i : 26 - i;
-                const T* row = src + row_base(g, o, y, z);
-                R v = load_dev<S, MODE != 2>(row_at<SB>(row, xo[1]), o, L.P.rho0);
-                v = add_rn(v, from_lo ? L.wt_lo[i] : L.wt_hi[i]);
-                h[i] = v;
-                continue;
-            }
-        }
-        const int pl = MODE == 2 ? 26 - i : i;   // w_i = w_{26-i}: the shift is the same
-        const T* grp = src + row_base(g, pl - pl % 3, ys[iy], zs[iz]);
-        const auto p = row_at<SB>(grp, vo[ix]);
+        const int ix = i % 3, iy = (i / 3) % 3, iz = i / 9, q = i / 3;
+        const bool wall = WALLS && ((iy == 2 && y == 0) || (iy == 0 && y == g.ny - 1));
+        // plane 26 - i (group 8 - q in reverse order) or i: the other one from a wall
+        const bool rev = (MODE == 2) != wall;
+        const T* grp = src + row_base(g, rev ? 24 - 3 * q : 3 * q, wall ? y : ys[iy], wall ? z : zs[iz]);
+        const auto p = row_at<SB>(grp, xo[wall ? 1 : ix] + (uint32_t)(rev ? 2 - ix : ix) * rb);
         // rows read at x once: non-temporal; x-shifted rows: non-temporal only with
         // NTX and not in the odd in-place gather (whose shifted reads share lines
         // with the neighbouring wave; its aligned rows non-temporal: 1024 x 512 x
         // 512 FP32 10,930 -> 10,832 us, FP16 shifted 6,038 -> 5,957 us per pair)
-        if (ix == 1 || (MODE != 2 && NTX)) h[i] = load_dev<S, true>(p, pl, L.P.rho0);
-        else h[i] = load_dev<S, false>(p, pl, L.P.rho0);
+        if (ix == 1 || (MODE != 2 && NTX)) h[i] = load_dev<S, true>(p, i, L.P.rho0);   // w_i = w_{26-i}
+        else h[i] = load_dev<S, false>(p, i, L.P.rho0);
     }
+    if constexpr (WALLS) add_wall_terms(g, y, L, h);
 }
 
 // Gather in the mode the geometry's streaming state asks for (read-out kernels;
@@ -370,22 +372,6 @@ __device__ __forceinline__ void gather_xlds(const typename Store<S>::T* __restri
     for (int i = 0; i < 27; ++i) {
         const int ix = i % 3;   // e_x = ix - 1: the value comes from x - e_x
         out[i] = ix == 1 ? raw[i] : sm[(i / 3) * 2 + ix / 2][bounce(i) ? x : (ix == 0 ? xp : xm)];
-    }
-}
-
-// The wall terms of the populations that arrived from a wall, on a row next to
-// one (y uniform; the same rounded addition as in gather).
-template <typename R>
-__device__ __forceinline__ void add_wall_terms(const Geom& g, int y, const Launch<R>& L, R (&h)[27]) {
-    if (y == 0) {
-#pragma unroll
-        for (int i = 0; i < 27; ++i)
-            if ((i / 3) % 3 == 2) h[i] = add_rn(h[i], L.wt_lo[i]);
-    }
-    if (y == g.ny - 1) {
-#pragma unroll
-        for (int i = 0; i < 27; ++i)
-            if ((i / 3) % 3 == 0) h[i] = add_rn(h[i], L.wt_hi[i]);
     }
 }
 
@@ -876,20 +862,84 @@ __global__ void __launch_bounds__(256) k_step_inplace(typename Store<S>::T* buf,
 #pragma unroll
             for (int i = 0; i < 27; ++i) {
                 const int ix = i % 3, iy = (i / 3) % 3, iz = i / 9;
-                if constexpr (WALLS) {
-                    const bool to_lo = (iy == 0) && (y == 0);
-                    const bool to_hi = (iy == 2) && (y == g.ny - 1);
-                    if (to_lo || to_hi) {
-                        const int o = 26 - i;
-                        __builtin_nontemporal_store(to_store<S>(h[i], o, L.P.rho0), buf + row_base(g, o, y, z) + x);
-                        continue;
-                    }
-                }
-                __builtin_nontemporal_store(to_store<S>(h[i], i, L.P.rho0),
-                                            (T*)((char*)(buf + row_base(g, i - ix, ys[iy], zs[iz])) + vo[ix]));
+                const bool wall = WALLS && ((iy == 0 && y == 0) || (iy == 2 && y == g.ny - 1));
+                T* const grp = buf + row_base(g, wall ? 24 - (i - ix) : i - ix, wall ? y : ys[iy], wall ? z : zs[iz]);
+                const uint32_t o = wall ? ((uint32_t)x + (uint32_t)(2 - ix) * (uint32_t)g.nx) * (uint32_t)sizeof(T) : vo[ix];
+                __builtin_nontemporal_store(to_store<S>(h[i], i, L.P.rho0), (T*)((char*)grp + o));   // w_i = w_{26-i}
             }
         }
     }
+}
+
+// The same on whole rows through LDS (one workgroup per row, lane = cell). The
+// locations of a row's cells are, on even steps, the row's own block of 27 nx
+// values, on odd ones nine blocks of 3 nx values (the three planes that differ
+// only in e_x of a row (y + e_y, z + e_z)); each is copied into LDS, updated
+// there and stored back as 16-byte vectors, at any alignment. A lane reads
+// and writes the same 27 places, shifted by e_x on odd steps: plane i of
+// x + e_i holds fbar_{26-i} and takes fbar~_i. Towards a wall the place is plane
+// 26 - i of the cell itself (the group opposite, in reverse order, not
+// shifted). So walls need no launch of their own, and the odd step no partial
+// lines: by lanes it wrote 109 to 115 bytes a cell of 108 (FP32).
+template <int S, bool WALLS, bool LES, bool FFIELD, bool VAR, bool ODD>
+__global__ void __launch_bounds__(512) k_step_inplace_row(typename Store<S>::T* buf,
+                                                          const typename Store<S>::R* __restrict__ force, const Geom g,
+                                                          const Launch<typename Store<S>::R> L) {
+    using R = typename Store<S>::R;
+    using T = typename Store<S>::T;
+    constexpr uint32_t V = 16 / sizeof(T);
+    extern __shared__ __align__(16) unsigned char lds_bytes[];
+    T* const sm = (T*)lds_bytes;
+    int bx, y, z;
+    block_coords(g.xcd, bx, y, z);
+    const uint32_t tid = threadIdx.x, bd = blockDim.x, nx = (uint32_t)g.nx;
+    const uint32_t wave0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid & ~63u));
+    const bool act = tid < nx;
+    const uint32_t x = act ? tid : 0u;
+    constexpr int NB = ODD ? 9 : 1;
+    const uint32_t len = (ODD ? 3u : 27u) * nx, gs = group_stride<T>(nx);
+    const int ys[3] = {y == 0 ? g.ny - 1 : y - 1, y, y == g.ny - 1 ? 0 : y + 1};   // y + e_y
+    const int zs[3] = {z == 0 ? g.nz - 1 : z - 1, z, z == g.nz - 1 ? 0 : z + 1};
+    auto bounce = [&](int q) { return ODD && WALLS && ((q % 3 == 0 && y == 0) || (q % 3 == 2 && y == g.ny - 1)); };
+    T* A[NB];
+    uint32_t off[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+        const bool w = bounce(q);
+        A[q] = ODD ? buf + row_base(g, w ? 24 - 3 * q : 3 * q, w ? y : ys[q % 3], w ? z : zs[q / 3])
+                   : buf + row_base(g, 0, y, z);
+        off[q] = (uint32_t)((uintptr_t)A[q] & 15u) / (uint32_t)sizeof(T);
+        const u32x4* base = (const u32x4*)((uintptr_t)A[q] & ~(uintptr_t)15);
+        const uint32_t n = (off[q] + len + V - 1u) / V;
+        for (uint32_t k = 0; k < n; k += bd)
+            if (tid + k < n) copy16_to_lds(at_row(base, (tid + k) * 16u), lds_bytes + 16u * (q * (gs / V) + k + wave0));
+    }
+    R F[3];
+    row_force<R, FFIELD, false>(force, g, L, (int)x, y, z, F);
+    wait_lds_copies();
+    __syncthreads();
+    // where plane i's place is (c the lane's cell)
+    auto place = [&](int i, uint32_t c) {
+        const int ix = i % 3, q = i / 3;
+        if constexpr (!ODD) return off[0] + (uint32_t)i * nx + c;
+        const uint32_t xs[3] = {c == 0u ? nx - 1u : c - 1u, nx + c, 2u * nx + (c + 1u >= nx ? 0u : c + 1u)};
+        return q * gs + off[q] + (bounce(q) ? c + (uint32_t)(2 - ix) * nx : xs[ix]);
+    };
+    if (act) {
+        T t[27];
+#pragma unroll
+        for (int i = 0; i < 27; ++i) t[i] = sm[place(ODD ? 26 - i : i, x)];
+        R h[27], ls[9], ld[9], acc[3];
+        stored_line_sums<S, WALLS>(t, g, y, L, h, ls, ld);
+        collide_cell<S, LES, VAR, false>(g, L, (int)x, y, z, h, ls, ld, F, acc, nullptr);
+        uint32_t c = x;   // the places are formed again: held over the collision they cost 27 registers
+        asm volatile("" : "+v"(c));
+#pragma unroll
+        for (int i = 0; i < 27; ++i) sm[place(ODD ? i : 26 - i, c)] = to_store<S>(h[i], i, L.P.rho0);   // w_i = w_{26-i}
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NB; ++q) store_block<T>(A[q], off[q], len, sm + q * gs, tid, bd);
 }
 
 // ---------------------------------------------------------------- scatter of canonical populations
@@ -1135,21 +1185,16 @@ __global__ void __launch_bounds__(256) k_adjoint(const typename Store<S>::T* __r
     R lam[27];
 #pragma unroll
     for (int i = 0; i < 27; ++i) {
-        if constexpr (WALLS) {
-            const int iy = (i / 3) % 3;   // e_y = iy - 1
-            if ((iy == 0 && y == 0) || (iy == 2 && y == g.ny - 1)) {
-                const R* own = lam_in + nx * (((size_t)y + (size_t)g.ny * z) * 27 + (size_t)(26 - i));
-                lam[i] = __builtin_nontemporal_load((const R*)((const char*)own + xo[1]));
-                continue;
-            }
-        }
+        const int ix = i % 3, iy = (i / 3) % 3, iz = i / 9;
+        const bool wall = WALLS && ((iy == 0 && y == 0) || (iy == 2 && y == g.ny - 1));
         // as for the state: the rows read at x are read once (non-temporal),
         // the x-shifted ones keep ordinary loads so that the lines a wave
         // shares with its neighbour stay in L2 (non-temporal loads of the
         // aligned rows: 1,015 -> 1,000 us at 256^3, 124.7 -> 115.8 us at 128^3)
-        const R* rowp = lam_in + nx * (((size_t)yd[(i / 3) % 3] + (size_t)g.ny * zd[i / 9]) * 27 + (size_t)i);
-        if (i % 3 == 1) lam[i] = __builtin_nontemporal_load((const R*)((const char*)rowp + xo[1]));
-        else lam[i] = *(const R*)((const char*)rowp + xo[i % 3]);
+        const size_t r = (size_t)(wall ? y : yd[iy]) + (size_t)g.ny * (wall ? z : zd[iz]);
+        const R* rowp = lam_in + nx * (r * 27 + (size_t)(wall ? 26 - i : i));
+        if (ix == 1) lam[i] = __builtin_nontemporal_load((const R*)((const char*)rowp + xo[1]));
+        else lam[i] = *(const R*)((const char*)rowp + xo[wall ? 1 : ix]);
     }
     const size_t row = nx * ((size_t)y + (size_t)g.ny * z);
     R F[3], g0[3];
@@ -1283,7 +1328,7 @@ static dim3 grid_for_step(const Geom& g, int& bx) {
 }
 
 // With walls, only the rows y = 0 and y = ny - 1 need the bounce-back code.
-// Where lanes gather for themselves (wide rows, in-place streaming) the interior
+// Where lanes gather for themselves (wide rows, odd in-place steps) the interior
 // rows run the periodic kernel (its y +- 1 never wraps there) and the two wall
 // rows a kernel of their own, so that the wall terms and extra row pointers do
 // not burden the registers of every workgroup. The LDS-exchange kernel takes all
@@ -1500,6 +1545,23 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
     return hipGetLastError();
 }
 
+// In-place rows through LDS: 16 to 512 cells (FP64: 256, by its LDS), but rows that
+// start on cache lines keep the per-lane kernels in FP64 and on even steps, where
+// those access whole lines (us per step, pair by lanes / even by lanes and odd by
+// rows / both by rows: 256^3 FP32 646 / 602 / 621, 384 x 384 x 192 1,204 / 1,125 /
+// 1,140, 512 x 512 x 128 FP16 735 / 687 / 707, 256 x 100 x 100 FP64 190 / 194 /
+// 196; 300 x 200 x 100 FP32 332 / 283 / 229, 187 x 151 x 133 FP16 94 / 91 / 85,
+// 201 x 100 x 100 FP64 174 / 184 / 166); and with 4-byte values on rows of up to
+// 128 cells, where the per-lane kernels' two workgroups on a CU are two to four
+// waves, all goes by rows (64^3 FP32 22.9 / 16.7 / 10.7, 128^3 98 / 84 / 79).
+template <int S>
+static bool inplace_rows(const Geom& g) {
+    constexpr size_t es = sizeof(typename Store<S>::T);
+    if (g.lanegather || g.rowloop || g.nx < 16 || g.nx > (S == 0 ? 256 : 512)) return false;
+    if ((size_t)g.nx * es % 128 != 0 || (es == 4 && g.nx <= 128)) return true;
+    return S != 0 && g.aa == 2;
+}
+
 template <int S, bool W, bool LES, bool FF>
 static hipError_t step_inplace_t(const LaunchArgs& a, void* buf) {
     using T = typename Store<S>::T;
@@ -1509,6 +1571,19 @@ static hipError_t step_inplace_t(const LaunchArgs& a, void* buf) {
     const bool odd = a.g.aa == 2, var = (a.flags & 3u) != 0;
     hipStream_t st = (hipStream_t)a.stream;
     const Launch<R> L = make_launch<R>(a);
+    if (inplace_rows<S>(a.g)) {
+        const dim3 rows(1, a.g.ny, a.g.nz);
+        const unsigned lds = odd ? row_lds<T>(a.g) : (27u * (unsigned)a.g.nx * (unsigned)sizeof(T) + 16u + 15u) / 16u * 16u;
+        auto launch = [&](auto v, auto o) {
+            k_step_inplace_row<S, W, LES, FF, decltype(v)::value, decltype(o)::value>
+                <<<rows, row_lanes(a.g), lds, st>>>((T*)buf, (const R*)a.force_field, a.g, L);
+        };
+        if (odd && var) launch(std::true_type(), std::true_type());
+        else if (odd) launch(std::false_type(), std::true_type());
+        else if (var) launch(std::true_type(), std::false_type());
+        else launch(std::false_type(), std::false_type());
+        return hipGetLastError();
+    }
     const unsigned cap = sizeof(T) == 4 && a.g.nx <= 512 ? kLdsTwoPerCu : 0u;
     if (odd && var) k_step_inplace<S, W, LES, FF, true, true><<<grid, bx, cap, st>>>((T*)buf, (const R*)a.force_field, a.g, L);
     else if (odd) k_step_inplace<S, W, LES, FF, false, true><<<grid, bx, cap, st>>>((T*)buf, (const R*)a.force_field, a.g, L);
@@ -1525,6 +1600,9 @@ static hipError_t step_inplace_w(const LaunchArgs& a, void* buf) {
 template <int S>
 hipError_t step_inplace_s(const LaunchArgs& a, void* buf) {
     if (a.g.aa != 1 && a.g.aa != 2) return hipErrorInvalidValue;
+    // by rows, and on even steps, which only add the wall terms, walls need no launch of their own
+    if (inplace_rows<S>(a.g) || a.g.aa == 1)
+        return a.walls ? step_inplace_w<S, true>(a, buf) : step_inplace_w<S, false>(a, buf);
     return split_wall_rows(a, [&](const LaunchArgs& b, bool w) {
         return w ? step_inplace_w<S, true>(b, buf) : step_inplace_w<S, false>(b, buf);
     });

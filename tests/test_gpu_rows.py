@@ -151,3 +151,18 @@ def test_start_by_rows(storage, nx, ny, nz, walls):
         for i in range(27):
             e = (i // 9 - 1, (i // 3) % 3 - 1, i % 3 - 1)
             assert torch.equal(s[:, :, i], torch.roll(t[:, :, i], [-v for v in e], dims=(0, 1, 2)))
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f32s", "f16s"])
+@pytest.mark.parametrize("nx", [15, 16, 17, 64, 129, 187, 256, 257, 300, 512, 513])
+@pytest.mark.parametrize("walls", [False, True])
+def test_in_place_rows(storage, nx, walls):
+    """In-place steps by rows and by lanes (tuning bit 5), after even and odd
+    numbers of steps, and against the two-buffer steps."""
+    torch = _torch()
+    from paper_1202_6074_amd.lattice import Lattice   # noqa: F401
+    for ny in (1, 2, 5):
+        for steps, flags in ((1, {}), (3, {"factorized": True, "reduced_compressibility": True}), (4, {})):
+            a, b = _states((nx, ny, 4), storage, walls, steps, (0, 32), force=steps != 3, les=steps != 4, flags=flags,
+                           in_place=True)
+            assert torch.equal(a, b), (ny, steps)
