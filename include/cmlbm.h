@@ -252,6 +252,19 @@ cmlbm_status cmlbm_step(cmlbm_handle h, int64_t nsteps);
  * equal buffers, with the sub-grid force or with in-place streaming. */
 cmlbm_status cmlbm_step_from(cmlbm_handle h, const void* src, void* dst);
 
+/* nsteps >= 1 steps of cmlbm_step_from in one call, from src into dst, with the
+ * handle's own two buffers in between: neither src nor dst may be one of
+ * them (CMLBM_EINVAL, as what cmlbm_step_from refuses), and the handle's
+ * state is undefined afterwards until a state is set or copied into
+ * cmlbm_state_buffer. */
+cmlbm_status cmlbm_steps_between(cmlbm_handle h, const void* src, void* dst, int64_t nsteps);
+
+/* nsteps >= 0 steps of cmlbm_step_from in one call, every state kept: step k
+ * (k = 0 .. nsteps-1) reads first (k = 0) or the state of step k-1 and writes
+ * its state at rest + k * stride bytes (stride at least the size of a
+ * population buffer). The handle's state is unchanged. */
+cmlbm_status cmlbm_steps_record(cmlbm_handle h, const void* first, void* rest, size_t stride, int64_t nsteps);
+
 /* Device pointer of the buffer holding the current state fbar(n)
  * (Eq. cascadedLBE3) in the internal layout (for device-to-device
  * checkpoints), and its size in bytes (bytes may be null). */
@@ -325,6 +338,13 @@ cmlbm_status cmlbm_reduce_noalloc(cmlbm_handle h, double* out);
  * compressibility (Secs. 12-13) are differentiated too; the sub-grid stress
  * as a force is not (CMLBM_EINVAL). */
 cmlbm_status cmlbm_adjoint_step(cmlbm_handle h, const void* state, const void* lam_in, void* lam_out, void* grad_F);
+
+/* nsteps >= 0 adjoint steps in one call over states as cmlbm_steps_record
+ * leaves them, last to first: states k = nsteps-1 .. 0, state 0 at first, the
+ * others at rest + (k-1) * stride. lam and lam_tmp take turns; the result is in
+ * lam for an even number of steps and in lam_tmp for an odd one. */
+cmlbm_status cmlbm_adjoint_steps(cmlbm_handle h, const void* first, const void* rest, size_t stride, int64_t nsteps,
+                                 void* lam, void* lam_tmp, void* grad_F);
 
 /* Seeds for the loss E = sum_x rho |u|^2 / 2 at the state held in `state`,
  * with rho and u of Eqs. densitycalculation and velocitycalculation:

@@ -62,6 +62,8 @@ SIGNATURES = {
     "cmlbm_init_equilibrium": ([_H, _P, _P, ctypes.c_int], ctypes.c_int),
     "cmlbm_step": ([_H, ctypes.c_int64], ctypes.c_int),
     "cmlbm_step_from": ([_H, _P, _P], ctypes.c_int),
+    "cmlbm_steps_between": ([_H, _P, _P, ctypes.c_int64], ctypes.c_int),
+    "cmlbm_steps_record": ([_H, _P, _P, ctypes.c_size_t, ctypes.c_int64], ctypes.c_int),
     "cmlbm_state_buffer": ([_H, ctypes.POINTER(_P), ctypes.POINTER(ctypes.c_size_t)], ctypes.c_int),
     "cmlbm_read_moments": ([_H, _P, _P, ctypes.c_int], ctypes.c_int),
     "cmlbm_get_populations": ([_H, _P, ctypes.c_int], ctypes.c_int),
@@ -69,6 +71,7 @@ SIGNATURES = {
     "cmlbm_reduce": ([_H, ctypes.POINTER(ctypes.c_double)], ctypes.c_int),
     "cmlbm_reduce_noalloc": ([_H, _P], ctypes.c_int),
     "cmlbm_adjoint_step": ([_H, _P, _P, _P, _P], ctypes.c_int),
+    "cmlbm_adjoint_steps": ([_H, _P, _P, ctypes.c_size_t, ctypes.c_int64, _P, _P, _P], ctypes.c_int),
     "cmlbm_energy_seed": ([_H, _P, _P, _P], ctypes.c_int),
     "cmlbm_set_sgs_buffers": ([_H, _P, _P, ctypes.c_size_t], ctypes.c_int),
     "cmlbm_copy": ([_P, _P, ctypes.c_size_t, _P], ctypes.c_int),
@@ -146,6 +149,14 @@ def cmlbm_step_from(h: int, src: int, dst: int):
     _check(load().cmlbm_step_from(h, src, dst), "cmlbm_step_from")
 
 
+def cmlbm_steps_between(h: int, src: int, dst: int, nsteps: int):
+    _check(load().cmlbm_steps_between(h, src, dst, int(nsteps)), "cmlbm_steps_between")
+
+
+def cmlbm_steps_record(h: int, first: int, rest: int, stride: int, nsteps: int):
+    _check(load().cmlbm_steps_record(h, first, rest, stride, int(nsteps)), "cmlbm_steps_record")
+
+
 def cmlbm_state_buffer(h: int):
     p = _P()
     n = ctypes.c_size_t()
@@ -180,6 +191,10 @@ def cmlbm_reduce_noalloc(h: int, out: int):
 
 def cmlbm_adjoint_step(h: int, state: int, lam_in: int, lam_out: int, grad_F: int):
     _check(load().cmlbm_adjoint_step(h, state, lam_in, lam_out, grad_F), "cmlbm_adjoint_step")
+
+
+def cmlbm_adjoint_steps(h: int, first: int, rest: int, stride: int, nsteps: int, lam: int, lam_tmp: int, grad_F: int):
+    _check(load().cmlbm_adjoint_steps(h, first, rest, stride, int(nsteps), lam, lam_tmp, grad_F), "cmlbm_adjoint_steps")
 
 
 def cmlbm_energy_seed(h: int, state: int, lam_out: int, grad_F: int):

@@ -12,8 +12,9 @@ run in reverse. With K >= nsteps the forward run writes every
 state into a buffer of its own (nsteps population buffers, e.g. 113 GB for
 500 steps at 128^3 in FP32) and the backward pass runs the adjoint steps only,
 without recomputation; the gradient is bitwise the same. Every step's work is done by the library's
-HIP kernels (``cmlbm_step_from``, ``cmlbm_adjoint_step``,
-``cmlbm_energy_seed``, ``cmlbm_reduce``); torch provides buffers and copies.
+HIP kernels, a segment's steps in one call each (``cmlbm_steps_between``, ``cmlbm_steps_record``,
+``cmlbm_adjoint_steps``: a call per step cost the host more than a step of a small box takes), with
+``cmlbm_energy_seed`` and ``cmlbm_reduce``; torch provides buffers and copies.
 """
 from __future__ import annotations
 
@@ -35,30 +36,34 @@ def _forward(lat: Lattice, F: torch.Tensor, f0_state: torch.Tensor, nsteps: int,
         raise ValueError(f"nsteps must be >= 0 and K >= 1 (got nsteps={nsteps}, K={K})")
     lat.set_force((0.0, 0.0, 0.0), F)
     cur = lat.state_buffer()
-    cur.copy_(f0_state)
     if _keep_all(nsteps, K):
         # every state kept, ckpts[n] = fbar(n) for n < nsteps, in one allocation
         # whose last entry receives the last step and then holds fbar(nsteps)
         states = torch.empty((nsteps + 1,) + tuple(cur.shape), dtype=cur.dtype, device=cur.device)
-        ckpts = [states[n] for n in range(nsteps)]
-        ckpts[0].copy_(cur)
-        for n in range(nsteps - 1):
-            lat.step_from(ckpts[n], ckpts[n + 1])
-        final = states[nsteps]
-        lat.step_from(ckpts[nsteps - 1], final)
-        cur.copy_(final)   # the lattice's state is fbar(nsteps) afterwards, as with checkpoints
-        E = lat.reduce()["ke"]
-        return E, ckpts, final
-    # the checkpoints in one allocation (one request to the allocator instead of
-    # one per checkpoint)
-    states = torch.empty(((nsteps + K - 1) // K,) + tuple(cur.shape), dtype=cur.dtype, device=cur.device)
-    ckpts = []
-    for n0 in range(0, nsteps, K):
-        ckpts.append(states[n0 // K])
-        ckpts[-1].copy_(lat.state_buffer())
-        lat.step(min(K, nsteps - n0))
-    E = lat.reduce()["ke"]
-    return E, ckpts, lat.state_buffer().clone()
+        states[0].copy_(f0_state)
+        lat.steps_record(states[0], states[1:])
+        cur.copy_(states[nsteps])   # the lattice's state is fbar(nsteps) afterwards, as with checkpoints
+        return lat.reduce()["ke"], states[:nsteps], states[nsteps]
+    # the checkpoints, and the final state after them, in one allocation (one
+    # request to the allocator instead of one per checkpoint)
+    nseg = (nsteps + K - 1) // K
+    states = torch.empty((nseg + 1,) + tuple(cur.shape), dtype=cur.dtype, device=cur.device)
+    if lat.in_place or lat.sgs_force:
+        # one buffer, or the sub-grid stress of the step before: the lattice's own
+        # steps, a copy of its state after each segment (E only: no adjoint)
+        cur.copy_(f0_state)
+        for s in range(nseg):
+            states[s].copy_(lat.state_buffer())
+            lat.step(min(K, nsteps - s * K))
+        states[nseg].copy_(lat.state_buffer())
+    else:
+        # the last step of each segment writes the next checkpoint, the first step
+        # of each reads it: no copies of states but of the first and the last
+        states[0].copy_(f0_state)
+        for s in range(nseg):
+            lat.steps_between(states[s], states[s + 1], min(K, nsteps - s * K))
+        cur.copy_(states[nseg])
+    return lat.reduce()["ke"], states[:nseg], states[nseg]
 
 
 def _backward(lat: Lattice, F: torch.Tensor, ckpts, final: torch.Tensor, nsteps: int, K: int):
@@ -74,26 +79,16 @@ def _backward(lat: Lattice, F: torch.Tensor, ckpts, final: torch.Tensor, nsteps:
     if nsteps == 0:   # E of the initial state: F enters only through u's F/2 term
         return gF
     if _keep_all(nsteps, K):
-        for k in range(nsteps - 1, -1, -1):
-            lat.adjoint_step(ckpts[k], lam, lam2, gF)
-            lam, lam2 = lam2, lam
+        lat.adjoint_steps(ckpts[0], ckpts[1:], lam, lam2, gF)
         return gF
-    # stash[k] holds fbar(n0 + k) of the current segment; its first entry is the
-    # checkpoint itself (only read), so no copy of it is made; the others share
-    # one allocation (the first backward pass measured 1 % faster than with K - 1
-    # separate ones at 128^3, K = 50)
-    block = torch.empty((max(K - 1, 1),) + tuple(ckpts[0].shape), dtype=ckpts[0].dtype, device=ckpts[0].device)
-    stash = [None] + [block[k] for k in range(K - 1)]
-    nseg = len(ckpts)
-    for s in range(nseg - 1, -1, -1):
-        n0 = s * K
-        steps = min(K, nsteps - n0)
-        stash[0] = ckpts[s]
-        for k in range(steps - 1):
-            lat.step_from(stash[k], stash[k + 1])
-        for k in range(steps - 1, -1, -1):
-            lat.adjoint_step(stash[k], lam, lam2, gF)
-            lam, lam2 = lam2, lam
+    # the states of a segment after its checkpoint, which is only read and needs no
+    # copy (one allocation: the first backward pass measured 1 % faster than with
+    # K - 1 separate ones at 128^3, K = 50)
+    block = torch.empty((K - 1,) + tuple(ckpts[0].shape), dtype=ckpts[0].dtype, device=ckpts[0].device)
+    for s in range(len(ckpts) - 1, -1, -1):
+        rest = block[:min(K, nsteps - s * K) - 1]
+        lat.steps_record(ckpts[s], rest)
+        lam, lam2 = lat.adjoint_steps(ckpts[s], rest, lam, lam2, gF)
     return gF
 
 

@@ -392,11 +392,42 @@ cmlbm_status cmlbm_step_from(cmlbm_handle h, const void* src, void* dst) {
     return e == hipSuccess ? CMLBM_OK : hip_fail(e, "step_from");
 }
 
+// Bytes of one population state.
+static size_t state_bytes(cmlbm_handle h) {
+    return (size_t)lattice_q(h->a.lattice) * (size_t)h->a.g.N * elem_size(h->a.storage);
+}
+
+cmlbm_status cmlbm_steps_between(cmlbm_handle h, const void* src, void* dst, int64_t nsteps) {
+    if (cmlbm_status s = check_handle(h)) return s;
+    if (nsteps < 1) return fail(CMLBM_EINVAL, "nsteps must be >= 1");
+    for (const void* b : h->buf)
+        if (src == b || dst == b) return fail(CMLBM_EINVAL, "src and dst must not be the handle's buffers");
+    for (int64_t n = 0; n < nsteps; ++n) {
+        void* to = n == nsteps - 1 ? dst : h->buf[n & 1];
+        if (cmlbm_status s = cmlbm_step_from(h, src, to)) return s;
+        src = to;
+    }
+    return CMLBM_OK;
+}
+
+cmlbm_status cmlbm_steps_record(cmlbm_handle h, const void* first, void* rest, size_t stride, int64_t nsteps) {
+    if (cmlbm_status s = check_handle(h)) return s;
+    if (nsteps < 0) return fail(CMLBM_EINVAL, "nsteps must be >= 0");
+    if (nsteps && !rest) return fail(CMLBM_EINVAL, "rest must be non-null");
+    if (stride < state_bytes(h)) return fail(CMLBM_EINVAL, "stride is smaller than a population buffer");
+    for (int64_t n = 0; n < nsteps; ++n) {
+        void* to = (char*)rest + (size_t)n * stride;
+        if (cmlbm_status s = cmlbm_step_from(h, first, to)) return s;
+        first = to;
+    }
+    return CMLBM_OK;
+}
+
 cmlbm_status cmlbm_state_buffer(cmlbm_handle h, void** buf, size_t* bytes) {
     if (cmlbm_status s = check_handle(h)) return s;
     if (!buf) return fail(CMLBM_EINVAL, "buf must be non-null");
     *buf = h->buf[h->cur];
-    if (bytes) *bytes = (size_t)lattice_q(h->a.lattice) * (size_t)h->a.g.N * elem_size(h->a.storage);
+    if (bytes) *bytes = state_bytes(h);
     return CMLBM_OK;
 }
 
@@ -479,6 +510,22 @@ cmlbm_status cmlbm_adjoint_step(cmlbm_handle h, const void* state, const void* l
         return fail(CMLBM_EINVAL, "state, lam_in, lam_out, grad_F must be non-null and lam_in != lam_out");
     hipError_t e = cm::launch_adjoint(h->a, state, lam_in, lam_out, grad_F);
     return e == hipSuccess ? CMLBM_OK : hip_fail(e, "adjoint_step");
+}
+
+cmlbm_status cmlbm_adjoint_steps(cmlbm_handle h, const void* first, const void* rest, size_t stride, int64_t nsteps,
+                                 void* lam, void* lam_tmp, void* grad_F) {
+    if (cmlbm_status s = check_handle(h)) return s;
+    if (nsteps < 0) return fail(CMLBM_EINVAL, "nsteps must be >= 0");
+    if (nsteps > 1 && !rest) return fail(CMLBM_EINVAL, "rest must be non-null");
+    if (stride < state_bytes(h)) return fail(CMLBM_EINVAL, "stride is smaller than a population buffer");
+    for (int64_t n = nsteps - 1; n >= 0; --n) {
+        const void* state = n ? (const char*)rest + (size_t)(n - 1) * stride : first;
+        if (cmlbm_status s = cmlbm_adjoint_step(h, state, lam, lam_tmp, grad_F)) return s;
+        void* t = lam;
+        lam = lam_tmp;
+        lam_tmp = t;
+    }
+    return CMLBM_OK;
 }
 
 cmlbm_status cmlbm_energy_seed(cmlbm_handle h, const void* state, void* lam_out, void* grad_F) {

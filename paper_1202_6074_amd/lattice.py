@@ -68,6 +68,7 @@ class Lattice:
         self.sdtype = STORAGE_DTYPE[self.storage]
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
         self.in_place = bool(in_place)
+        self.sgs_force = False
         self.buf = [torch.empty((self.Q, self.nz, self.ny, self.nx), dtype=self.sdtype, device=self.device)
                     for _ in range(1 if self.in_place else 2)]
         desc = L.Desc()
@@ -102,6 +103,7 @@ class Lattice:
                    | (L.SGS_FORCE if sgs_force else 0))
         r.reserved = 0
         L.cmlbm_set_relaxation(self.h, r)
+        self.sgs_force = bool(sgs_force)
         if sgs_force and getattr(self, "stress", None) is None:
             planes = 3 if self.lattice == L.D2Q9 else 6
             self.stress = [torch.zeros((planes, self.nz, self.ny, self.nx), dtype=self.dtype, device=self.device)
@@ -187,6 +189,29 @@ class Lattice:
         L.cmlbm_step_from(self.h, src.data_ptr(), dst.data_ptr())
         self._after_use(src, dst)
 
+    def steps_between(self, src: torch.Tensor, dst: torch.Tensor, nsteps: int):
+        """nsteps >= 1 steps from src into dst (step_from in one call), with the
+        lattice's own buffers in between: its state is undefined afterwards."""
+        for t, nm in ((src, "src"), (dst, "dst")):
+            _check_tensor(t, self.Q * self.N, self.sdtype, self.device, nm)
+        L.cmlbm_steps_between(self.h, src.data_ptr(), dst.data_ptr(), nsteps)
+        self._after_use(src, dst)
+
+    def steps_record(self, first: torch.Tensor, rest: torch.Tensor):
+        """Steps from the state `first`, as many as `rest` has entries, each state
+        into the next entry of rest (step_from in one call)."""
+        self._check_states(first, rest)
+        L.cmlbm_steps_record(self.h, first.data_ptr(), rest.data_ptr(), self._state_bytes(), rest.shape[0])
+        self._after_use(first, rest)
+
+    def _state_bytes(self) -> int:
+        return self.buf[0].numel() * self.buf[0].element_size()
+
+    def _check_states(self, first, rest):
+        _check_tensor(first, self.Q * self.N, self.sdtype, self.device, "first")
+        n = rest.shape[0] if isinstance(rest, torch.Tensor) and rest.dim() else 0
+        _check_tensor(rest, n * self.Q * self.N, self.sdtype, self.device, "rest")
+
     def state_buffer(self) -> torch.Tensor:
         ptr, _ = L.cmlbm_state_buffer(self.h)
         for b in self.buf:
@@ -237,6 +262,19 @@ class Lattice:
         self._check_adjoint_args(state, lam_in, lam_out, grad_F)
         L.cmlbm_adjoint_step(self.h, state.data_ptr(), lam_in.data_ptr(), lam_out.data_ptr(), grad_F.data_ptr())
         self._after_use(state, lam_in, lam_out, grad_F)
+
+    def adjoint_steps(self, first: torch.Tensor, rest: torch.Tensor, lam: torch.Tensor, lam_tmp: torch.Tensor,
+                      grad_F: torch.Tensor):
+        """adjoint_step over the states `rest` (last to first) and then `first` in one
+        call. lam and lam_tmp take turns: returns (the one that holds the result,
+        the other)."""
+        self._check_states(first, rest)
+        self._check_adjoint_args(first, lam, lam_tmp, grad_F)
+        n = rest.shape[0] + 1
+        L.cmlbm_adjoint_steps(self.h, first.data_ptr(), rest.data_ptr(), self._state_bytes(), n, lam.data_ptr(),
+                              lam_tmp.data_ptr(), grad_F.data_ptr())
+        self._after_use(first, rest, lam, lam_tmp, grad_F)
+        return (lam_tmp, lam) if n % 2 else (lam, lam_tmp)
 
     def _check_adjoint_args(self, state, lam_in, lam_out, grad_F):
         _check_tensor(state, 27 * self.N, self.sdtype, self.device, "state")

@@ -325,3 +325,73 @@ def test_gradient_with_sec12_13_operators_fp64_matches_autograd(fact, rc, cs, wa
     assert abs(E - E_ref) < 1e-13 * abs(E_ref)
     g = g.cpu().numpy().reshape(3, -1)
     assert np.abs(g - g_ref).max() < 1e-10 * np.abs(g_ref).max()
+
+
+@pytest.mark.parametrize("walls", [False, True])
+@pytest.mark.parametrize("n", [1, 2, 5])
+def test_segments_in_one_call_equal_their_steps(walls, n):
+    """steps_between, steps_record and adjoint_steps against the calls for one step
+    (bitwise), and what they refuse."""
+    torch = _torch()
+    from paper_1202_6074_amd import _lib
+    from paper_1202_6074_amd.lattice import Lattice
+    nx, ny, nz = 12, 7, 5
+    g = torch.Generator().manual_seed(n)
+    lat = Lattice((nx, ny, nz), storage="f32", walls=walls)
+    lat.set_relaxation(1.7, cs_smag=0.12)
+    lat.set_force(field=(1e-3 * torch.randn((3, nz, ny, nx), generator=g)).cuda())
+    lat.init_equilibrium((0.05 * torch.randn((3, nz, ny, nx), generator=g)).cuda())
+    states = torch.empty((n + 1,) + tuple(lat.buf[0].shape), device="cuda")
+    states[0].copy_(lat.state_buffer())
+    for k in range(n):
+        lat.step_from(states[k], states[k + 1])
+    kept = torch.empty_like(states[1:])
+    lat.steps_record(states[0], kept)
+    assert torch.equal(kept, states[1:])
+    last = torch.empty_like(states[0])
+    lat.steps_between(states[0], last, n)
+    assert torch.equal(last, states[n])
+    lam = torch.randn((nz, ny, 27, nx), generator=g).cuda()
+    out = []
+    for one_call in (False, True):
+        a, b, gF = lam.clone(), torch.empty_like(lam), torch.zeros((3, nz, ny, nx), device="cuda")
+        if one_call:
+            a, b = lat.adjoint_steps(states[0], states[1:n], a, b, gF)
+        else:
+            for k in range(n - 1, -1, -1):
+                lat.adjoint_step(states[k], a, b, gF)
+                a, b = b, a
+        out.append((a, gF))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    with pytest.raises(_lib.CmlbmError):   # the lattice's own buffers hold the states in between
+        lat.steps_between(lat.buf[0], last, n)
+    with pytest.raises(_lib.CmlbmError):
+        lat.steps_between(states[0], last, 0)
+    with pytest.raises(_lib.CmlbmError):
+        _lib.cmlbm_steps_record(lat.h, states[0].data_ptr(), kept.data_ptr(), 4, n)
+
+
+@pytest.mark.parametrize("kind", [dict(in_place=True), dict(sgs=True), dict(lattice="d2q9")])
+def test_energy_of_lattices_without_an_adjoint(kind):
+    """The forward pass gives E also where there is no adjoint step."""
+    torch = _torch()
+    from paper_1202_6074_amd.adjoint import EnergyAdjoint
+    from paper_1202_6074_amd.lattice import Lattice
+    shape = (12, 8) if "lattice" in kind else (12, 8, 6)
+    g = torch.Generator().manual_seed(3)
+    E = []
+    for by_hand in (False, True):
+        lat = Lattice(shape, storage="f64", in_place=kind.get("in_place", False), lattice=kind.get("lattice", "d3q27"))
+        lat.set_relaxation(1.7, cs_smag=0.2, sgs_force=kind.get("sgs", False))
+        if not by_hand:
+            F = (1e-4 * torch.randn((lat.D, lat.nz, lat.ny, lat.nx), generator=g, dtype=torch.float64)).cuda()
+            u = (0.05 * torch.randn((lat.D, lat.nz, lat.ny, lat.nx), generator=g, dtype=torch.float64)).cuda()
+        lat.init_equilibrium(u)
+        if by_hand:
+            lat.set_force(field=F)
+            lat.step(5)
+            E.append(lat.reduce()["ke"])
+        else:
+            E.append(float(EnergyAdjoint.apply(F, lat, lat.state_buffer().clone(), 5, 2)))
+            assert lat.reduce()["ke"] == E[0]
+    assert E[0] == E[1]
