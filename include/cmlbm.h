@@ -135,24 +135,16 @@ typedef struct {
                                bits 0-1 must be 0; bits above 7 too;
                                bit 2: one block per grid row in the step
                                kernel (looping over x); bits 3-4 workgroup
-                               order of the step kernel: 0 library default
-                               (XCD-aware for FP64 storage and when a row
-                               spans several workgroups, nx > 256 without
-                               bit 2; runs of 32 for periodic D3Q27 FP32 and
-                               FP32-shifted rows of 129-256 cells without
-                               bit 2, except the sub-grid-force step; runs of
-                               256 for FP16 rows of the two-cells-per-lane
-                               kernel; plain otherwise), 1
-                               plain, 2 XCD-aware (each XCD takes a
-                               contiguous range of rows), 3 runs of 32
-                               consecutive workgroups per XCD in turn
-                               (orders whose workgroup count is not a
-                               multiple of 8, resp. 256, fall back to
-                               plain);
+                               order of the step kernel: 0 library default,
+                               by storage and row length, 1 plain, 2 XCD-aware
+                               (each XCD takes a contiguous range of rows), 3
+                               runs of 32 consecutive workgroups per XCD in
+                               turn (the workgroups after the last full round
+                               in the plain order); steps with several rows
+                               per workgroup always run in the plain order;
                                bit 5: per-lane shifted loads in the step
-                               kernel also where one workgroup covers a row
-                               (no LDS exchange; also no two-cell FP16
-                               kernel); bit 6: FP16 storage, one cell per lane
+                               kernel for all rows (no LDS, one row per
+                               workgroup, no two-cell FP16 kernel); bit 6: FP16 storage, one cell per lane
                                also on even rows of at most 512 cells (no
                                two-cell kernel); bit 7: every step and
                                adjoint step in one launch (by default the

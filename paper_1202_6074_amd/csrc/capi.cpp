@@ -248,6 +248,9 @@ cmlbm_status cmlbm_create(const cmlbm_desc* d, void* buf_a, void* buf_b, size_t 
         a.g.ybase = 0;
         a.g.ystride = 1;
         a.g.yrows = d->ny;
+        a.g.zbase = 0;
+        a.g.pack = 0;
+        a.g.packm = 0;
     }
     a.lattice = d->lattice;
     a.storage = d->storage;

@@ -488,6 +488,62 @@ __device__ __forceinline__ void gather_rows(const typename Store<S>::T* __restri
     }
 }
 
+// ---------------------------------------------------------------- several rows per workgroup
+// Short rows: the lanes of a workgroup take g.pack rows y, y + 1, ... of one z in
+// turn, so that the row, unlike everywhere else, is the lane's own. Returns
+// whether the lane has a cell (else x, y are some cell's). Grid: x over groups
+// of g.pack rows, y over z.
+__device__ __forceinline__ bool packed_cell(const Geom& g, int& x, int& y, int& z) {
+    const uint32_t tid = threadIdx.x;
+    const uint32_t r = (tid * g.packm) >> 16;   // tid / nx: exact for tid < 256 and nx <= 256
+    x = (int)(tid - r * (uint32_t)g.nx);
+    y = (int)(blockIdx.x * (uint32_t)g.pack + r);
+    z = (int)blockIdx.y + g.zbase;
+    const bool act = r < (uint32_t)g.pack && y < g.ny;
+    if (!act) {
+        x = 0;
+        y = g.ny - 1;
+    }
+    return act;
+}
+
+// Plane i of an array in the populations' row layout at (x, y, z) + SGN e_i for
+// all i, x and y the lane's own, z uniform: a row pointer per (plane, z) that
+// is the same for the whole workgroup and 32-bit lane offsets, nine of them for
+// the nine (e_x, e_y) (a z-plane of such rows is shorter than 2^32 bytes). The
+// lanes of a row read it in one instruction, so the shifted reads touch no more
+// lines than the others. WALLS: where y + SGN e_y lies beyond a wall, plane 26 - i of the
+// cell itself.
+template <int SGN, bool WALLS, bool NT, typename T>
+__device__ __forceinline__ void gather_packed(const T* src, const Geom& g, int x, int y, int z, T (&t)[27]) {
+    const uint32_t es = (uint32_t)sizeof(T), rl = 27u * (uint32_t)g.nx * es;
+    const uint32_t xm = (uint32_t)(x == 0 ? g.nx - 1 : x - 1) * es, xp = (uint32_t)(x == g.nx - 1 ? 0 : x + 1) * es;
+    const uint32_t ym = (uint32_t)(y == 0 ? g.ny - 1 : y - 1) * rl, yp = (uint32_t)(y == g.ny - 1 ? 0 : y + 1) * rl;
+    const int zm = z == 0 ? g.nz - 1 : z - 1, zp = z == g.nz - 1 ? 0 : z + 1;
+    const uint32_t xo[3] = {SGN < 0 ? xp : xm, (uint32_t)x * es, SGN < 0 ? xm : xp};
+    const uint32_t yo[3] = {SGN < 0 ? yp : ym, (uint32_t)y * rl, SGN < 0 ? ym : yp};
+    const int zo[3] = {SGN < 0 ? zp : zm, z, SGN < 0 ? zm : zp};
+    auto at = [&](int i, int zz, uint32_t o) {
+        const auto p = at_row(src + ((size_t)zz * g.ny * 27 + i) * g.nx, o);
+        if constexpr (NT) return __builtin_nontemporal_load(p);
+        else return *p;
+    };
+#pragma unroll
+    for (int i = 0; i < 27; ++i) t[i] = at(i, zo[i / 9], yo[(i / 3) % 3] + xo[i % 3]);
+    if constexpr (WALLS) {
+        if (y == 0) {
+#pragma unroll
+            for (int i = 0; i < 27; ++i)
+                if ((i / 3) % 3 == (SGN < 0 ? 2 : 0)) t[i] = at(26 - i, z, yo[1] + xo[1]);
+        }
+        if (y == g.ny - 1) {
+#pragma unroll
+            for (int i = 0; i < 27; ++i)
+                if ((i / 3) % 3 == (SGN < 0 ? 0 : 2)) t[i] = at(26 - i, z, yo[1] + xo[1]);
+        }
+    }
+}
+
 template <typename R, bool FFIELD>
 __device__ __forceinline__ void cell_force(const R* __restrict__ force, const Geom g, int c, const Launch<R>& L, R& Fx,
                                            R& Fy, R& Fz) {
@@ -693,6 +749,67 @@ __global__ void __launch_bounds__(512) k_step_row(const typename Store<S>::T* __
         }
         __syncthreads();
         store_block<T>(D, o, 27u * nx, sm, tid, blockDim.x);
+    }
+}
+
+// ---------------------------------------------------------------- step, several rows per workgroup
+// The step on short rows, which leave lanes of a row's own workgroup idle: bound
+// by instruction issue and latency there, by HBM when the lanes are full (20 x
+// 200 x 200 FP32 48.7 us a step by row, 34.4 packed, 5.3 TB/s; 32 x 200 x 200 FP16
+// 42.0 and 28.1). No exchange of shifted values: gather_packed.
+// DIRECT: rows of whole cache lines: each lane stores its own values; else the
+// workgroup's rows, one block of 27 nx values each and one after the other, go
+// through LDS and are stored in whole vectors.
+template <int S, bool WALLS, bool LES, bool FFIELD, bool VAR, bool SGS, bool DIRECT>
+__global__ void __launch_bounds__(256) k_step_packed(const typename Store<S>::T* __restrict__ src,
+                                                     typename Store<S>::T* __restrict__ dst,
+                                                     const typename Store<S>::R* __restrict__ force, const Geom g,
+                                                     const Launch<typename Store<S>::R> L,
+                                                     const typename Store<S>::R* __restrict__ rs_prev = nullptr,
+                                                     typename Store<S>::R* __restrict__ rs_next = nullptr) {
+    using R = typename Store<S>::R;
+    using T = typename Store<S>::T;
+    int x, y, z;
+    const bool act = packed_cell(g, x, y, z);
+    T t[27];
+    R sv[SGS ? 18 : 1], F[3], acc[3];
+    gather_packed<-1, WALLS, DIRECT>(src, g, x, y, z, t);
+    if constexpr (SGS) sgs_load<R, false>(rs_prev, g, x, y, z, sv);
+    row_force<R, FFIELD, false>(force, g, L, x, y, z, F);
+    if constexpr (DIRECT) {
+        if (!act) return;
+    }
+    const uint32_t nx = (uint32_t)g.nx;
+    extern __shared__ __align__(16) unsigned char lds_bytes[];
+    T* const sm = (T*)lds_bytes;
+    const int y0 = (int)(blockIdx.x * (uint32_t)g.pack);
+    T* const D = dst + row_base(g, 0, y0, z);   // the workgroup's block
+    const uint32_t o = (uint32_t)((uintptr_t)D & 15u) / (uint32_t)sizeof(T);
+    if (act) {
+        R h[27], ls[9], ld[9];
+        stored_line_sums<S, WALLS>(t, g, y, L, h, ls, ld);
+        if constexpr (SGS) sgs_combine(sv, acc);
+        collide_cell<S, LES, VAR, SGS>(g, L, x, y, z, h, ls, ld, F, acc, rs_next);
+        uint32_t at = (uint32_t)(y - y0) * 27u * nx + (uint32_t)x;
+        if constexpr (DIRECT) {
+            at *= (uint32_t)sizeof(T);
+#pragma unroll
+            for (int i = 0; i < 27; ++i)
+                __builtin_nontemporal_store(to_store<S>(h[i], i, L.P.rho0), at_row(D + (size_t)i * nx, at));
+        } else {
+            at += o;
+#pragma unroll
+            for (int i = 0; i < 27; ++i) {
+                sm[at] = to_store<S>(h[i], i, L.P.rho0);
+                at += nx;
+                asm volatile("" : "+v"(at));
+            }
+        }
+    }
+    if constexpr (!DIRECT) {
+        __syncthreads();
+        const uint32_t rows = (uint32_t)(g.ny - y0 < g.pack ? g.ny - y0 : g.pack);
+        store_block<T>(D, o, rows * 27u * nx, sm, threadIdx.x, blockDim.x);
     }
 }
 
@@ -1156,7 +1273,8 @@ __global__ void __launch_bounds__(ROWS ? 512 : 256) k_read(const typename Store<
 // opposite population of its own cell (plus a constant), so there
 // lam~_i(x) = lam_{26-i}(x, n+1). LES: the collision with the eddy rate;
 // VAR: with the Sec. 12-13 operators (L.P.rc, L.P.fact).
-template <int S, bool FFIELD, bool WALLS, bool LES, bool VAR>
+// PACKED: several rows per workgroup (packed_cell), for short rows.
+template <int S, bool FFIELD, bool WALLS, bool LES, bool VAR, bool PACKED>
 __global__ void __launch_bounds__(256) k_adjoint(const typename Store<S>::T* __restrict__ state,
                                                  const typename Store<S>::R* __restrict__ lam_in,
                                                  typename Store<S>::R* __restrict__ lam_out,
@@ -1164,15 +1282,27 @@ __global__ void __launch_bounds__(256) k_adjoint(const typename Store<S>::T* __r
                                                  const typename Store<S>::R* __restrict__ force, const Geom g,
                                                  const Launch<typename Store<S>::R> L) {
     using R = typename Store<S>::R;
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y, z = blockIdx.z + g.zbase;
-    if (x >= g.nx) return;
+    int x, y, z;
+    if constexpr (PACKED) {
+        if (!packed_cell(g, x, y, z)) return;
+    } else {
+        x = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+        y = (int)blockIdx.y;
+        z = (int)blockIdx.z + g.zbase;
+        if (x >= g.nx) return;
+    }
     // fbar(n): ordinary loads also for the x-shifted rows, so that the cache
     // lines a wave shares with its neighbour stay in L2 for the second reader
     // (with non-temporal loads they were fetched from HBM again: 256 against
     // 240 B/cell of reads, 3 % slower at 256^3)
     R h[27];
-    gather<S, WALLS, 0, false>(state, g, x, y, z, L, h);
+    if constexpr (PACKED) {
+        typename Store<S>::T t[27];
+        gather_packed<-1, WALLS, false>(state, g, x, y, z, t);
+        stored_devs<S, WALLS>(t, g, y, L, h);
+    } else {
+        gather<S, WALLS, 0, false>(state, g, x, y, z, L, h);
+    }
     // lambda at x + e_i: the rows (y + ey, z + ez) are block-uniform (scalar
     // registers); only the x offset (x - 1, x, x + 1 with wrap) is per lane.
     // (An LDS exchange of the x-shifted values, as in the step kernel, was
@@ -1183,8 +1313,9 @@ __global__ void __launch_bounds__(256) k_adjoint(const typename Store<S>::T* __r
     const int yd[3] = {y == 0 ? g.ny - 1 : y - 1, y, y == g.ny - 1 ? 0 : y + 1};
     const int zd[3] = {z == 0 ? g.nz - 1 : z - 1, z, z == g.nz - 1 ? 0 : z + 1};
     R lam[27];
+    if constexpr (PACKED) gather_packed<1, WALLS, false>(lam_in, g, x, y, z, lam);
 #pragma unroll
-    for (int i = 0; i < 27; ++i) {
+    for (int i = 0; i < (PACKED ? 0 : 27); ++i) {
         const int ix = i % 3, iy = (i / 3) % 3, iz = i / 9;
         const bool wall = WALLS && ((iy == 0 && y == 0) || (iy == 2 && y == g.ny - 1));
         // as for the state: the rows read at x are read once (non-temporal),
@@ -1204,8 +1335,13 @@ __global__ void __launch_bounds__(256) k_adjoint(const typename Store<S>::T* __r
     for (int d = 0; d < 3; ++d) g0[d] = grad_F[(size_t)d * N + row + x];
     R gF[3] = {R(0), R(0), R(0)};
     collide_adjoint<R, LES, VAR>(h, lam, F[0], F[1], F[2], L.P, gF);
+    if constexpr (PACKED) {
+        const uint32_t o = ((uint32_t)y * 27u * (uint32_t)g.nx + (uint32_t)x) * (uint32_t)sizeof(R);
 #pragma unroll
-    for (int i = 0; i < 27; ++i) __builtin_nontemporal_store(lam[i], lam_out + (row * 27 + (size_t)i * nx) + x);
+        for (int i = 0; i < 27; ++i) *at_row(lam_out + ((size_t)z * g.ny * 27 + i) * nx, o) = lam[i];
+    }
+#pragma unroll
+    for (int i = 0; i < (PACKED ? 0 : 27); ++i) __builtin_nontemporal_store(lam[i], lam_out + (row * 27 + (size_t)i * nx) + x);
 #pragma unroll
     for (int d = 0; d < 3; ++d) grad_F[(size_t)d * N + row + x] = g0[d] + gF[d];
 }
@@ -1431,6 +1567,40 @@ static int row_lanes(const Geom& g) { return (g.nx + 63) / 64 * 64; }
 template <typename T>
 static unsigned row_lds(const Geom& g) { return 9u * group_stride<T>((uint32_t)g.nx) * (unsigned)sizeof(T); }
 
+// Several rows per workgroup (packed_cell): the lanes of a workgroup, 128 or 256,
+// whichever its whole rows fill better (47 cells: 94 of 128, 235 of 256); where
+// they are level 256, but 128 for fewer than 1,024 workgroups (step of 32^3 FP64
+// 5.3 us in 128 lanes, 6.1 in 256; of 20 x 200 x 200 FP32 35.4 and 34.4).
+static int pack_lanes(const Geom& g) {
+    const int r1 = 128 / g.nx, r2 = 256 / g.nx;
+    if (2 * r1 < r2) return 256;
+    return (int64_t)((g.ny + r2 - 1) / r2) * g.nz < 1024 && r1 ? 128 : 256;
+}
+// The launch geometry for `lanes` lanes (at least nx).
+static dim3 pack_rows(Geom& g, int lanes) {
+    const int r = lanes / g.nx;
+    g.pack = r < g.ny ? r : g.ny;
+    g.packm = (uint32_t)((65536 + g.nx - 1) / g.nx);
+    return dim3((g.ny + g.pack - 1) / g.pack, g.nz);
+}
+// Short rows whose step packs several rows into a workgroup: where that fills at
+// least 1.4 times the lanes of one row in workgroups of whole waves (1.2 in
+// FP16, which is bound by instruction issue). us per step, row / packed: 20 x 200
+// x 200 FP32 48.7 / 34.4, FP16 42.5 / 22.1; 32 x 200 x 200 FP32 50.7 / 48.0, FP16
+// 42.0 / 28.1, FP64 107 / 94; 70 x 200 x 100 FP16 43.7 / 33.3, FP32 57.9 / 56.7; with
+// less to fill 45 x 60 x 80 FP32 12.2 / 13.0, 96^3 36.4 / 38.5, 128^3 75.7 / 83.1. But FP32
+// rows of whole cache lines of lattices inside the L2s, where launches and
+// latency count (32^3 4.7 / 4.9).
+template <int S>
+static bool packed_rows(const Geom& g) {
+    constexpr size_t es = sizeof(typename Store<S>::T);
+    if (g.lanegather || g.rowloop || g.nx < 8 || g.nx > 128) return false;
+    if (es == 4 && g.nx % 32 == 0 && !past_l2<S>(g)) return false;
+    const int lanes = pack_lanes(g), fill = lanes / g.nx * g.nx;
+    const int row = (g.nx + 63) / 64 * 64;
+    return (double)fill * row >= (es == 2 ? 1.2 : 1.4) * g.nx * lanes;
+}
+
 // Calls f with the row width XL of the LDS-exchange kernel as a compile-time
 // constant: the workgroup's width for this row length (grid_for_step).
 template <typename F>
@@ -1491,6 +1661,18 @@ static hipError_t launch_z_chunks(const Geom& g, const dim3& grid, bool chunked,
     return hipSuccess;
 }
 
+// launch(grid, lanes, LDS, geometry, whether rows are whole cache lines) of a
+// step with several rows per workgroup.
+template <int S, typename F>
+static void launch_packed(const LaunchArgs& a, F&& launch) {
+    constexpr size_t es = sizeof(typename Store<S>::T);
+    Geom gp = a.g;
+    const int lanes = pack_lanes(a.g);
+    const dim3 gq = pack_rows(gp, lanes);
+    if ((size_t)gp.nx * es % 128 == 0) launch(gq, lanes, 0u, gp, std::true_type());
+    else launch(gq, lanes, (unsigned)(((size_t)gp.pack * 27 * gp.nx * es + 47) / 16 * 16), gp, std::false_type());
+}
+
 template <int S, bool W, bool LES, bool FF>
 static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
     using T = typename Store<S>::T;
@@ -1513,6 +1695,14 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
             else k_step_f16pair<LES, FF, false><<<gp, bp, pcap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
             return hipGetLastError();
         }
+    }
+    if (packed_rows<S>(a.g)) {
+        launch_packed<S>(a, [&](const dim3& gq, int lanes, unsigned lds, const Geom& gp, auto d) {
+            constexpr bool D = decltype(d)::value;
+            if (var) k_step_packed<S, W, LES, FF, true, false, D><<<gq, lanes, lds, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gp, L);
+            else k_step_packed<S, W, LES, FF, false, false, D><<<gq, lanes, lds, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gp, L);
+        });
+        return hipGetLastError();
     }
     if (whole_rows<S>(a.g)) {
         // rows that start on cache lines (wider than 256 cells: the others of
@@ -1627,6 +1817,14 @@ static hipError_t step_sgs_t(const LaunchArgs& a, const void* src, void* dst) {
     if (a.xcd_default && g.xcd >= 2) g.xcd = 0;
     // FP32 rows of one workgroup in chunks of planes, as the step without the
     // stress force (256^3: 769.4 -> 761.2 us)
+    if (packed_rows<S>(g)) {
+        launch_packed<S>(a, [&](const dim3& gq, int lanes, unsigned lds, const Geom& gp, auto d) {
+            constexpr bool D = decltype(d)::value;
+            if (var) k_step_packed<S, false, false, FF, true, true, D><<<gq, lanes, lds, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gp, L, rp, rn);
+            else k_step_packed<S, false, false, FF, false, true, D><<<gq, lanes, lds, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gp, L, rp, rn);
+        });
+        return hipGetLastError();
+    }
     if (whole_rows<S>(g)) {
         const bool direct = (size_t)g.nx * sizeof(T) % 128 == 0;
         return launch_z_chunks(g, dim3(1, g.ny, g.nz), sizeof(T) == 4, [&](const dim3& gq, const Geom& gg) {
@@ -1667,7 +1865,7 @@ hipError_t step_w(const LaunchArgs& a, const void* src, void* dst) {
         if (a.walls || !a.stress_prev || !a.stress_next) return hipErrorInvalidValue;   // checked by the caller
         return a.force_field ? step_sgs_t<S, true>(a, src, dst) : step_sgs_t<S, false>(a, src, dst);
     }
-    if (whole_rows<S>(a.g) || one_block_per_row(a.g))
+    if (packed_rows<S>(a.g) || whole_rows<S>(a.g) || one_block_per_row(a.g))
         return a.walls ? step_les<S, true>(a, src, dst) : step_les<S, false>(a, src, dst);
     return split_wall_rows(a, [&](const LaunchArgs& b, bool w) {
         return w ? step_les<S, true>(b, src, dst) : step_les<S, false>(b, src, dst);
@@ -1757,6 +1955,23 @@ static hipError_t read_t(const LaunchArgs& a, const void* src, void* out0, void*
                    : read_o<S, W, false, false, float>(a, src, out0, out1);
 }
 
+// Rows whose adjoint step packs several into a workgroup: up to 64 cells, or where
+// that fills at least 1.2 times the lanes of one row (us, row / packed: 32 x 100 x
+// 100 FP32 28.2 / 21.9, 64 x 100 x 100 38.3 / 35.5, 70 x 100 x 100 56.7 / 43.8, 20 x 100 x 100 FP16
+// 22.8 / 14.8; 96^3 FP32 51.0 / 52.1, 128^3 119 / 137); and, one row in a workgroup, 4-byte rows
+// that are not whole 32-byte sectors, for the ordinary stores, which share
+// sectors between rows (150^3 269 / 234, 250 x 100 x 100 188 / 171, 101 x 90 x 80 52.9 / 46.7; of
+// whole sectors 120 x 100 x 100 74 / 82, 256 x 256 x 128 497 / 549).
+template <int S>
+static bool packed_adjoint(const Geom& g) {
+    if (g.nx < 8 || g.nx > 256) return false;
+    if (g.nx <= 64) return true;
+    if (sizeof(typename Store<S>::R) == 4 && g.nx % 8 != 0) return true;
+    if (g.nx > 128) return false;
+    const int lanes = pack_lanes(g), fill = lanes / g.nx * g.nx;
+    return fill * ((g.nx + 63) / 64 * 64) * 10 >= 12 * g.nx * lanes;
+}
+
 template <int S, bool FF, bool W, bool LES, bool VAR>
 static hipError_t adjoint_k(const LaunchArgs& a, const void* state, const void* lam_in, void* lam_out, void* grad_F) {
     using T = typename Store<S>::T;
@@ -1764,8 +1979,16 @@ static hipError_t adjoint_k(const LaunchArgs& a, const void* state, const void* 
     int bx;
     const dim3 grid = grid_for(a.g, bx);
     const auto L = make_launch<R>(a);
+    if (packed_adjoint<S>(a.g)) {
+        Geom gp = a.g;
+        const int lanes = a.g.nx > 128 ? bx : pack_lanes(a.g);
+        const dim3 gq = pack_rows(gp, lanes);
+        k_adjoint<S, FF, W, LES, VAR, true><<<gq, lanes, 0, (hipStream_t)a.stream>>>(
+            (const T*)state, (const R*)lam_in, (R*)lam_out, (R*)grad_F, (const R*)a.force_field, gp, L);
+        return hipGetLastError();
+    }
     return launch_z_chunks(a.g, grid, true, [&](const dim3& gq, const Geom& gg) {
-        k_adjoint<S, FF, W, LES, VAR><<<gq, bx, 0, (hipStream_t)a.stream>>>((const T*)state, (const R*)lam_in, (R*)lam_out,
+        k_adjoint<S, FF, W, LES, VAR, false><<<gq, bx, 0, (hipStream_t)a.stream>>>((const T*)state, (const R*)lam_in, (R*)lam_out,
                                                                             (R*)grad_F, (const R*)a.force_field, gg, L);
     });
 

@@ -21,6 +21,10 @@ struct Geom {
     // separately when there are walls)
     int ybase, ystride, yrows;
     int zbase;     // first z-plane of this launch (launches over chunks of planes)
+    // launches of several rows per workgroup (packed_cell): how many, and
+    // 65536 / nx rounded up, for the lane's row
+    int pack;
+    uint32_t packm;
 };
 
 struct LaunchArgs {

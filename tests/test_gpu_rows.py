@@ -166,3 +166,45 @@ def test_in_place_rows(storage, nx, walls):
             a, b = _states((nx, ny, 4), storage, walls, steps, (0, 32), force=steps != 3, les=steps != 4, flags=flags,
                            in_place=True)
             assert torch.equal(a, b), (ny, steps)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f32s", "f16s"])
+@pytest.mark.parametrize("nx", [8, 9, 16, 20, 32, 33, 40, 64, 70, 85, 100, 128])
+@pytest.mark.parametrize("walls", [False, True])
+def test_several_rows_per_workgroup(storage, nx, walls):
+    """Short rows packed into workgroups: heights below, at and above the number of
+    rows in one, few and many workgroups."""
+    torch = _torch()
+    for ny, nz in ((1, 3), (13, 2), (33, 40)):
+        for force, les, flags in ((True, True, {}), (False, False, {"factorized": True, "reduced_compressibility": True})):
+            a, b = _states((nx, ny, nz), storage, walls, 2, (0, 32), force, les, flags)
+            assert torch.equal(a, b), (ny, nz)
+        if not walls:
+            a, b = _states((nx, ny, nz), storage, False, 3, (0, 32), flags={"sgs_force": True})
+            assert torch.equal(a, b), (ny, nz)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("nx", [8, 20, 33, 64, 70, 75, 101, 250])
+@pytest.mark.parametrize("walls", [False, True])
+def test_adjoint_of_packed_rows(storage, nx, walls):
+    """An adjoint step against the one of the same fields repeated along x in rows of
+    more than 256 cells, which go one to a workgroup: bitwise the same."""
+    torch = _torch()
+    from paper_1202_6074_amd.lattice import Lattice
+    for ny, nz in ((1, 2), (11, 3), (30, 40)):
+        m = -(-257 // nx)
+        g = torch.Generator().manual_seed(nx + ny)
+        u = (0.05 * torch.randn((3, nz, ny, nx), generator=g, dtype=torch.float64)).cuda()
+        F = (1e-3 * torch.randn((3, nz, ny, nx), generator=g, dtype=torch.float64)).cuda()
+        lam0 = torch.randn((nz, ny, 27, nx), generator=g, dtype=torch.float64).cuda()
+        out = []
+        for rep in (1, m):
+            lat = Lattice((nx * rep, ny, nz), storage=storage, walls=walls, wall_u_hi=(0.02, 0.0, 0.01))
+            lat.set_relaxation(1.7, cs_smag=0.12)
+            lat.set_force(field=F.repeat(1, 1, 1, rep))
+            lat.init_equilibrium(u.repeat(1, 1, 1, rep))
+            lam, gF = lat.lam_buffer(), torch.ones((3, nz, ny, nx * rep), dtype=lat.dtype, device="cuda")
+            lat.adjoint_step(lat.state_buffer(), lam0.repeat(1, 1, 1, rep).to(lat.dtype), lam, gF)
+            out.append((lam, gF))
+        assert torch.equal(out[0][0].repeat(1, 1, 1, m), out[1][0]) and torch.equal(out[0][1].repeat(1, 1, 1, m), out[1][1])
