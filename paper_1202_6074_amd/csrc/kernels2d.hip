@@ -15,6 +15,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "cm_math2d.hpp"
 #include "kernels.hpp"
 #include "store.hpp"
@@ -73,8 +75,11 @@ __device__ __forceinline__ R wall_term(int i, const R (&U)[2], R rho0) {
     return R(6) * w9<R>(i) * rho0 * (R(ex) * U[0] + R(ey) * U[1]);
 }
 
-// Gather of fbar(n) at (x, y): y is uniform per block, so the nine source
-// rows are uniform pointers and only the x offset varies across lanes.
+// Gather of fbar(n) at (x, y): y is uniform per block, so the nine source rows
+// are uniform pointers and only the x offset varies across lanes. WALLS: a row
+// from a wall is the opposite one of the cell itself, a scalar select, and the
+// wall terms are added at the end (with a branch for each population the loads
+// were not in flight together: 300 x 3000 FP16 18.6 us a step, now 14.6).
 template <int S, bool WALLS, typename R = typename Store<S>::R>
 __device__ __forceinline__ void gather(const typename Store<S>::T* __restrict__ src, const Geom g, int x, int y,
                                        const Launch<R>& L, R (&h)[9]) {
@@ -85,24 +90,23 @@ __device__ __forceinline__ void gather(const typename Store<S>::T* __restrict__ 
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
         const int ix = i % 3, iy = i / 3;
-        if constexpr (WALLS) {
-            const bool from_lo = (iy == 2) && (y == 0);
-            const bool from_hi = (iy == 0) && (y == g.ny - 1);
-            if (from_lo || from_hi) {
-                const int o = 8 - i;
-                const T* row = src + row_base(g, o, y);
-                R v = load_dev<S, true>((const T*)((const char*)row + xo[1]), o, L.P.rho0);
-                v += wall_term<R>(i, from_lo ? L.ulo : L.uhi, L.P.rho0);
-                h[i] = v;
-                continue;
-            }
-        }
-        const T* row = src + row_base(g, i, ys[iy]);
+        const bool wall = WALLS && ((iy == 2 && y == 0) || (iy == 0 && y == g.ny - 1));
+        const T* row = src + row_base(g, wall ? 8 - i : i, wall ? y : ys[iy]);
         // the rows read at x are read once (non-temporal); the x-shifted ones
         // keep ordinary loads, so that the lines a wave shares with its
         // neighbour stay in L2 (8192^2 FP32: 868 -> 836 us per step)
-        if (ix == 1) h[i] = load_dev<S, true>((const T*)((const char*)row + xo[1]), i, L.P.rho0);
-        else h[i] = load_dev<S>((const T*)((const char*)row + xo[ix]), i, L.P.rho0);
+        if (ix == 1) h[i] = load_dev<S, true>((const T*)((const char*)row + xo[1]), i, L.P.rho0);   // w_i = w_{8-i}
+        else h[i] = load_dev<S>((const T*)((const char*)row + xo[wall ? 1 : ix]), i, L.P.rho0);
+    }
+    if constexpr (WALLS) {
+        if (y == 0) {
+#pragma unroll
+            for (int i = 6; i < 9; ++i) h[i] += wall_term<R>(i, L.ulo, L.P.rho0);
+        }
+        if (y == g.ny - 1) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) h[i] += wall_term<R>(i, L.uhi, L.P.rho0);
+        }
     }
 }
 
@@ -142,7 +146,7 @@ __device__ __forceinline__ void cell_force(const R* __restrict__ force, const Ge
 }
 
 // ---------------------------------------------------------------- step
-template <int S, bool WALLS, bool LES, bool FFIELD, bool VAR, bool SGS = false>
+template <int S, bool WALLS, bool LES, bool FFIELD, bool VAR, bool SGS, bool NT>
 __global__ void __launch_bounds__(256) k2_step(const typename Store<S>::T* __restrict__ src,
                                                typename Store<S>::T* __restrict__ dst,
                                                const typename Store<S>::R* __restrict__ force, const Geom g,
@@ -178,8 +182,11 @@ __global__ void __launch_bounds__(256) k2_step(const typename Store<S>::T* __res
         }
         const uint32_t xt = (uint32_t)x * (uint32_t)sizeof(T);
 #pragma unroll
-        for (int i = 0; i < 9; ++i)
-            __builtin_nontemporal_store(to_store<S>(h[i], i, L.P.rho0), (T*)((char*)(dst + row_base(g, i, y)) + xt));
+        for (int i = 0; i < 9; ++i) {
+            T* const p = (T*)((char*)(dst + row_base(g, i, y)) + xt);
+            if constexpr (NT) __builtin_nontemporal_store(to_store<S>(h[i], i, L.P.rho0), p);
+            else *p = to_store<S>(h[i], i, L.P.rho0);
+        }
     }
 }
 
@@ -357,20 +364,30 @@ static Launch<R> make_launch(const LaunchArgs& a) {
     return L;
 }
 
+// Non-temporal stores of the step (f gets them as a compile-time constant): rows
+// of whole cache lines of buffers beyond the 256 MB Infinity Cache. Smaller ones
+// are found there again by the next step, and rows that share lines would write
+// them in parts (us per step, ordinary / non-temporal: 4096^2 FP32 230 / 211, FP16
+// 155 / 151; 2048^2 FP32 49.8 / 52.4, 2429 x 2067 FP32-shifted between walls 64 /
+// 79, FP16 51.7 / 54.3, 3000 x 500 FP64 39 / 42, 1500^2 with the sub-grid force 47 / 52).
+template <typename T, typename F>
+static void with_stores(const Geom& g, F&& f) {
+    if ((size_t)g.nx * sizeof(T) % 128 == 0 && 9 * (size_t)g.N * sizeof(T) >= ((size_t)256 << 20)) f(std::true_type());
+    else f(std::false_type());
+}
+
 template <int S, bool W, bool LES, bool FF>
 static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
     using T = typename Store<S>::T;
     using R = typename Store<S>::R;
     int bx;
     const dim3 grid = grid_for(a.g, bx, a.g.rowloop != 0);
-    if (a.flags & 3u)
-        k2_step<S, W, LES, FF, true><<<grid, bx, 0, (hipStream_t)a.stream>>>((const T*)src, (T*)dst,
-                                                                            (const R*)a.force_field, a.g,
-                                                                            make_launch<R>(a));
-    else
-        k2_step<S, W, LES, FF, false><<<grid, bx, 0, (hipStream_t)a.stream>>>((const T*)src, (T*)dst,
-                                                                             (const R*)a.force_field, a.g,
-                                                                             make_launch<R>(a));
+    const bool var = (a.flags & 3u) != 0;
+    with_stores<T>(a.g, [&](auto n) {
+        constexpr bool NT = decltype(n)::value;
+        if (var) k2_step<S, W, LES, FF, true, false, NT><<<grid, bx, 0, (hipStream_t)a.stream>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, make_launch<R>(a));
+        else k2_step<S, W, LES, FF, false, false, NT><<<grid, bx, 0, (hipStream_t)a.stream>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, make_launch<R>(a));
+    });
     return hipGetLastError();
 }
 
@@ -385,10 +402,12 @@ static hipError_t step_sgs_t(const LaunchArgs& a, const void* src, void* dst) {
     const Launch<R> L = make_launch<R>(a);
     const R* rp = (const R*)a.stress_prev;
     R* rn = (R*)a.stress_next;
-    if (a.flags & 3u)
-        k2_step<S, false, false, FF, true, true><<<grid, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L, rp, rn);
-    else
-        k2_step<S, false, false, FF, false, true><<<grid, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L, rp, rn);
+    const bool var = (a.flags & 3u) != 0;
+    with_stores<T>(a.g, [&](auto n) {
+        constexpr bool NT = decltype(n)::value;
+        if (var) k2_step<S, false, false, FF, true, true, NT><<<grid, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L, rp, rn);
+        else k2_step<S, false, false, FF, false, true, NT><<<grid, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L, rp, rn);
+    });
     return hipGetLastError();
 }
 
