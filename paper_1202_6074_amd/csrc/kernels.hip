@@ -988,6 +988,55 @@ __global__ void __launch_bounds__(256) k_step_inplace(typename Store<S>::T* buf,
     }
 }
 
+// The same with several rows per workgroup (packed_cell), for short rows. On odd
+// steps plane i of x + e_i holds fbar_{26-i} and takes fbar~_i (towards a wall,
+// plane 26 - i of the cell itself): the lanes of a row write all of it in one
+// instruction, shifted or not.
+template <int S, bool WALLS, bool LES, bool FFIELD, bool VAR, bool ODD>
+__global__ void __launch_bounds__(256) k_step_inplace_packed(typename Store<S>::T* buf,
+                                                             const typename Store<S>::R* __restrict__ force,
+                                                             const Geom g, const Launch<typename Store<S>::R> L) {
+    using R = typename Store<S>::R;
+    using T = typename Store<S>::T;
+    int x, y, z;
+    if (!packed_cell(g, x, y, z)) return;
+    const uint32_t es = (uint32_t)sizeof(T), rl = 27u * (uint32_t)g.nx * es, own = (uint32_t)y * rl + (uint32_t)x * es;
+    T* const plane = buf + (size_t)z * g.ny * 27 * g.nx;   // plane 0 of this z, y = 0
+    T t[27];
+    if constexpr (ODD) {
+        T s[27];
+        gather_packed<1, WALLS, false>(buf, g, x, y, z, s);
+#pragma unroll
+        for (int i = 0; i < 27; ++i) t[i] = s[26 - i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < 27; ++i) t[i] = *at_row(plane + (size_t)i * g.nx, own);
+    }
+    R F[3], h[27], ls[9], ld[9], acc[3];
+    row_force<R, FFIELD, false>(force, g, L, x, y, z, F);
+    stored_line_sums<S, WALLS>(t, g, y, L, h, ls, ld);
+    collide_cell<S, LES, VAR, false>(g, L, x, y, z, h, ls, ld, F, acc, nullptr);
+    if constexpr (!ODD) {
+#pragma unroll
+        for (int i = 0; i < 27; ++i) *at_row(plane + (size_t)(26 - i) * g.nx, own) = to_store<S>(h[i], i, L.P.rho0);
+    } else {
+        const uint32_t xo[3] = {(uint32_t)(x == 0 ? g.nx - 1 : x - 1) * es, (uint32_t)x * es,
+                                (uint32_t)(x == g.nx - 1 ? 0 : x + 1) * es};
+        const uint32_t yo[3] = {(uint32_t)(y == 0 ? g.ny - 1 : y - 1) * rl, (uint32_t)y * rl,
+                                (uint32_t)(y == g.ny - 1 ? 0 : y + 1) * rl};
+        const int zo[3] = {z == 0 ? g.nz - 1 : z - 1, z, z == g.nz - 1 ? 0 : z + 1};
+#pragma unroll
+        for (int i = 0; i < 27; ++i) {
+            const int iy = (i / 3) % 3;
+            const T v = to_store<S>(h[i], i, L.P.rho0);   // w_i = w_{26-i}
+            if (WALLS && ((iy == 0 && y == 0) || (iy == 2 && y == g.ny - 1)))
+                *at_row(plane + (size_t)(26 - i) * g.nx, own) = v;
+            else
+                *at_row(buf + ((size_t)zo[i / 9] * g.ny * 27 + i) * g.nx, yo[iy] + xo[i % 3]) = v;
+        }
+    }
+}
+
 // The same on whole rows through LDS (one workgroup per row, lane = cell). The
 // locations of a row's cells are, on even steps, the row's own block of 27 nx
 // values, on odd ones nine blocks of 3 nx values (the three planes that differ
@@ -1591,14 +1640,22 @@ static dim3 pack_rows(Geom& g, int lanes) {
 // less to fill 45 x 60 x 80 FP32 12.2 / 13.0, 96^3 36.4 / 38.5, 128^3 75.7 / 83.1. But FP32
 // rows of whole cache lines of lattices inside the L2s, where launches and
 // latency count (32^3 4.7 / 4.9).
+// In place (us per step, row / packed): 20 x 200 x 200 FP32 45.6 / 32.2, FP16 46.5 / 21.8,
+// FP64 77.2 / 57.3; 32 x 200 x 200 FP32 51.2 / 44.5; 70 x 200 x 100 FP32 62.5 / 53.2, FP16
+// 47.6 / 31.6; 32^3 FP32 6.2 / 4.7.
 template <int S>
-static bool packed_rows(const Geom& g) {
+static bool packed_fill(const Geom& g) {
     constexpr size_t es = sizeof(typename Store<S>::T);
     if (g.lanegather || g.rowloop || g.nx < 8 || g.nx > 128) return false;
-    if (es == 4 && g.nx % 32 == 0 && !past_l2<S>(g)) return false;
     const int lanes = pack_lanes(g), fill = lanes / g.nx * g.nx;
     const int row = (g.nx + 63) / 64 * 64;
     return (double)fill * row >= (es == 2 ? 1.2 : 1.4) * g.nx * lanes;
+}
+
+template <int S>
+static bool packed_rows(const Geom& g) {
+    if (sizeof(typename Store<S>::T) == 4 && g.nx % 32 == 0 && !past_l2<S>(g)) return false;
+    return packed_fill<S>(g);
 }
 
 // Calls f with the row width XL of the LDS-exchange kernel as a compile-time
@@ -1761,6 +1818,20 @@ static hipError_t step_inplace_t(const LaunchArgs& a, void* buf) {
     const bool odd = a.g.aa == 2, var = (a.flags & 3u) != 0;
     hipStream_t st = (hipStream_t)a.stream;
     const Launch<R> L = make_launch<R>(a);
+    if (packed_fill<S>(a.g)) {
+        Geom gp = a.g;
+        const int lanes = pack_lanes(a.g);
+        const dim3 gq = pack_rows(gp, lanes);
+        auto launch = [&](auto v, auto o) {
+            k_step_inplace_packed<S, W, LES, FF, decltype(v)::value, decltype(o)::value>
+                <<<gq, lanes, 0, st>>>((T*)buf, (const R*)a.force_field, gp, L);
+        };
+        if (odd && var) launch(std::true_type(), std::true_type());
+        else if (odd) launch(std::false_type(), std::true_type());
+        else if (var) launch(std::true_type(), std::false_type());
+        else launch(std::false_type(), std::false_type());
+        return hipGetLastError();
+    }
     if (inplace_rows<S>(a.g)) {
         const dim3 rows(1, a.g.ny, a.g.nz);
         const unsigned lds = odd ? row_lds<T>(a.g) : (27u * (unsigned)a.g.nx * (unsigned)sizeof(T) + 16u + 15u) / 16u * 16u;
@@ -1791,7 +1862,7 @@ template <int S>
 hipError_t step_inplace_s(const LaunchArgs& a, void* buf) {
     if (a.g.aa != 1 && a.g.aa != 2) return hipErrorInvalidValue;
     // by rows, and on even steps, which only add the wall terms, walls need no launch of their own
-    if (inplace_rows<S>(a.g) || a.g.aa == 1)
+    if (packed_fill<S>(a.g) || inplace_rows<S>(a.g) || a.g.aa == 1)
         return a.walls ? step_inplace_w<S, true>(a, buf) : step_inplace_w<S, false>(a, buf);
     return split_wall_rows(a, [&](const LaunchArgs& b, bool w) {
         return w ? step_inplace_w<S, true>(b, buf) : step_inplace_w<S, false>(b, buf);

@@ -208,3 +208,15 @@ def test_adjoint_of_packed_rows(storage, nx, walls):
             lat.adjoint_step(lat.state_buffer(), lam0.repeat(1, 1, 1, rep).to(lat.dtype), lam, gF)
             out.append((lam, gF))
         assert torch.equal(out[0][0].repeat(1, 1, 1, m), out[1][0]) and torch.equal(out[0][1].repeat(1, 1, 1, m), out[1][1])
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f32s", "f16s"])
+@pytest.mark.parametrize("nx", [8, 9, 20, 32, 33, 70, 75, 128])
+@pytest.mark.parametrize("walls", [False, True])
+def test_in_place_several_rows_per_workgroup(storage, nx, walls):
+    torch = _torch()
+    for ny, nz in ((1, 3), (2, 2), (13, 2), (33, 40)):
+        for steps, flags in ((1, {}), (3, {"factorized": True, "reduced_compressibility": True}), (4, {})):
+            a, b = _states((nx, ny, nz), storage, walls, steps, (0, 32), force=steps != 3, les=steps != 4, flags=flags,
+                           in_place=True)
+            assert torch.equal(a, b), (ny, nz, steps)
