@@ -43,6 +43,21 @@ __device__ __forceinline__ size_t row_base(const Geom& g, int i, int y, int z) {
     return (r * 27 + i) * g.nx;
 }
 
+// Plane i of grid row (y, z) for rows of at most 512 cells: 32-bit factors (27 rows
+// are fewer than 2^32 bytes), where row_base multiplies in 64 bits. The scalar
+// unit that forms these addresses serves all four SIMDs of a CU: with 64-bit
+// products and a loop around each copy the step by rows spent 650 scalar
+// instructions a wave beside 720 vector ones, now 405 (us per step, before / after:
+// 301 x 200 x 200 FP16 270 / 262, 200^3 FP16 176 / 172, 300 x 181 x 90 FP32-shifted
+// channel 195 / 192, 500 x 300 x 100 FP32 616 / 609; the LDS-exchange, two-cell and
+// in-place kernels measured the same or up to 2 % slower with it).
+template <typename T>
+__device__ __forceinline__ T* short_row(T* base, const Geom& g, int i, int y, int z) {
+    const uint32_t rb = (uint32_t)g.nx * (uint32_t)sizeof(T), r = (uint32_t)z * (uint32_t)g.ny + (uint32_t)y;
+    using C = typename std::conditional<std::is_const<T>::value, const char, char>::type;
+    return (T*)((C*)base + (uint64_t)r * (27u * rb) + (uint32_t)i * rb);
+}
+
 // Address of an element: a row pointer that is the same for every lane of the
 // workgroup, plus the lane's 32-bit byte offset. Every kernel here takes y and
 // z from the block index, so its row pointers are workgroup-uniform; read
@@ -418,6 +433,24 @@ __device__ __forceinline__ void copy16_to_lds(P src, void* lds) {
 }
 __device__ __forceinline__ void wait_lds_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// LDS element at a byte offset: where offsets are formed in bytes, one addition
+// of a scalar makes an address, in elements the shift is a second instruction
+// (54 of them in the step of 187 x 151 x 133 FP16, bound by instruction issue).
+template <typename T>
+__device__ __forceinline__ T& lds_at(T* sm, uint32_t bytes) { return *(T*)((unsigned char*)sm + bytes); }
+
+// The copies of n vectors from `from` into LDS at `to` by the workgroup's lanes, at
+// most PASSES vectors a lane.
+template <int PASSES>
+__device__ __forceinline__ void copy_vectors(const u32x4* from, unsigned char* to, uint32_t n, uint32_t tid, uint32_t wave0,
+                                             uint32_t bd) {
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        const uint32_t k = (uint32_t)p * bd;
+        if (tid + k < n) copy16_to_lds(at_row(from, (tid + k) * 16u), to + 16u * (k + wave0));
+    }
+}
+
 // Elements of LDS that hold a group of three adjacent rows of nx values with up
 // to one 16-byte vector of misalignment, in whole vectors.
 template <typename T>
@@ -456,7 +489,6 @@ template <int S, bool WALLS, typename Other>
 __device__ __forceinline__ void gather_rows(const typename Store<S>::T* __restrict__ src, const Geom& g, uint32_t x, int y,
                                             int z, typename Store<S>::T* sm, typename Store<S>::T (&t)[27], Other&& other) {
     using T = typename Store<S>::T;
-    constexpr uint32_t V = 16 / sizeof(T);
     const uint32_t tid = threadIdx.x, bd = blockDim.x, nx = (uint32_t)g.nx;
     const uint32_t wave0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid & ~63u));
     const int ys[3] = {y == g.ny - 1 ? 0 : y + 1, y, y == 0 ? g.ny - 1 : y - 1};
@@ -465,26 +497,27 @@ __device__ __forceinline__ void gather_rows(const typename Store<S>::T* __restri
     // the own row, its three populations in reverse order and not shifted
     auto bounce = [&](int q) { return WALLS && ((q % 3 == 2 && y == 0) || (q % 3 == 0 && y == g.ny - 1)); };
     const uint32_t gs = group_stride<T>(nx);
-    uint32_t off[9];   // misalignment of each group, in elements
+    constexpr uint32_t es = (uint32_t)sizeof(T);
+    uint32_t off[9];   // misalignment of each group, in bytes
 #pragma unroll
     for (int q = 0; q < 9; ++q) {
         const bool w = bounce(q);
-        const T* A = src + row_base(g, w ? 24 - 3 * q : 3 * q, w ? y : ys[q % 3], w ? z : zs[q / 3]);
-        off[q] = (uint32_t)((uintptr_t)A & 15u) / (uint32_t)sizeof(T);
+        const T* A = short_row(src, g, w ? 24 - 3 * q : 3 * q, w ? y : ys[q % 3], w ? z : zs[q / 3]);
+        off[q] = (uint32_t)((uintptr_t)A & 15u);
         const u32x4* base = (const u32x4*)((uintptr_t)A & ~(uintptr_t)15);
-        const uint32_t n = (off[q] + 3u * nx + V - 1u) / V;
-        for (uint32_t k = 0; k < n; k += bd)   // one pass, two for FP64
-            if (tid + k < n)
-                copy16_to_lds(at_row(base, (tid + k) * 16u), (unsigned char*)sm + 16u * (q * (gs / V) + k + wave0));
+        const uint32_t n = (off[q] + 3u * nx * es + 15u) / 16u;
+        // 3 nx values and a vector: within bd vectors of 4- or 2-byte values, 2 bd of FP64
+        copy_vectors<es == 8 ? 2 : 1>(base, (unsigned char*)sm + es * q * gs, n, tid, wave0, bd);
     }
     other();
     wait_lds_copies();
     __syncthreads();
-    const uint32_t xs[3] = {x + 1u >= nx ? 0u : x + 1u, nx + x, 2u * nx + (x == 0u ? nx - 1u : x - 1u)};   // x - e_x
+    // x - e_x, in bytes
+    const uint32_t xs[3] = {es * (x + 1u >= nx ? 0u : x + 1u), es * (nx + x), es * (2u * nx + (x == 0u ? nx - 1u : x - 1u))};
 #pragma unroll
     for (int i = 0; i < 27; ++i) {
         const int ix = i % 3, q = i / 3;
-        t[i] = sm[q * gs + off[q] + (bounce(q) ? x + (uint32_t)(2 - ix) * nx : xs[ix])];
+        t[i] = lds_at(sm, (es * q * gs + off[q]) + (bounce(q) ? es * (x + (uint32_t)(2 - ix) * nx) : xs[ix]));
     }
 }
 
@@ -736,14 +769,14 @@ __global__ void __launch_bounds__(512) k_step_row(const typename Store<S>::T* __
         // (unguarded, the collision of the idle lanes cost 15 vector registers)
         if (act) collide_cell<S, LES, VAR, SGS>(g, L, (int)x, y, z, h, ls, ld, F, acc, rs_next);
         __syncthreads();   // every lane has read its values: the LDS takes the results
-        T* const D = dst + row_base(g, 0, y, z);
+        T* const D = short_row(dst, g, 0, y, z);
         const uint32_t o = (uint32_t)((uintptr_t)D & 15u) / (uint32_t)sizeof(T);
         if (act) {
-            uint32_t at = o + x;   // stepped row by row: 27 addresses held at once spilled
+            uint32_t at = (o + x) * (uint32_t)sizeof(T);   // stepped row by row: 27 addresses held at once spilled
 #pragma unroll
             for (int i = 0; i < 27; ++i) {
-                sm[at] = to_store<S>(h[i], i, L.P.rho0);
-                at += nx;
+                lds_at(sm, at) = to_store<S>(h[i], i, L.P.rho0);
+                at += nx * (uint32_t)sizeof(T);
                 asm volatile("" : "+v"(at));
             }
         }
@@ -783,7 +816,7 @@ __global__ void __launch_bounds__(256) k_step_packed(const typename Store<S>::T*
     extern __shared__ __align__(16) unsigned char lds_bytes[];
     T* const sm = (T*)lds_bytes;
     const int y0 = (int)(blockIdx.x * (uint32_t)g.pack);
-    T* const D = dst + row_base(g, 0, y0, z);   // the workgroup's block
+    T* const D = short_row(dst, g, 0, y0, z);   // the workgroup's block
     const uint32_t o = (uint32_t)((uintptr_t)D & 15u) / (uint32_t)sizeof(T);
     if (act) {
         R h[27], ls[9], ld[9];
@@ -797,11 +830,11 @@ __global__ void __launch_bounds__(256) k_step_packed(const typename Store<S>::T*
             for (int i = 0; i < 27; ++i)
                 __builtin_nontemporal_store(to_store<S>(h[i], i, L.P.rho0), at_row(D + (size_t)i * nx, at));
         } else {
-            at += o;
+            at = (at + o) * (uint32_t)sizeof(T);
 #pragma unroll
             for (int i = 0; i < 27; ++i) {
-                sm[at] = to_store<S>(h[i], i, L.P.rho0);
-                at += nx;
+                lds_at(sm, at) = to_store<S>(h[i], i, L.P.rho0);
+                at += nx * (uint32_t)sizeof(T);
                 asm volatile("" : "+v"(at));
             }
         }
