@@ -92,13 +92,17 @@ bool rate_ok(double w) { return std::isfinite(w) && w > 0.0 && w < 2.0; }
 // rows that start on cache lines (512 x 512 x 128 FP32 1,277 / 1,295 / 1,275,
 // 384 x 384 x 200 1,202 / 1,142 / 1,154).
 // In-place rows of one workgroup go in the plain order (us per step, plain / runs
-// of 32 or XCD-aware: 300 x 200 x 100 FP32 229 / 251, 512 x 256 x 128 607 / 640,
-// 200 x 100 x 100 FP64 150 / 159, 256 x 256 x 128 FP32 303 / 302).
+// of 32: 300 x 200 x 100 FP32 231 / 234, 512 x 256 x 128 608 / 612, 192^3 253 /
+// 253, 200 x 100 x 100 FP64 150 / 159, 256 x 256 x 128 FP32 303 / 302), but for
+// 4-byte rows that start on cache lines and are split into two workgroups which
+// they do not fill (384 x 384 x 192 1,152 / 1,087, 448 x 200 x 100 336 / 326, 320 x
+// 200 x 200 478 / 476).
 constexpr int kXcdRun = 32;
 int default_xcd_order(int lattice, int storage, int nx, bool rowloop, bool walls, bool in_place, bool lane_gather) {
-    if (lattice == CMLBM_D3Q27 && in_place && !rowloop && !lane_gather && nx <= (storage == CMLBM_F64 ? 256 : 512)) return 0;
-    if (storage == CMLBM_F64) return 1;
     const bool four_byte = storage == CMLBM_F32 || storage == CMLBM_F32_SHIFTED;
+    if (lattice == CMLBM_D3Q27 && in_place && !rowloop && !lane_gather && nx <= (storage == CMLBM_F64 ? 256 : 512))
+        return four_byte && nx > 256 && nx % 32 == 0 && nx % 256 != 0 ? kXcdRun : 0;
+    if (storage == CMLBM_F64) return 1;
     if (!rowloop && nx > 256) {
         if (lattice != CMLBM_D3Q27 || lane_gather || nx > 512) return 1;
         if (!four_byte) return 0;

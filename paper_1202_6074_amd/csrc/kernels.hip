@@ -1712,15 +1712,18 @@ static bool pair_rows(const Geom& g, const void* src, const void* dst, const voi
 }
 
 // Occupancy caps by LDS reservation: with 60,000 bytes of the CU's 160 KB of
-// LDS reserved per workgroup, at most two workgroups share a CU; with 40,960
-// bytes, three for a kernel that holds 9 KB of its own. The reserved LDS itself
-// is not used. Measured at 256^3 and 512^3, fewer resident rows per CU made the
-// DRAM traffic of these kernels more efficient: the in-place pair of kernels
-// with 4-byte populations on rows of at most 512 cells 3-6 % faster at two
-// workgroups per CU (FP16: slower; rows of 1024 cells: not faster), the
-// two-cells-per-lane FP16 kernel about 1 % faster at three. The LDS-exchange
+// LDS reserved per workgroup, at most two workgroups share a CU, with 50,000
+// three; with 40,960 bytes, three for a kernel that holds 9 KB of its own. The
+// reserved LDS itself is not used. Fewer resident rows per CU make the DRAM
+// traffic of these kernels more efficient. The per-lane in-place pair with 4-byte
+// populations on rows of at most 512 cells: two workgroups where they are full
+// 256-lane ones, three where rows leave lanes idle or take 192 (us per step, two /
+// three: 256 x 256 x 128 305 / 310, 512 x 256 x 128 608 / 611; 160^3 154 / 147,
+// 192^3 263 / 253, 320 x 200 x 200 529 / 476, 384^3 2,279 / 2,171, 448 x 200 x 100
+// 337 / 326; FP16: slower with any; rows of 1024 cells: not faster). The
+// two-cells-per-lane FP16 kernel is about 1 % faster at three; the LDS-exchange
 // step kernels are fastest at their full occupancy (six to seven workgroups).
-constexpr unsigned kLdsTwoPerCu = 60000, kLdsPairCap = 40960;
+constexpr unsigned kLdsTwoPerCu = 60000, kLdsThreePerCu = 50000, kLdsPairCap = 40960;
 
 // A step over many z-planes runs as launches of at most kZChunk planes each:
 // the end of each launch brings the eight XCDs back to the same planes, where
@@ -1878,7 +1881,7 @@ static hipError_t step_inplace_t(const LaunchArgs& a, void* buf) {
         else launch(std::false_type(), std::false_type());
         return hipGetLastError();
     }
-    const unsigned cap = sizeof(T) == 4 && a.g.nx <= 512 ? kLdsTwoPerCu : 0u;
+    const unsigned cap = sizeof(T) != 4 || a.g.nx > 512 ? 0u : (a.g.nx % 256 ? kLdsThreePerCu : kLdsTwoPerCu);
     if (odd && var) k_step_inplace<S, W, LES, FF, true, true><<<grid, bx, cap, st>>>((T*)buf, (const R*)a.force_field, a.g, L);
     else if (odd) k_step_inplace<S, W, LES, FF, false, true><<<grid, bx, cap, st>>>((T*)buf, (const R*)a.force_field, a.g, L);
     else if (var) k_step_inplace<S, W, LES, FF, true, false><<<grid, bx, cap, st>>>((T*)buf, (const R*)a.force_field, a.g, L);

@@ -154,7 +154,7 @@ def test_start_by_rows(storage, nx, ny, nz, walls):
 
 
 @pytest.mark.parametrize("storage", ["f64", "f32", "f32s", "f16s"])
-@pytest.mark.parametrize("nx", [15, 16, 17, 64, 129, 187, 256, 257, 300, 512, 513])
+@pytest.mark.parametrize("nx", [15, 16, 17, 64, 129, 187, 192, 256, 257, 300, 320, 384, 512, 513])
 @pytest.mark.parametrize("walls", [False, True])
 def test_in_place_rows(storage, nx, walls):
     """In-place steps by rows and by lanes (tuning bit 5), after even and odd
