@@ -149,7 +149,8 @@ typedef struct {
                                two-cell kernel); bit 7: every step and
                                adjoint step in one launch (by default the
                                FP32 and FP32-shifted step with one workgroup
-                               per row, and the adjoint step, run over
+                               per row, the two-cell FP16 step of more than
+                               2^25 cells, and the adjoint step, run over
                                chunks of 128 z-planes); 0 = defaults          */
     double wall_u_lo[3];    /* velocity of the wall at y = -1/2                  */
     double wall_u_hi[3];    /* velocity of the wall at y = ny - 1/2              */

@@ -88,7 +88,7 @@ bool rate_ok(double w) { return std::isfinite(w) && w > 0.0 && w < 2.0; }
 // well: FP16 in the plain order, which needs no division by the grid's sizes
 // (the kernels are bound by instruction issue; us per step, plain / runs of 32 /
 // XCD-aware: 301 x 200 x 200 310 / - / 345; the two-cell kernel at 512 x 512 x
-// 128 663 / 679 / -), FP32 in runs of 32 (300 x 200 x 200 - / 467 / 481) but for
+// 128 656 / 666 / 671, in chunks of planes at 512^3 2,692 / - / 2,726), FP32 in runs of 32 (300 x 200 x 200 - / 467 / 481) but for
 // rows that start on cache lines (512 x 512 x 128 FP32 1,277 / 1,295 / 1,275,
 // 384 x 384 x 200 1,202 / 1,142 / 1,154).
 // In-place rows of one workgroup go in the plain order (us per step, plain / runs

@@ -1733,13 +1733,14 @@ constexpr unsigned kLdsTwoPerCu = 60000, kLdsThreePerCu = 50000, kLdsPairCap = 4
 // 596.0 / 586.5 on two machines, 256 x 256 x 1024 2,679 / 2,483; chunks of 64
 // and 32 planes gained less or lost. The adjoint kernel gains as well (256^3
 // FP32: 1,041 / 1,020 us; chunks of 64 the same there but 4 % slower at
-// 128^3, chunks of 32 slower). Not faster, so kept in one launch: the
-// FP16 two-cell kernel (2,665 / 2,701 us at 512^3), FP32-shifted rows of 512
-// cells (5,192 / 5,208), FP64 rows of 512 cells (9,953 / 9,751 on one machine but
-// 9,578 / 10,113 on another), the in-place kernels (256^3: 653 / 656 us), the
-// wall rows and the D2Q9 step (8192^2: 869 us in one launch, 875-927 us in
-// chunks of 4096-512 rows). The FP32 sub-grid-force step with one workgroup
-// per row gains 1.1 % (769.4 / 761.2 us at 256^3).
+// 128^3, chunks of 32 slower), and the two-cells-per-lane FP16 kernel in the plain
+// order on large grids (there). Not faster, so kept in one launch: the other
+// FP16 steps (187 x 151 x 400 226 / 240 us, 128 x 128 x 512 149 / 163, 256^3 298 /
+// 299, 401^3 1,476 / 1,476), FP64 rows of 512 cells (9,953 / 9,751 on one machine
+// but 9,578 / 10,113 on another), the in-place kernels (256^3: 653 / 656 us) and
+// the D2Q9 step (8192^2: 869 us in one launch, 875-927 us in chunks of 4096-512
+// rows). The FP32 sub-grid-force step with one workgroup per row gains 1.1 %
+// (769.4 / 761.2 us at 256^3).
 constexpr int kZChunk = 128;
 template <typename Launch1>
 static hipError_t launch_z_chunks(const Geom& g, const dim3& grid, bool chunked, Launch1&& launch) {
@@ -1784,9 +1785,14 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
             // 335 and 343, in 256 lanes for all widths and the cap 381)
             const int bp = (a.g.nx / 2 + 63) / 64 * 64;
             const unsigned pcap = a.g.nx > 448 ? kLdsPairCap : 0u;
-            if (var) k_step_f16pair<LES, FF, true><<<gp, bp, pcap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
-            else k_step_f16pair<LES, FF, false><<<gp, bp, pcap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
-            return hipGetLastError();
+            // past 2^25 cells in chunks of planes, in the plain order (us per step, one
+            // launch plain / one launch XCD-aware / chunks: 512^3 2,903 / 2,712 / 2,692,
+            // 512 x 512 x 256 1,397 / 1,358 / 1,343, 384^3 1,175 / 1,175 / 1,120; 320 x
+            // 200 x 512 700 / 736 / 702)
+            return launch_z_chunks(a.g, gp, (int64_t)a.g.N > (int64_t)1 << 25, [&](const dim3& gq, const Geom& gg) {
+                if (var) k_step_f16pair<LES, FF, true><<<gq, bp, pcap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L);
+                else k_step_f16pair<LES, FF, false><<<gq, bp, pcap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L);
+            });
         }
     }
     if (packed_rows<S>(a.g)) {
@@ -1831,7 +1837,7 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
 // In-place rows through LDS: 16 to 512 cells (FP64: 256, by its LDS), but rows that
 // start on cache lines keep the per-lane kernels in FP64 and on even steps, where
 // those access whole lines (us per step, pair by lanes / even by lanes and odd by
-// rows / both by rows: 256^3 FP32 646 / 602 / 621, 384 x 384 x 192 1,204 / 1,125 /
+// rows / both by rows: 256^3 FP32 646 / 602 / 621, 384 x 384 x 192 1,204 / 1,087 /
 // 1,140, 512 x 512 x 128 FP16 735 / 687 / 707, 256 x 100 x 100 FP64 190 / 194 /
 // 196; 300 x 200 x 100 FP32 332 / 283 / 229, 187 x 151 x 133 FP16 94 / 91 / 85,
 // 201 x 100 x 100 FP64 174 / 184 / 166); and with 4-byte values on rows of up to

@@ -220,3 +220,12 @@ def test_in_place_several_rows_per_workgroup(storage, nx, walls):
             a, b = _states((nx, ny, nz), storage, walls, steps, (0, 32), force=steps != 3, les=steps != 4, flags=flags,
                            in_place=True)
             assert torch.equal(a, b), (ny, nz, steps)
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(512, 480, 140), (500, 520, 130)])
+def test_two_cell_rows_in_chunks_of_planes(nx, ny, nz):
+    """The two-cell FP16 kernel past 2^25 cells, in chunks of 128 planes and in
+    one launch (tuning bit 7)."""
+    torch = _torch()
+    a, b = _states((nx, ny, nz), "f16s", False, 2, (0, 128))
+    assert torch.equal(a, b)
