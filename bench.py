@@ -262,11 +262,9 @@ def channel_section(steps, warmup):
                        "U = 0.02; F_x = 1e-6; Cs = 0.12, omega0 = 1.95)",
            "mlups": round(N * steps / dt / 1e6, 1), "bytes_per_cell": 216,
            "gbs": round(216 * N / (dt / steps) / 1e9, 1),
-           "kernels": {"interior_rows": "k_step<f32,interior_rows,les,uniform_force>@256^3_channel",
-                       "wall_rows": "k_step<f32,wall_rows,les,uniform_force>@256^3_channel"},
-           "traffic": {"interior_rows": measured_traffic("k_step<f32,interior_rows,les,uniform_force>@256^3_channel"),
-                       "wall_rows": measured_traffic("k_step<f32,wall_rows,les,uniform_force>@256^3_channel")},
-           "note": "uniform force: 27 x 4 x 2 bytes per cell; wall rows run a kernel of their own"}
+           "kernel": "k_step<f32,walls,les,uniform_force>@256^3_channel",
+           "traffic": measured_traffic("k_step<f32,walls,les,uniform_force>@256^3_channel"),
+           "note": "uniform force: 27 x 4 x 2 bytes per cell; wall rows in the same launch"}
     lat.close()
     del lat
     torch.cuda.empty_cache()
