@@ -365,14 +365,20 @@ static Launch<R> make_launch(const LaunchArgs& a) {
 }
 
 // Non-temporal stores of the step (f gets them as a compile-time constant): rows
-// of whole cache lines of buffers beyond the 256 MB Infinity Cache. Smaller ones
-// are found there again by the next step, and rows that share lines would write
-// them in parts (us per step, ordinary / non-temporal: 4096^2 FP32 230 / 211, FP16
-// 155 / 151; 2048^2 FP32 49.8 / 52.4, 2429 x 2067 FP32-shifted between walls 64 /
-// 79, FP16 51.7 / 54.3, 3000 x 500 FP64 39 / 42, 1500^2 with the sub-grid force 47 / 52).
+// of whole cache lines of buffers two of which are well beyond the 256 MB Infinity
+// Cache. Smaller ones are found there again by the next step, and rows that share
+// lines would write them in parts, which in FP64 costs less than what ordinary
+// stores evict up to 384 MiB (us per step, ordinary / non-temporal: 4096^2 FP32 230 /
+// 211, FP16 155 / 151; 2048 x 1400 FP64 82 / 69; 2048^2 FP32 49.8 / 52.4; sharing
+// lines 4001^2 FP32 249 / 292, FP16 160 / 171, 2429 x 2067 FP32-shifted between walls
+// 64 / 79, FP16 51.7 / 54.3; FP64 3000 x 500 38 / 42, 1500^2 60 / 64, 2501 x 1001 78 /
+// 73, 2000 x 1501 89 / 75, 3179 x 951 95 / 91, 1801^2 103 / 97, 4001 x 2001 243 / 257;
+// 1500^2 with the sub-grid force 47 / 52).
 template <typename T, typename F>
 static void with_stores(const Geom& g, F&& f) {
-    if ((size_t)g.nx * sizeof(T) % 128 == 0 && 9 * (size_t)g.N * sizeof(T) >= ((size_t)256 << 20)) f(std::true_type());
+    const size_t bytes = 9 * (size_t)g.N * sizeof(T);
+    const bool lines = (size_t)g.nx * sizeof(T) % 128 == 0 || (sizeof(T) == 8 && bytes < ((size_t)384 << 20));
+    if (lines && bytes >= ((size_t)168 << 20)) f(std::true_type());
     else f(std::false_type());
 }
 
