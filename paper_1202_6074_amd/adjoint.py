@@ -18,9 +18,27 @@ HIP kernels, a segment's steps in one call each (``cmlbm_steps_between``, ``cmlb
 """
 from __future__ import annotations
 
+from contextlib import contextmanager
+
 import torch
 
 from .lattice import Lattice
+
+
+@contextmanager
+def _on_stream_of(lat: Lattice, *inputs: torch.Tensor):
+    """torch's work inside runs on the lattice's stream, where its kernels run:
+    after what the caller queued so far, and before what the caller queues next.
+    inputs: the caller's tensors that are read inside."""
+    caller = torch.cuda.current_stream(lat.device)
+    if caller == lat.stream:
+        yield caller
+        return
+    lat.stream.wait_stream(caller)
+    lat._after_use(*[t for t in inputs if t.device == lat.device])
+    with torch.cuda.stream(lat.stream):
+        yield caller
+    caller.wait_stream(lat.stream)
 
 
 def _keep_all(nsteps: int, K: int) -> bool:
@@ -102,20 +120,24 @@ class EnergyAdjoint(torch.autograd.Function):
     copies of F, of the checkpoints and of the final state, so several applies
     on one lattice, and steps or force changes between forward and backward,
     leave each gradient that of its own forward pass. After either pass the
-    lattice's force field is the F of that pass.
+    lattice's force field is the F of that pass. A lattice on a stream of its own
+    works there; the caller's stream waits for it.
     """
 
     @staticmethod
     def forward(ctx, F, lat, f0_state, nsteps, K):
-        Fs = F.detach().to(device=lat.device, dtype=lat.dtype).clone()
-        E, ckpts, final = _forward(lat, Fs, f0_state, int(nsteps), int(K))
+        with _on_stream_of(lat, F, f0_state):
+            Fs = F.detach().to(device=lat.device, dtype=lat.dtype).clone()
+            E, ckpts, final = _forward(lat, Fs, f0_state, int(nsteps), int(K))
         ctx.lat, ctx.F, ctx.ckpts, ctx.final = lat, Fs, ckpts, final
         ctx.nsteps, ctx.K = int(nsteps), int(K)
         return torch.tensor(E, dtype=torch.float64, device=F.device)
 
     @staticmethod
     def backward(ctx, gE):
-        gF = _backward(ctx.lat, ctx.F, ctx.ckpts, ctx.final, ctx.nsteps, ctx.K)
+        with _on_stream_of(ctx.lat) as caller:
+            gF = _backward(ctx.lat, ctx.F, ctx.ckpts, ctx.final, ctx.nsteps, ctx.K)
+            gF.record_stream(caller)   # used there from now on
         ctx.ckpts = ctx.final = None
         return (gE.to(gF.dtype) * gF), None, None, None, None
 
