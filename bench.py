@@ -28,8 +28,8 @@ sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBS = 8000.0
 KERNEL_SOURCES = ["paper_1202_6074_amd/csrc/cm_math.hpp", "paper_1202_6074_amd/csrc/kernels.hip",
-                  "paper_1202_6074_amd/csrc/store.hpp", "paper_1202_6074_amd/csrc/cm_math2d.hpp",
-                  "paper_1202_6074_amd/csrc/kernels2d.hip"]
+                  "paper_1202_6074_amd/csrc/store.hpp", "paper_1202_6074_amd/csrc/rules.hpp",
+                  "paper_1202_6074_amd/csrc/cm_math2d.hpp", "paper_1202_6074_amd/csrc/kernels2d.hip"]
 EXTRAS = ("variants", "adjoint", "d2q9", "inplace", "channel", "precision", "small")
 
 

@@ -137,7 +137,8 @@ typedef struct {
                                kernel (looping over x); bits 3-4 workgroup
                                order of the step kernel: 0 library default,
                                by storage and row length, 1 plain, 2 XCD-aware
-                               (each XCD takes a contiguous range of rows), 3
+                               (each XCD takes a contiguous range of rows;
+                               as 3 where the workgroups are no multiple of 8), 3
                                runs of 32 consecutive workgroups per XCD in
                                turn (the workgroups after the last full round
                                in the plain order); steps with several rows

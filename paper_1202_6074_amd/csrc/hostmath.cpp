@@ -10,8 +10,10 @@
 // The D2Q9 entries take populations in the paper's velocity order and
 // rates2 = {rho0, omega_3, omega_4 = omega_5, omega_6, omega_7, omega_8,
 //           cs_smag, flags}.
+// cmhost_rule_*: the launch rules of rules.hpp.
 #include "cm_math.hpp"
 #include "cm_math2d.hpp"
+#include "rules.hpp"
 
 namespace {
 
@@ -215,4 +217,7 @@ void cmhost_equilibrium_f64(const double* rho, const double* u, const double* F,
                             int rc) {
     equilibrium_n<double>(rho, u, F, rho0, n, out, rc);
 }
+
+uint32_t cmhost_rule_ordered_block(uint32_t lin, uint32_t total, int order) { return cm::ordered_block(lin, total, order); }
+
 }

@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "rules.hpp"
+
 namespace cm {
 
 // Storage mode S: element type T in memory, compute type R, and whether the
@@ -16,32 +18,17 @@ template <> struct Store<1> { using T = float;    using R = float;  static const
 template <> struct Store<2> { using T = float;    using R = float;  static constexpr bool shifted = true; };
 template <> struct Store<3> { using T = _Float16; using R = float;  static constexpr bool shifted = true; };
 
-// Coordinates (x block, y, z) of this workgroup in a grid of (gx, ny, nz)
-// blocks. Consecutive workgroups are dispatched round-robin to the eight
-// XCDs, each with its own L2. xcd = 0: that order (block k on XCD k % 8);
-// xcd = 1: XCD k takes the k-th contiguous eighth of the blocks (in x, y, z
-// order), so that rows that share data (x-halo cache lines, neighbouring
-// stress rows) are read through one L2; xcd = R >= 2: runs of R consecutive
-// blocks go to the XCDs in turn (8 R blocks per round; the blocks after the last
-// full round in the plain order). Any bijection is correct; this one only
-// changes which L2 serves a block and when.
+// Coordinates (x block, y, z) of this workgroup in a grid of (gx, ny, nz) blocks,
+// in the order `xcd` (ordered_block).
 __device__ __forceinline__ void block_coords(int xcd, int& bx, int& y, int& z) {
-    if (xcd == 0) {
+    if (xcd == 0) {   // without the divisions
         bx = (int)blockIdx.x;
         y = (int)blockIdx.y;
         z = (int)blockIdx.z;
         return;
     }
     const uint32_t gx = gridDim.x, gy = gridDim.y, gz = gridDim.z;
-    uint32_t lin = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-    const uint32_t total = gx * gy * gz;
-    if (xcd == 1) {
-        const uint32_t k = lin & 7u, rest = total & 7u;   // the first `rest` eighths are one longer
-        lin = k * (total >> 3) + (k < rest ? k : rest) + (lin >> 3);
-    } else {
-        const uint32_t run = (uint32_t)xcd, round = lin / (8u * run), k = lin % (8u * run);
-        if ((round + 1u) * 8u * run <= total) lin = round * 8u * run + (k & 7u) * run + (k >> 3);
-    }
+    const uint32_t lin = ordered_block(blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z), gx * gy * gz, xcd);
     bx = (int)(lin % gx);
     const uint32_t r = lin / gx;
     y = (int)(r % gy);

@@ -1,0 +1,38 @@
+"""The rules that choose a launch's kernel, width and order (csrc/rules.hpp, built
+for the host): which side of a measured line a size falls on. Results do not
+depend on them; the GPU tests compare the routes bit for bit."""
+import ctypes
+import os
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HOSTLIB = os.path.join(ROOT, "paper_1202_6074_amd", "libcmlbm_hostmath.so")
+
+
+@pytest.fixture(scope="module")
+def rules():
+    if not os.path.exists(HOSTLIB):
+        from paper_1202_6074_amd.build import build_hostmath
+        build_hostmath()
+    return ctypes.CDLL(HOSTLIB)
+
+
+@pytest.mark.parametrize("order", [0, 1, 2, 32, 256])
+@pytest.mark.parametrize("total", [1, 7, 8, 9, 255, 256, 257, 1000, 1001, 4096, 10002])
+def test_workgroup_orders(rules, order, total):
+    """Every order visits every place once. Contiguous eighths only where the count
+    has them; else whole runs of 32 go to one XCD (workgroups k, k + 8, ...)."""
+    at = [rules.cmhost_rule_ordered_block(k, total, order) for k in range(total)]
+    assert sorted(at) == list(range(total))
+    run = 32 if order == 1 and total % 8 else order
+    if order == 0:
+        assert at == list(range(total))
+    elif order == 1 and total % 8 == 0:
+        for xcd in range(8):
+            assert at[xcd::8] == list(range(xcd * total // 8, (xcd + 1) * total // 8))
+    else:
+        full = total // (8 * run) * 8 * run
+        for xcd in range(8):
+            assert all(p // run % 8 == xcd for p in at[xcd:full:8])
+        assert at[full:] == list(range(full, total))
