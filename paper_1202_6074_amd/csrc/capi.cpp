@@ -11,6 +11,7 @@
 
 #include "../../include/cmlbm.h"
 #include "kernels.hpp"
+#include "rules.hpp"
 
 struct cmlbm_lattice {
     cm::LaunchArgs a;
@@ -68,48 +69,6 @@ uint64_t lane_span(int32_t nx, int storage) {
 int lattice_q(int lattice) { return lattice == CMLBM_D2Q9 ? 9 : 27; }
 
 bool rate_ok(double w) { return std::isfinite(w) && w > 0.0 && w < 2.0; }
-
-// Workgroup order chosen when the caller gives no hint. When a grid row spans
-// several workgroups (nx > 256 without the row loop), the plain order sends
-// neighbouring workgroups of one row to different XCDs, whose L2s then fetch
-// the cache lines shared at the block boundary twice (and, in the odd
-// in-place step, both write parts of the same lines). Measured on MI355X
-// (MLUPS, plain / XCD-aware): FP32 512^3 26,002 / 27,664; FP32 1024^3 in place
-// 21,423 / 27,103; FP64 512^3 11,539 / 13,311. With one 256-lane workgroup per
-// row (periodic D3Q27, FP32 and FP32-shifted rows of 129-256 cells) runs of
-// 32 rows per XCD in turn (at 256^3 the eight runs of a round cover one
-// z-plane) beat both; measured on four machines at 256^3 (us per step, plain /
-// XCD-aware / runs): two-buffer step 602 / 627 / 594, 614 / - / 604,
-// 603 / - / 594, 599 / 624 / 591; in place 661 / 673 / 645, 661 / - / 645,
-// 660 / - / 644; FP32 shifted 605 / - / 592. Not faster, so kept plain: walls
-// (plain / runs 593 / 596 us), rows of 128 cells (77.4 / 78.0 us at 128^3),
-// FP16 storage (plain / XCD-aware at 256^3: 329 / 330 us, in place 362 / 373).
-// Two-buffer D3Q27 steps on rows of 257-512 cells run one workgroup per row as
-// well: FP16 in the plain order, which needs no division by the grid's sizes
-// (the kernels are bound by instruction issue; us per step, plain / runs of 32 /
-// XCD-aware: 301 x 200 x 200 310 / - / 345; the two-cell kernel at 512 x 512 x
-// 128 656 / 666 / 671, in chunks of planes at 512^3 2,692 / - / 2,726), FP32 in runs of 32 (300 x 200 x 200 - / 467 / 481) but for
-// rows that start on cache lines (512 x 512 x 128 FP32 1,277 / 1,295 / 1,275,
-// 384 x 384 x 200 1,202 / 1,142 / 1,154).
-// In-place rows of one workgroup go in the plain order (us per step, plain / runs
-// of 32: 300 x 200 x 100 FP32 231 / 234, 512 x 256 x 128 608 / 612, 192^3 253 /
-// 253, 200 x 100 x 100 FP64 150 / 159, 256 x 256 x 128 FP32 303 / 302), but for
-// 4-byte rows that start on cache lines and are split into two workgroups which
-// they do not fill (384 x 384 x 192 1,152 / 1,087, 448 x 200 x 100 336 / 326, 320 x
-// 200 x 200 478 / 476).
-constexpr int kXcdRun = 32;
-int default_xcd_order(int lattice, int storage, int nx, bool rowloop, bool walls, bool in_place, bool lane_gather) {
-    const bool four_byte = storage == CMLBM_F32 || storage == CMLBM_F32_SHIFTED;
-    if (lattice == CMLBM_D3Q27 && in_place && !rowloop && !lane_gather && nx <= (storage == CMLBM_F64 ? 256 : 512))
-        return four_byte && nx > 256 && nx % 32 == 0 && nx % 256 != 0 ? kXcdRun : 0;
-    if (storage == CMLBM_F64) return 1;
-    if (!rowloop && nx > 256) {
-        if (lattice != CMLBM_D3Q27 || lane_gather || nx > 512) return 1;
-        if (!four_byte) return 0;
-        return nx % 32 ? kXcdRun : 1;
-    }
-    return lattice == CMLBM_D3Q27 && four_byte && !rowloop && !walls && nx > 128 ? kXcdRun : 0;
-}
 
 // Host memory that devices write reduced values to: 64 slots of 8 doubles in one
 // page, allocated with the first handle and held until the process ends (an
@@ -245,8 +204,10 @@ cmlbm_status cmlbm_create(const cmlbm_desc* d, void* buf_a, void* buf_b, size_t 
         a.g.pairs_off = (d->tuning & 64u) ? 1 : 0;
         a.g.one_launch = (d->tuning & 128u) ? 1 : 0;
         const unsigned order = (d->tuning >> 3) & 3u;
-        a.g.xcd = order == 1u ? 0 : (order == 2u ? 1 : (order == 3u ? kXcdRun : default_xcd_order(d->lattice, d->storage, d->nx, a.g.rowloop != 0, (d->walls & 1u) != 0,
-                                                                                inplace, a.g.lanegather != 0)));
+        a.g.xcd = order == 1u ? 0 : (order == 2u ? 1 : cm::kXcdRun);
+        if (order == 0u)
+            a.g.xcd = cm::default_order(d->lattice, d->storage, d->nx, a.g.rowloop != 0, (d->walls & 1u) != 0, inplace,
+                                        a.g.lanegather != 0);
         a.xcd_default = order == 0u ? 1 : 0;
         a.g.aa = inplace ? 1 : 0;
         a.g.ybase = 0;

@@ -219,5 +219,8 @@ void cmhost_equilibrium_f64(const double* rho, const double* u, const double* F,
 }
 
 uint32_t cmhost_rule_ordered_block(uint32_t lin, uint32_t total, int order) { return cm::ordered_block(lin, total, order); }
+int cmhost_rule_default_order(int lattice, int storage, int nx, int rowloop, int walls, int in_place, int lane_gather) {
+    return cm::default_order(lattice, storage, nx, rowloop, walls, in_place, lane_gather);
+}
 
 }

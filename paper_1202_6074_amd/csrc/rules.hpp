@@ -31,4 +31,54 @@ CM_RULE uint32_t ordered_block(uint32_t lin, uint32_t total, int order) {
     return (round + 1u) * 8u * run <= total ? round * 8u * run + (k & 7u) * run + (k >> 3) : lin;
 }
 
+// Workgroup order when the caller gives no hint. lattice: 0 D3Q27, 1 D2Q9; storage: 0
+// FP64, 1 FP32, 2 FP32 shifted, 3 FP16 shifted. When a grid row spans
+// several workgroups (nx > 256 without the row loop), the plain order sends
+// neighbouring workgroups of one row to different XCDs, whose L2s then fetch
+// the cache lines shared at the block boundary twice (and, in the odd
+// in-place step, both write parts of the same lines). Measured on MI355X
+// (MLUPS, plain / XCD-aware): FP32 512^3 26,002 / 27,664; FP32 1024^3 in place
+// 21,423 / 27,103; FP64 512^3 11,539 / 13,311. With one workgroup per
+// row no lines are shared. FP32 and FP32-shifted rows of 129-256 cells (periodic
+// D3Q27): runs of 32 rows per XCD in turn (at 256^3 the eight runs of a round cover one
+// z-plane) beat both; measured on four machines at 256^3 (us per step, plain /
+// XCD-aware / runs): two-buffer step 602 / 627 / 594, 614 / - / 604,
+// 603 / - / 594, 599 / 624 / 591; in place 661 / 673 / 645, 661 / - / 645,
+// 660 / - / 644; FP32 shifted 605 / - / 592. Not faster, so kept plain: walls
+// (plain / runs 593 / 596 us), rows of 128 cells (77.4 / 78.0 us at 128^3),
+// FP16 storage (plain / XCD-aware at 256^3: 329 / 330 us, in place 362 / 373).
+// FP64 rows of up to 256 cells: plain where they start on cache lines (plain /
+// XCD-aware / runs: 128^3 155 / 161 / 155, 96 x 200 x 101 143 / 156 / 144, 192 x 150 x
+// 101 210 / 222 / 210, 64 x 363 x 75 129 / 136 / 131), else runs (201 x 200 x 200 601 /
+// 616 / 589, 130 x 200 x 200 400 / 407 / 382, 150 x 150 x 101 172 / 181 / 169).
+// Two-buffer D3Q27 steps on rows of 257-512 cells run one workgroup per row as
+// well: FP16 in the plain order, which needs no division by the grid's sizes
+// (the kernels are bound by instruction issue; us per step, plain / runs /
+// XCD-aware: 301 x 200 x 200 310 / - / 345; the two-cell kernel at 512 x 512 x
+// 128 656 / 666 / 671, in chunks of planes at 512^3 2,692 / - / 2,726), 4-byte rows
+// in runs (plain / runs / XCD-aware: 300 x 200 x 200 - / 467 / 481, 288 x 200 x 200 425 /
+// 433 / 439, 320 x 200 x 200 474 / 473 / 484, 384 x 200 x 200 571 / 570 / 580, 384^3
+// 2,302 / 2,229 / 2,213, 448 x 200 x 200 679 / 675 / 681, 480 x 200 x 200 732 / 720 / 721;
+// 416 x 200 x 200 618 / 626 / 637), full rows of 512 in the plain one (512 x 200 x 200
+// 728 / 756 / 761, 512 x 64 x 64 78.0 / 82.5 / 84.6, 512 x 512 x 256 2,560 / 2,589 / 2,557).
+// In-place rows of one workgroup go in the plain order (us per step, plain / runs
+// of 32: 300 x 200 x 100 FP32 231 / 234, 512 x 256 x 128 608 / 612, 192^3 253 /
+// 253, 200 x 100 x 100 FP64 150 / 159, 256 x 256 x 128 FP32 303 / 302), but for
+// 4-byte rows that start on cache lines and are split into two workgroups which
+// they do not fill (384 x 384 x 192 1,152 / 1,087, 448 x 200 x 100 336 / 326, 320 x
+// 200 x 200 478 / 476).
+constexpr int kXcdRun = 32;
+inline int default_order(int lattice, int storage, int nx, bool rowloop, bool walls, bool in_place, bool lane_gather) {
+    const bool f64 = storage == 0, four_byte = storage == 1 || storage == 2;
+    if (lattice != 0) return f64 || (!rowloop && nx > 256) ? 1 : 0;
+    if (in_place && !rowloop && !lane_gather && nx <= (f64 ? 256 : 512))
+        return four_byte && nx > 256 && nx % 32 == 0 && nx % 256 != 0 ? kXcdRun : 0;
+    if (f64) return nx > 256 || lane_gather || rowloop ? 1 : (nx % 16 ? kXcdRun : 0);
+    if (!rowloop && nx > 256) {
+        if (lane_gather || nx > 512) return 1;
+        return four_byte && nx < 512 ? kXcdRun : 0;
+    }
+    return four_byte && !rowloop && !walls && nx > 128 ? kXcdRun : 0;
+}
+
 }  // namespace cm

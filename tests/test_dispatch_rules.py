@@ -36,3 +36,17 @@ def test_workgroup_orders(rules, order, total):
         for xcd in range(8):
             assert all(p // run % 8 == xcd for p in at[xcd:full:8])
         assert at[full:] == list(range(full, total))
+
+
+F64, F32, F32S, F16 = 0, 1, 2, 3
+
+
+@pytest.mark.parametrize("storage,nx,want", [
+    # one workgroup per row: no lines are shared between workgroups, so not order 1
+    (F64, 64, 0), (F64, 128, 0), (F64, 192, 0), (F64, 256, 0), (F64, 150, 32), (F64, 201, 32),
+    (F32, 288, 32), (F32, 384, 32), (F32S, 480, 32), (F32, 300, 32), (F32, 511, 32), (F32, 512, 0), (F32S, 512, 0),
+    (F32, 256, 32), (F32, 128, 0), (F16, 301, 0), (F16, 512, 0),
+    # several workgroups per row
+    (F64, 257, 1), (F64, 512, 1), (F32, 513, 1), (F16, 700, 1)])
+def test_default_order_of_two_buffer_rows(rules, storage, nx, want):
+    assert rules.cmhost_rule_default_order(0, storage, nx, 0, 0, 0, 0) == want
