@@ -1638,7 +1638,9 @@ static bool one_block_per_row(const Geom& g) { return g.nx <= 256 && !g.lanegath
 // too few lanes and vectors to gain.
 // (past_l2: one buffer of more than 16 MB.)
 template <int S>
-static bool past_l2(const Geom& g) { return 27 * (size_t)g.N * sizeof(typename Store<S>::T) >= ((size_t)16 << 20); }
+static size_t state_bytes(const Geom& g) { return 27 * (size_t)g.N * sizeof(typename Store<S>::T); }
+template <int S>
+static bool past_l2(const Geom& g) { return state_bytes<S>(g) >= ((size_t)16 << 20); }
 template <int S>
 static bool whole_rows(const Geom& g) {
     constexpr size_t es = sizeof(typename Store<S>::T);
@@ -1825,11 +1827,12 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
         });
     }
     if (one_block_per_row(a.g)) {
+        const unsigned lds = S == 0 ? xlds_reserve_f64(bx, state_bytes<S>(a.g)) : 0u;
         return launch_z_chunks(a.g, grid, sizeof(T) == 4, [&](const dim3& gq, const Geom& gg) {
             with_row_width(bx, [&](auto xl) {
                 constexpr int XL = decltype(xl)::value;
-                if (var) k_step<S, W, LES, FF, true, false, XL><<<gq, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L);
-                else k_step<S, W, LES, FF, false, false, XL><<<gq, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L);
+                if (var) k_step<S, W, LES, FF, true, false, XL><<<gq, bx, lds, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L);
+                else k_step<S, W, LES, FF, false, false, XL><<<gq, bx, lds, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L);
             });
         });
     }

@@ -81,4 +81,15 @@ inline int default_order(int lattice, int storage, int nx, bool rowloop, bool wa
     return four_byte && !rowloop && !walls && nx > 128 ? kXcdRun : 0;
 }
 
+// LDS that an FP64 launch of the LDS-exchange kernel reserves beside the kernel's own,
+// for workgroups of `width` lanes: what a 256-lane one holds (36,864 bytes, four workgroups on a
+// CU) for narrower ones of states of 88 MiB or more. With fewer rows in flight their DRAM
+// accesses stay closer together (us per step, own LDS / reserved: 128 x 256 x 256 617 / 589,
+// 128^3 153 / 148, 112 x 200 x 200 327 / 315, 64 x 200 x 200 188 / 182, 64 x 64 x 128 43.5 / 42.0;
+// smaller states fit the caches and want the lanes: 64^3 22.6 / 24.6, 64 x 100 x 50 26.6 /
+// 28.5). The line lies between 69 and 99 MB.
+inline unsigned xlds_reserve_f64(int width, size_t state_bytes) {
+    return width <= 128 && state_bytes >= (size_t)88 << 20 ? 18u * 8u * (256u - (width <= 64 ? 64u : 128u)) : 0u;
+}
+
 }  // namespace cm

@@ -50,3 +50,11 @@ F64, F32, F32S, F16 = 0, 1, 2, 3
     (F64, 257, 1), (F64, 512, 1), (F32, 513, 1), (F16, 700, 1)])
 def test_default_order_of_two_buffer_rows(rules, storage, nx, want):
     assert rules.cmhost_rule_default_order(0, storage, nx, 0, 0, 0, 0) == want
+
+
+@pytest.mark.parametrize("nx,ny,nz,width,want", [
+    (128, 256, 256, 128, 18432), (112, 200, 200, 128, 18432), (64, 200, 200, 64, 27648), (64, 64, 128, 64, 27648),
+    (64, 64, 64, 64, 0), (64, 100, 50, 64, 0), (192, 200, 200, 192, 0), (256, 256, 256, 256, 0)])
+def test_narrow_fp64_rows_reserve_lds_past_the_caches(rules, nx, ny, nz, width, want):
+    got = rules.cmhost_rule_xlds_reserve_f64(width, ctypes.c_size_t(27 * 8 * nx * ny * nz))
+    assert got == want and (want == 0 or 18 * 8 * width + got == 36864)
