@@ -222,6 +222,7 @@ uint32_t cmhost_rule_ordered_block(uint32_t lin, uint32_t total, int order) { re
 int cmhost_rule_default_order(int lattice, int storage, int nx, int rowloop, int walls, int in_place, int lane_gather) {
     return cm::default_order(lattice, storage, nx, rowloop, walls, in_place, lane_gather);
 }
+int cmhost_rule_walled_pairs(int nx, int64_t rows) { return cm::walled_pairs(nx, rows); }
 unsigned cmhost_rule_xlds_reserve_f64(int width, size_t bytes) { return cm::xlds_reserve_f64(width, bytes); }
 
 }

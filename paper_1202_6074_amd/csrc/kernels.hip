@@ -1809,7 +1809,7 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
         });
         return hipGetLastError();
     }
-    if (whole_rows<S>(a.g)) {
+    if (whole_rows<S>(a.g) && a.g.yrows == a.g.ny) {   // (the kernel takes all rows)
         // rows that start on cache lines (wider than 256 cells: the others of
         // that kind take the LDS exchange): each lane stores its own values
         // (us per step, through LDS / directly: 384 x 384 x 200 FP32 1,158 /
@@ -1985,7 +1985,8 @@ hipError_t step_w(const LaunchArgs& a, const void* src, void* dst) {
         if (a.walls || !a.stress_prev || !a.stress_next) return hipErrorInvalidValue;   // checked by the caller
         return a.force_field ? step_sgs_t<S, true>(a, src, dst) : step_sgs_t<S, false>(a, src, dst);
     }
-    if (packed_rows<S>(a.g) || whole_rows<S>(a.g) || one_block_per_row(a.g))
+    const bool pairs = S == 3 && a.walls && walled_pairs(a.g.nx, (int64_t)a.g.ny * a.g.nz) && pair_rows(a.g, src, dst, a.force_field);
+    if (!pairs && (packed_rows<S>(a.g) || whole_rows<S>(a.g) || one_block_per_row(a.g)))
         return a.walls ? step_les<S, true>(a, src, dst) : step_les<S, false>(a, src, dst);
     return split_wall_rows(a, [&](const LaunchArgs& b, bool w) {
         return w ? step_les<S, true>(b, src, dst) : step_les<S, false>(b, src, dst);

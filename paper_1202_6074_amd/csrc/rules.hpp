@@ -92,4 +92,14 @@ inline unsigned xlds_reserve_f64(int width, size_t state_bytes) {
     return width <= 128 && state_bytes >= (size_t)88 << 20 ? 18u * 8u * (256u - (width <= 64 ? 64u : 128u)) : 0u;
 }
 
+// Even FP16 rows between walls: whether the interior rows take the two-cell kernel and
+// the two wall rows a launch of their own, or all rows go through LDS in one launch. The
+// two-cell kernel issues half the instructions for the memory accesses; the second launch costs
+// about 6 us (us per step, one launch / two-cell and walls: 352 x 200 x 200 354 / 281, 368
+// 358 / 330, 390 401 / 337, 400 403 / 347, 448 x 200 x 100 184 / 184, 480 x 100 x 100 109 / 101, 512 x
+// 512 x 256 1,401 / 1,331, 384^3 1,197 / 1,065; narrower rows 300 x 200 x 200 295 / 319, 320 263 /
+// 262, 340 349 / 348; fewer rows 510 x 64 x 64 48.1 / 50.8, 384 x 64 x 64 36.0 / 37.0, 512 x 20 x 20
+// 8.7 / 14.1, but 400 x 64 x 64 45.9 / 40.5).
+inline bool walled_pairs(int nx, int64_t rows) { return nx >= 352 && rows >= 8192; }
+
 }  // namespace cm

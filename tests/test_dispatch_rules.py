@@ -58,3 +58,10 @@ def test_default_order_of_two_buffer_rows(rules, storage, nx, want):
 def test_narrow_fp64_rows_reserve_lds_past_the_caches(rules, nx, ny, nz, width, want):
     got = rules.cmhost_rule_xlds_reserve_f64(width, ctypes.c_size_t(27 * 8 * nx * ny * nz))
     assert got == want and (want == 0 or 18 * 8 * width + got == 36864)
+
+
+@pytest.mark.parametrize("nx,ny,nz,want", [
+    (352, 200, 200, 1), (400, 200, 200, 1), (512, 512, 256, 1), (480, 100, 100, 1),
+    (300, 200, 200, 0), (258, 200, 200, 0), (512, 64, 64, 0), (400, 16, 16, 0)])
+def test_walled_fp16_rows_in_the_two_cell_kernel(rules, nx, ny, nz, want):
+    assert rules.cmhost_rule_walled_pairs(nx, ctypes.c_int64(ny * nz)) == want

@@ -229,3 +229,14 @@ def test_two_cell_rows_in_chunks_of_planes(nx, ny, nz):
     torch = _torch()
     a, b = _states((nx, ny, nz), "f16s", False, 2, (0, 128))
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("nx", [352, 400, 510, 512])
+@pytest.mark.parametrize("ny", [3, 91])
+def test_two_cell_rows_between_walls(nx, ny):
+    """Even FP16 rows of 352 to 512 cells, from 8,192 rows on: the interior by the
+    two-cell kernel and the wall rows by lanes, against all by lanes."""
+    torch = _torch()
+    for force, les, flags in ((True, True, {}), (False, False, {"factorized": True, "reduced_compressibility": True})):
+        a, b = _states((nx, ny, -(-8192 // ny)), "f16s", True, 2, (0, 32), force, les, flags)
+        assert torch.equal(a, b)
