@@ -223,6 +223,8 @@ int cmhost_rule_default_order(int lattice, int storage, int nx, int rowloop, int
     return cm::default_order(lattice, storage, nx, rowloop, walls, in_place, lane_gather);
 }
 int cmhost_rule_walled_pairs(int nx, int64_t rows) { return cm::walled_pairs(nx, rows); }
+int cmhost_rule_packed_lanes(int nx, int ny, int lanes) { return cm::packed_rows_of(nx, ny, lanes).lanes; }
+int cmhost_rule_packed_rows(int nx, int ny, int lanes) { return cm::packed_rows_of(nx, ny, lanes).rows; }
 unsigned cmhost_rule_xlds_reserve_f64(int width, size_t bytes) { return cm::xlds_reserve_f64(width, bytes); }
 
 }

@@ -1664,10 +1664,11 @@ static int pack_lanes(const Geom& g) {
     if (2 * r1 < r2) return 256;
     return (int64_t)((g.ny + r2 - 1) / r2) * g.nz < 1024 && r1 ? 128 : 256;
 }
-// The launch geometry for `lanes` lanes (at least nx).
-static dim3 pack_rows(Geom& g, int lanes) {
-    const int r = lanes / g.nx;
-    g.pack = r < g.ny ? r : g.ny;
+// The launch geometry for `lanes` lanes (at least nx), cut to the waves that its rows fill.
+static dim3 pack_rows(Geom& g, int& lanes) {
+    const PackedRows p = packed_rows_of(g.nx, g.ny, lanes);
+    g.pack = p.rows;
+    lanes = p.lanes;
     g.packm = (uint32_t)((65536 + g.nx - 1) / g.nx);
     return dim3((g.ny + g.pack - 1) / g.pack, g.nz);
 }
@@ -1767,7 +1768,7 @@ template <int S, typename F>
 static void launch_packed(const LaunchArgs& a, F&& launch) {
     constexpr size_t es = sizeof(typename Store<S>::T);
     Geom gp = a.g;
-    const int lanes = pack_lanes(a.g);
+    int lanes = pack_lanes(a.g);
     const dim3 gq = pack_rows(gp, lanes);
     if ((size_t)gp.nx * es % 128 == 0) launch(gq, lanes, 0u, gp, std::true_type());
     else launch(gq, lanes, (unsigned)(((size_t)gp.pack * 27 * gp.nx * es + 47) / 16 * 16), gp, std::false_type());
@@ -1869,7 +1870,7 @@ static hipError_t step_inplace_t(const LaunchArgs& a, void* buf) {
     const Launch<R> L = make_launch<R>(a);
     if (packed_fill<S>(a.g)) {
         Geom gp = a.g;
-        const int lanes = pack_lanes(a.g);
+        int lanes = pack_lanes(a.g);
         const dim3 gq = pack_rows(gp, lanes);
         auto launch = [&](auto v, auto o) {
             k_step_inplace_packed<S, W, LES, FF, decltype(v)::value, decltype(o)::value>
@@ -2102,7 +2103,7 @@ static hipError_t adjoint_k(const LaunchArgs& a, const void* state, const void* 
     const auto L = make_launch<R>(a);
     if (packed_adjoint<S>(a.g)) {
         Geom gp = a.g;
-        const int lanes = a.g.nx > 128 ? bx : pack_lanes(a.g);
+        int lanes = a.g.nx > 128 ? bx : pack_lanes(a.g);
         const dim3 gq = pack_rows(gp, lanes);
         k_adjoint<S, FF, W, LES, VAR, true><<<gq, lanes, 0, (hipStream_t)a.stream>>>(
             (const T*)state, (const R*)lam_in, (R*)lam_out, (R*)grad_F, (const R*)a.force_field, gp, L);

@@ -102,4 +102,16 @@ inline unsigned xlds_reserve_f64(int width, size_t state_bytes) {
 // 8.7 / 14.1, but 400 x 64 x 64 45.9 / 40.5).
 inline bool walled_pairs(int nx, int64_t rows) { return nx >= 352 && rows >= 8192; }
 
+// Rows and lanes of a workgroup that takes several rows of one z-plane, given at most
+// `lanes` lanes: a plane of fewer rows gets the waves that hold them (us per step, all lanes /
+// cut: 20 x 1 x 8000 FP64 40.2 / 21.1, FP32 18.3 / 11.0, 32 x 1 x 4000 FP16 10.5 / 8.1, in
+// place FP64 13.8 / 12.5; adjoint 32 x 1 x 4000 FP64 75.8 / 24.9).
+struct PackedRows {
+    int rows, lanes;
+};
+inline PackedRows packed_rows_of(int nx, int ny, int lanes) {
+    const int r = lanes / nx, rows = r < ny ? r : ny;
+    return {rows, (rows * nx + 63) / 64 * 64};
+}
+
 }  // namespace cm

@@ -65,3 +65,12 @@ def test_narrow_fp64_rows_reserve_lds_past_the_caches(rules, nx, ny, nz, width, 
     (300, 200, 200, 0), (258, 200, 200, 0), (512, 64, 64, 0), (400, 16, 16, 0)])
 def test_walled_fp16_rows_in_the_two_cell_kernel(rules, nx, ny, nz, want):
     assert rules.cmhost_rule_walled_pairs(nx, ctypes.c_int64(ny * nz)) == want
+
+
+@pytest.mark.parametrize("nx", [8, 9, 20, 32, 47, 64, 85, 100, 128])
+@pytest.mark.parametrize("ny", [1, 2, 3, 5, 40])
+@pytest.mark.parametrize("lanes", [128, 256])
+def test_packed_workgroups_hold_no_idle_waves(rules, nx, ny, lanes):
+    rows, got = rules.cmhost_rule_packed_rows(nx, ny, lanes), rules.cmhost_rule_packed_lanes(nx, ny, lanes)
+    assert 1 <= rows <= ny and rows * nx <= got <= lanes and got % 64 == 0
+    assert got - rows * nx < 64 and (rows == ny or (rows + 1) * nx > lanes)
