@@ -225,6 +225,10 @@ int cmhost_rule_default_order(int lattice, int storage, int nx, int rowloop, int
 int cmhost_rule_walled_pairs(int nx, int64_t rows) { return cm::walled_pairs(nx, rows); }
 int cmhost_rule_packed_lanes(int nx, int ny, int lanes) { return cm::packed_rows_of(nx, ny, lanes).lanes; }
 int cmhost_rule_packed_rows(int nx, int ny, int lanes) { return cm::packed_rows_of(nx, ny, lanes).rows; }
+int cmhost_rule_wide_rows(int es, int ny, int64_t rows, int walls, int sgs) { return cm::wide_rows(es, ny, rows, walls, sgs); }
+int cmhost_rule_inplace_rows_fill(int es, int nx, int ny, int64_t rows, int walls) {
+    return cm::inplace_rows_fill(es, nx, ny, rows, walls);
+}
 unsigned cmhost_rule_xlds_reserve_f64(int width, size_t bytes) { return cm::xlds_reserve_f64(width, bytes); }
 
 }

@@ -1634,18 +1634,19 @@ static bool one_block_per_row(const Geom& g) { return g.nx <= 256 && !g.lanegath
 // to 512 cells: all that the two-cell FP16 kernel does not take (per-lane
 // gather / whole rows: 300 x 200 x 200 FP32 747 / 467, 320 574 / 469,
 // 384 x 384 x 200 1,205 / 1,142, 512 x 512 x 128 1,298 / 1,275), but not FP64,
-// whose LDS would leave two workgroups on a CU. Rows shorter than 16 cells fill
-// too few lanes and vectors to gain.
+// whose LDS would leave two workgroups on a CU, and not on small lattices (wide_rows).
+// Rows shorter than 16 cells fill too few lanes and vectors to gain.
 // (past_l2: one buffer of more than 16 MB.)
 template <int S>
 static size_t state_bytes(const Geom& g) { return 27 * (size_t)g.N * sizeof(typename Store<S>::T); }
 template <int S>
 static bool past_l2(const Geom& g) { return state_bytes<S>(g) >= ((size_t)16 << 20); }
 template <int S>
-static bool whole_rows(const Geom& g) {
+static bool whole_rows(const LaunchArgs& a) {
     constexpr size_t es = sizeof(typename Store<S>::T);
+    const Geom& g = a.g;
     if (g.lanegather || g.rowloop || g.nx < 16 || g.nx > 512) return false;
-    if (g.nx > 256) return es != 8;
+    if (g.nx > 256) return es != 8 && wide_rows((int)es, g.ny, (int64_t)g.ny * g.nz, a.walls != 0, (a.flags & 4u) != 0);
     return (size_t)g.nx * es % 128 != 0 && past_l2<S>(g);
 }
 
@@ -1810,7 +1811,7 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
         });
         return hipGetLastError();
     }
-    if (whole_rows<S>(a.g) && a.g.yrows == a.g.ny) {   // (the kernel takes all rows)
+    if (whole_rows<S>(a) && a.g.yrows == a.g.ny) {   // (the kernel takes all rows)
         // rows that start on cache lines (wider than 256 cells: the others of
         // that kind take the LDS exchange): each lane stores its own values
         // (us per step, through LDS / directly: 384 x 384 x 200 FP32 1,158 /
@@ -1852,9 +1853,11 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
 // 128 cells, where the per-lane kernels' two workgroups on a CU are two to four
 // waves, all goes by rows (64^3 FP32 22.9 / 16.7 / 10.7, 128^3 98 / 84 / 79).
 template <int S>
-static bool inplace_rows(const Geom& g) {
+static bool inplace_rows(const LaunchArgs& a) {
     constexpr size_t es = sizeof(typename Store<S>::T);
+    const Geom& g = a.g;
     if (g.lanegather || g.rowloop || g.nx < 16 || g.nx > (S == 0 ? 256 : 512)) return false;
+    if (!inplace_rows_fill((int)es, g.nx, g.ny, (int64_t)g.ny * g.nz, a.walls != 0)) return false;
     if ((size_t)g.nx * es % 128 != 0 || (es == 4 && g.nx <= 128)) return true;
     return S != 0 && g.aa == 2;
 }
@@ -1882,7 +1885,7 @@ static hipError_t step_inplace_t(const LaunchArgs& a, void* buf) {
         else launch(std::false_type(), std::false_type());
         return hipGetLastError();
     }
-    if (inplace_rows<S>(a.g)) {
+    if (inplace_rows<S>(a)) {
         const dim3 rows(1, a.g.ny, a.g.nz);
         const unsigned lds = odd ? row_lds<T>(a.g) : (27u * (unsigned)a.g.nx * (unsigned)sizeof(T) + 16u + 15u) / 16u * 16u;
         auto launch = [&](auto v, auto o) {
@@ -1912,7 +1915,7 @@ template <int S>
 hipError_t step_inplace_s(const LaunchArgs& a, void* buf) {
     if (a.g.aa != 1 && a.g.aa != 2) return hipErrorInvalidValue;
     // by rows, and on even steps, which only add the wall terms, walls need no launch of their own
-    if (packed_fill<S>(a.g) || inplace_rows<S>(a.g) || a.g.aa == 1)
+    if (packed_fill<S>(a.g) || inplace_rows<S>(a) || a.g.aa == 1)
         return a.walls ? step_inplace_w<S, true>(a, buf) : step_inplace_w<S, false>(a, buf);
     return split_wall_rows(a, [&](const LaunchArgs& b, bool w) {
         return w ? step_inplace_w<S, true>(b, buf) : step_inplace_w<S, false>(b, buf);
@@ -1946,7 +1949,7 @@ static hipError_t step_sgs_t(const LaunchArgs& a, const void* src, void* dst) {
         });
         return hipGetLastError();
     }
-    if (whole_rows<S>(g)) {
+    if (whole_rows<S>(a)) {
         const bool direct = (size_t)g.nx * sizeof(T) % 128 == 0;
         return launch_z_chunks(g, dim3(1, g.ny, g.nz), sizeof(T) == 4, [&](const dim3& gq, const Geom& gg) {
             auto launch = [&](auto v, auto d) {
@@ -1987,7 +1990,7 @@ hipError_t step_w(const LaunchArgs& a, const void* src, void* dst) {
         return a.force_field ? step_sgs_t<S, true>(a, src, dst) : step_sgs_t<S, false>(a, src, dst);
     }
     const bool pairs = S == 3 && a.walls && walled_pairs(a.g.nx, (int64_t)a.g.ny * a.g.nz) && pair_rows(a.g, src, dst, a.force_field);
-    if (!pairs && (packed_rows<S>(a.g) || whole_rows<S>(a.g) || one_block_per_row(a.g)))
+    if (!pairs && (packed_rows<S>(a.g) || whole_rows<S>(a) || one_block_per_row(a.g)))
         return a.walls ? step_les<S, true>(a, src, dst) : step_les<S, false>(a, src, dst);
     return split_wall_rows(a, [&](const LaunchArgs& b, bool w) {
         return w ? step_les<S, true>(b, src, dst) : step_les<S, false>(b, src, dst);

@@ -114,4 +114,34 @@ inline PackedRows packed_rows_of(int nx, int ny, int lanes) {
     return {rows, (rows * nx + 63) / 64 * 64};
 }
 
+// Whether two-buffer rows of 257 to 512 cells (es bytes a value) are many enough for the
+// kernel that copies whole rows through LDS, one workgroup a row: with about one row
+// on a CU its copies, barriers and stores follow one another and show, where the
+// per-lane kernel has twice the workgroups and no barrier (us per step, rows / lanes, at 256,
+// 400 and 576 rows: 300 x 16 x 16 FP32 7.2 / 6.9, 330 x 20 x 20 9.1 / 9.5, 300 x 24 x 24 9.6 /
+// 12.2; FP16, at 400, 676 and 1,024: 511 x 20 x 20 9.7 / 8.2, 511 x 26 x 26 11.4 / 13.8, 345 x
+// 32 x 32 11.6 / 14.7, at 576 345 x 24 x 24 9.9 / 8.6; with the sub-grid force FP32 300 x 16 x 16 8.9 / 9.3,
+// at 64 7.0 / 6.1, FP16 400 x 24 x 24 12.3 / 14.0, at 256 8.1 / 7.5). Between walls the per-lane
+// kernels take two launches, so rows win there at any size (300 x 8 x 8 6.7 / 11.0), but
+// where there are wall rows only.
+inline bool wide_rows(int es, int ny, int64_t rows, bool walls, bool sgs) {
+    if (walls && ny > 2) return true;
+    return rows >= (es == 2 ? (sgs ? 400 : 640) : (sgs ? 256 : 320));
+}
+
+// The same of the in-place steps by rows (16 to 512 cells), whose per-lane kernels also access
+// the cell's own rows: us per step, rows / lanes, FP32 55 x 8 x 8 6.3 / 5.2, 200 x 24 x 24 8.8 / 8.3,
+// 55 x 26 x 30 7.4 / 8.0, 200 x 26 x 30 9.4 / 11.6, 317 x 16 x 16 8.2 / 8.0, 317 x 24 x 24 10.5 / 12.8, 512 x
+// 24 x 24 15.8 / 14.7, 512 x 32 x 32 22.3 / 22.9; FP16 55 x 100 x 100 20.0 / 17.5, 100 x 64 x 64 15.0 /
+// 14.0, 200 x 48 x 48 14.8 / 14.5, 200 x 64 x 64 22.4 / 23.3, 120 x 64 x 64 13.9 / 15.3, 317 x 24 x 24 10.3 / 9.1,
+// 317 x 32 x 32 11.2 / 13.7; FP64 55 x 200 x 200 179 / 168, 120 x 100 x 100 92.7 / 86.9, 120 x 200 x
+// 200 361 / 390, 200 x 100 x 100 150 / 151, 200 x 200 x 200 600 / 682. Between walls the odd
+// per-lane step takes two launches.
+inline bool inplace_rows_fill(int es, int nx, int ny, int64_t rows, bool walls) {
+    if (walls && ny > 2) return true;
+    if (es == 4) return rows >= (nx > 256 && nx % 32 ? 512 : 768);
+    if (nx < 96) return false;
+    return rows >= (es == 8 ? 16384 : (nx > 256 ? 1024 : 4096));
+}
+
 }  // namespace cm

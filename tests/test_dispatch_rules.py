@@ -74,3 +74,19 @@ def test_packed_workgroups_hold_no_idle_waves(rules, nx, ny, lanes):
     rows, got = rules.cmhost_rule_packed_rows(nx, ny, lanes), rules.cmhost_rule_packed_lanes(nx, ny, lanes)
     assert 1 <= rows <= ny and rows * nx <= got <= lanes and got % 64 == 0
     assert got - rows * nx < 64 and (rows == ny or (rows + 1) * nx > lanes)
+
+
+@pytest.mark.parametrize("es,ny,nz,walls,sgs,want", [
+    (4, 2, 63, 0, 0, 0), (4, 16, 16, 0, 0, 0), (4, 24, 24, 0, 0, 1), (2, 48, 11, 0, 0, 0), (2, 24, 24, 0, 0, 0), (2, 26, 26, 0, 0, 1),
+    (4, 8, 8, 0, 1, 0), (4, 16, 16, 0, 1, 1), (2, 16, 16, 0, 1, 0), (2, 24, 24, 0, 1, 1),
+    (4, 8, 8, 1, 0, 1), (2, 3, 2, 1, 0, 1), (4, 2, 2, 1, 0, 0)])
+def test_wide_rows_by_row_from_enough_rows(rules, es, ny, nz, walls, sgs, want):
+    assert rules.cmhost_rule_wide_rows(es, ny, ctypes.c_int64(ny * nz), walls, sgs) == want
+
+
+@pytest.mark.parametrize("es,nx,ny,nz,walls,want", [
+    (4, 55, 3, 72, 0, 0), (4, 200, 24, 24, 0, 0), (4, 200, 32, 32, 0, 1), (4, 267, 3, 2, 0, 0), (4, 317, 24, 24, 0, 1), (4, 512, 24, 24, 0, 0),
+    (4, 512, 32, 32, 0, 1), (2, 55, 200, 200, 0, 0), (2, 120, 64, 64, 0, 1), (2, 200, 32, 32, 0, 0), (2, 317, 24, 24, 0, 0), (2, 317, 32, 32, 0, 1),
+    (8, 55, 200, 200, 0, 0), (8, 120, 100, 100, 0, 0), (8, 200, 200, 200, 0, 1), (8, 55, 8, 8, 1, 1), (2, 300, 2, 2, 1, 0)])
+def test_in_place_rows_by_row_from_enough_rows(rules, es, nx, ny, nz, walls, want):
+    assert rules.cmhost_rule_inplace_rows_fill(es, nx, ny, ctypes.c_int64(ny * nz), walls) == want

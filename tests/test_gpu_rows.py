@@ -240,3 +240,15 @@ def test_two_cell_rows_between_walls(nx, ny):
     for force, les, flags in ((True, True, {}), (False, False, {"factorized": True, "reduced_compressibility": True})):
         a, b = _states((nx, ny, -(-8192 // ny)), "f16s", True, 2, (0, 32), force, les, flags)
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("storage,nx,ny,nz", [
+    ("f32", 55, 41, 25), ("f32s", 129, 41, 25), ("f32", 257, 23, 23), ("f32", 300, 41, 25), ("f32", 512, 41, 25), ("f16s", 97, 65, 64),
+    ("f16s", 187, 65, 64), ("f16s", 257, 33, 33), ("f16s", 384, 41, 25), ("f64", 100, 129, 128), ("f64", 201, 129, 128)])
+@pytest.mark.parametrize("walls", [False, True])
+def test_in_place_rows_of_larger_lattices(storage, nx, ny, nz, walls):
+    """In-place steps by rows where periodic lattices take them, against the steps by lanes."""
+    torch = _torch()
+    for steps, flags in ((1, {}), (3, {"factorized": True, "reduced_compressibility": True}), (4, {})):
+        a, b = _states((nx, ny, nz), storage, walls, steps, (0, 32), force=steps != 3, les=steps != 4, flags=flags, in_place=True)
+        assert torch.equal(a, b), steps
