@@ -229,6 +229,8 @@ int cmhost_rule_wide_rows(int es, int ny, int64_t rows, int walls, int sgs) { re
 int cmhost_rule_inplace_rows_fill(int es, int nx, int ny, int64_t rows, int walls) {
     return cm::inplace_rows_fill(es, nx, ny, rows, walls);
 }
+int cmhost_rule_adjoint_rows_pack(int64_t rows) { return cm::adjoint_rows_pack(rows); }
+int cmhost_rule_adjoint_one_wave(int64_t rows) { return cm::adjoint_one_wave(rows); }
 unsigned cmhost_rule_xlds_reserve_f64(int width, size_t bytes) { return cm::xlds_reserve_f64(width, bytes); }
 
 }

@@ -2086,11 +2086,13 @@ static hipError_t read_t(const LaunchArgs& a, const void* src, void* out0, void*
 // 22.8 / 14.8; 96^3 FP32 51.0 / 52.1, 128^3 119 / 137); and, one row in a workgroup, 4-byte rows
 // that are not whole 32-byte sectors, for the ordinary stores, which share
 // sectors between rows (150^3 269 / 234, 250 x 100 x 100 188 / 171, 101 x 90 x 80 52.9 / 46.7; of
-// whole sectors 120 x 100 x 100 74 / 82, 256 x 256 x 128 497 / 549).
+// whole sectors 120 x 100 x 100 74 / 82, 256 x 256 x 128 497 / 549). Not over 64 cells on few rows
+// (adjoint_rows_pack).
 template <int S>
 static bool packed_adjoint(const Geom& g) {
     if (g.nx < 8 || g.nx > 256) return false;
     if (g.nx <= 64) return true;
+    if (!adjoint_rows_pack((int64_t)g.ny * g.nz)) return false;
     if (sizeof(typename Store<S>::R) == 4 && g.nx % 8 != 0) return true;
     if (g.nx > 128) return false;
     const int lanes = pack_lanes(g), fill = lanes / g.nx * g.nx;
@@ -2102,11 +2104,15 @@ static hipError_t adjoint_k(const LaunchArgs& a, const void* state, const void* 
     using T = typename Store<S>::T;
     using R = typename Store<S>::R;
     int bx;
-    const dim3 grid = grid_for(a.g, bx);
+    dim3 grid = grid_for(a.g, bx);
+    if (a.g.nx <= 256 && adjoint_one_wave((int64_t)a.g.ny * a.g.nz)) {
+        bx = 64;
+        grid.x = (a.g.nx + 63) / 64;
+    }
     const auto L = make_launch<R>(a);
     if (packed_adjoint<S>(a.g)) {
         Geom gp = a.g;
-        int lanes = a.g.nx > 128 ? bx : pack_lanes(a.g);
+        int lanes = a.g.nx > 128 ? row_lanes(a.g) : pack_lanes(a.g);
         const dim3 gq = pack_rows(gp, lanes);
         k_adjoint<S, FF, W, LES, VAR, true><<<gq, lanes, 0, (hipStream_t)a.stream>>>(
             (const T*)state, (const R*)lam_in, (R*)lam_out, (R*)grad_F, (const R*)a.force_field, gp, L);

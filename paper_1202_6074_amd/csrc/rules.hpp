@@ -144,4 +144,12 @@ inline bool inplace_rows_fill(int es, int nx, int ny, int64_t rows, bool walls) 
     return rows >= (es == 8 ? 16384 : (nx > 256 ? 1024 : 4096));
 }
 
+// Adjoint rows of 65 to 256 cells: packed, or one row in a workgroup with ordinary stores,
+// from 2,048 rows on (us, packed / by row: 75 x 32 x 32 FP32 11.1 / 9.6, 89 x 5 x 56 8.5 / 8.3, 250 x
+// 5 x 56 10.9 / 9.8; of more rows 101 x 90 x 80 46.7 / 52.9); and below 512 rows one wave a
+// workgroup, which spreads them over the CUs (89 x 5 x 56 7.1 in one-wave workgroups, 8.3 in two-wave
+// ones).
+inline bool adjoint_rows_pack(int64_t rows) { return rows >= 2048; }
+inline bool adjoint_one_wave(int64_t rows) { return rows < 512; }
+
 }  // namespace cm

@@ -90,3 +90,10 @@ def test_wide_rows_by_row_from_enough_rows(rules, es, ny, nz, walls, sgs, want):
     (8, 55, 200, 200, 0, 0), (8, 120, 100, 100, 0, 0), (8, 200, 200, 200, 0, 1), (8, 55, 8, 8, 1, 1), (2, 300, 2, 2, 1, 0)])
 def test_in_place_rows_by_row_from_enough_rows(rules, es, nx, ny, nz, walls, want):
     assert rules.cmhost_rule_inplace_rows_fill(es, nx, ny, ctypes.c_int64(ny * nz), walls) == want
+
+
+@pytest.mark.parametrize("ny,nz,pack,one_wave", [(5, 56, 0, 1), (16, 16, 0, 1), (32, 32, 0, 0), (90, 80, 1, 0)])
+def test_adjoint_rows_of_few_and_many(rules, ny, nz, pack, one_wave):
+    rows = ctypes.c_int64(ny * nz)
+    assert rules.cmhost_rule_adjoint_rows_pack(rows) == pack
+    assert rules.cmhost_rule_adjoint_one_wave(rows) == one_wave

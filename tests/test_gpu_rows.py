@@ -252,3 +252,29 @@ def test_in_place_rows_of_larger_lattices(storage, nx, ny, nz, walls):
     for steps, flags in ((1, {}), (3, {"factorized": True, "reduced_compressibility": True}), (4, {})):
         a, b = _states((nx, ny, nz), storage, walls, steps, (0, 32), force=steps != 3, les=steps != 4, flags=flags, in_place=True)
         assert torch.equal(a, b), steps
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("nx", [70, 75, 101, 128, 193, 250, 256])
+@pytest.mark.parametrize("walls", [False, True])
+def test_adjoint_of_few_and_many_rows(storage, nx, walls):
+    """As test_adjoint_of_packed_rows below, between and above the numbers of rows at which
+    65 to 256 cells change their kernel: fields repeated along x give the same bits."""
+    torch = _torch()
+    from paper_1202_6074_amd.lattice import Lattice
+    for ny, nz in ((7, 11), (16, 33), (46, 45)):
+        m = -(-257 // nx)
+        g = torch.Generator().manual_seed(nx + ny)
+        u = (0.05 * torch.randn((3, nz, ny, nx), generator=g, dtype=torch.float64)).cuda()
+        F = (1e-3 * torch.randn((3, nz, ny, nx), generator=g, dtype=torch.float64)).cuda()
+        lam0 = torch.randn((nz, ny, 27, nx), generator=g, dtype=torch.float64).cuda()
+        out = []
+        for rep in (1, m):
+            lat = Lattice((nx * rep, ny, nz), storage=storage, walls=walls, wall_u_hi=(0.02, 0.0, 0.01))
+            lat.set_relaxation(1.7, cs_smag=0.12)
+            lat.set_force(field=F.repeat(1, 1, 1, rep))
+            lat.init_equilibrium(u.repeat(1, 1, 1, rep))
+            lam, gF = lat.lam_buffer(), torch.ones((3, nz, ny, nx * rep), dtype=lat.dtype, device="cuda")
+            lat.adjoint_step(lat.state_buffer(), lam0.repeat(1, 1, 1, rep).to(lat.dtype), lam, gF)
+            out.append((lam, gF))
+        assert torch.equal(out[0][0].repeat(1, 1, 1, m), out[1][0]) and torch.equal(out[0][1].repeat(1, 1, 1, m), out[1][1])
