@@ -231,6 +231,8 @@ int cmhost_rule_inplace_rows_fill(int es, int nx, int ny, int64_t rows, int wall
 }
 int cmhost_rule_adjoint_rows_pack(int64_t rows) { return cm::adjoint_rows_pack(rows); }
 int cmhost_rule_adjoint_one_wave(int64_t rows) { return cm::adjoint_one_wave(rows); }
+int cmhost_rule_start_by_rows(int es, int nx, size_t bytes) { return cm::start_by_rows(es, nx, bytes); }
+int cmhost_rule_set_by_rows(int es, int nx, size_t bytes) { return cm::set_by_rows(es, nx, bytes); }
 unsigned cmhost_rule_xlds_reserve_f64(int width, size_t bytes) { return cm::xlds_reserve_f64(width, bytes); }
 
 }

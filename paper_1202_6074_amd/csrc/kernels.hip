@@ -1997,11 +1997,8 @@ hipError_t step_w(const LaunchArgs& a, const void* src, void* dst) {
     });
 }
 
-// Setting a state: one workgroup per row, through LDS (push_rows), for rows of 16
-// to 512 cells of lattices past the L2s (set_populations of 20 x 50 x 50 FP32 8.8
-// us by lane, 10.2 by row; of 100^3 75.6 and 55.8).
-template <int S>
-static bool push_by_rows(const Geom& g) { return g.nx >= 16 && g.nx <= 512 && past_l2<S>(g); }
+// Setting a state: one workgroup per row, through LDS (push_rows), or by lanes
+// (start_by_rows, set_by_rows).
 template <int S>
 static unsigned push_lds(const Geom& g) {
     return 3u * group_stride<typename Store<S>::T>((uint32_t)g.nx) * (unsigned)sizeof(typename Store<S>::T);
@@ -2011,7 +2008,7 @@ static hipError_t init_t(const LaunchArgs& a, void* dst, const void* rho, const 
     using T = typename Store<S>::T;
     using R = typename Store<S>::R;
     hipStream_t st = (hipStream_t)a.stream;
-    if (push_by_rows<S>(a.g)) {
+    if (start_by_rows((int)sizeof(T), a.g.nx, state_bytes<S>(a.g))) {
         k_init_equilibrium<S, W, FF, true><<<dim3(1, a.g.ny, a.g.nz), row_lanes(a.g), push_lds<S>(a.g), st>>>(
             (T*)dst, (const R*)a.force_field, rho, u, dt, a.g, make_launch<R>(a));
     } else {
@@ -2028,7 +2025,7 @@ static hipError_t setpop_t(const LaunchArgs& a, void* dst, const void* f, int dt
     using T = typename Store<S>::T;
     using R = typename Store<S>::R;
     hipStream_t st = (hipStream_t)a.stream;
-    if (push_by_rows<S>(a.g)) {
+    if (set_by_rows((int)sizeof(T), a.g.nx, state_bytes<S>(a.g))) {
         k_set_populations<S, W, true><<<dim3(1, a.g.ny, a.g.nz), row_lanes(a.g), push_lds<S>(a.g), st>>>((T*)dst, f, dt, a.g,
                                                                                                     make_launch<R>(a));
     } else {

@@ -278,3 +278,66 @@ def test_adjoint_of_few_and_many_rows(storage, nx, walls):
             lat.adjoint_step(lat.state_buffer(), lam0.repeat(1, 1, 1, rep).to(lat.dtype), lam, gF)
             out.append((lam, gF))
         assert torch.equal(out[0][0].repeat(1, 1, 1, m), out[1][0]) and torch.equal(out[0][1].repeat(1, 1, 1, m), out[1][1])
+
+
+ELEM = {"f64": 8, "f32": 4, "f32s": 4, "f16s": 2}
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f32s", "f16s"])
+@pytest.mark.parametrize("nx", [16, 20, 24, 33, 40, 65, 130, 187, 256, 257, 300, 511, 512])
+@pytest.mark.parametrize("walls", [False, True])
+def test_large_lattices_set_and_read_as_small_ones(storage, nx, walls):
+    """Starting, setting and reading a lattice of more than 192 MiB a buffer (by rows, where
+    its rows are of a kind that goes by rows) against one below 16 MiB (by lanes) whose
+    fields are the same, repeated along z: bitwise the same, on the walls too."""
+    torch = _torch()
+    from paper_1202_6074_amd.lattice import Lattice
+    es, nz = ELEM[storage], 3
+    ny = (9 << 20) // (27 * es * nx * nz)
+    m = -(-(193 << 20) // (27 * es * nx * ny * nz))
+    assert 27 * es * nx * ny * nz < 16 << 20 and 27 * es * nx * ny * nz * m >= 192 << 20
+    g = torch.Generator().manual_seed(nx)
+    dt = torch.float64 if storage == "f64" else torch.float32
+    u = (0.05 * torch.randn((3, nz, ny, nx), generator=g, dtype=torch.float64)).to(dt).cuda()
+    rho = (1 + 0.02 * torch.randn((nz, ny, nx), generator=g, dtype=torch.float64)).to(dt).cuda()
+    F = (1e-3 * torch.randn((3, nz, ny, nx), generator=g, dtype=torch.float64)).to(dt).cuda()
+    got = []
+    for rep in (1, m):
+        lat = Lattice((nx, ny, nz * rep), storage=storage, walls=walls, wall_u_lo=(0.01, 0.0, -0.02), wall_u_hi=(-0.03, 0.0, 0.01))
+        lat.set_force(field=F.repeat(1, rep, 1, 1))
+        lat.init_equilibrium(u.repeat(1, rep, 1, 1), rho.repeat(rep, 1, 1))
+        lat.step(1)
+        f, f32, mom = lat.populations(), lat.populations(torch.float32), lat.moments()
+        lat.init_equilibrium(u.repeat(1, rep, 1, 1), rho.repeat(rep, 1, 1))
+        start = lat.state_buffer().clone()
+        lat.set_populations(f)
+        got.append((start.view(-1, ny, 27, nx), lat.state_buffer().view(-1, ny, 27, nx), f, f32, mom))
+        lat.close()
+    (start, state, f, f32, mom), big = got
+    assert torch.equal(start.repeat(m, 1, 1, 1), big[0])
+    assert torch.equal(state.repeat(m, 1, 1, 1), big[1])
+    assert torch.equal(f.repeat(1, m, 1, 1), big[2]) and torch.equal(f32.repeat(1, m, 1, 1), big[3])
+    assert torch.equal(mom[0].repeat(m, 1, 1), big[4][0]) and torch.equal(mom[1].repeat(1, m, 1, 1), big[4][1])
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16s"])
+@pytest.mark.parametrize("nx", [40, 187, 300])
+@pytest.mark.parametrize("walls", [False, True])
+def test_large_in_place_lattices_start_as_small_ones(storage, nx, walls):
+    """The same for the start and the setting of an in-place lattice."""
+    torch = _torch()
+    from paper_1202_6074_amd.lattice import Lattice
+    es, nz = ELEM[storage], 3
+    ny = (9 << 20) // (27 * es * nx * nz)
+    m = -(-(193 << 20) // (27 * es * nx * ny * nz))
+    g = torch.Generator().manual_seed(nx)
+    u = (0.05 * torch.randn((3, nz, ny, nx), generator=g)).cuda()
+    got = []
+    for rep in (1, m):
+        lat = Lattice((nx, ny, nz * rep), storage=storage, walls=walls, wall_u_hi=(-0.03, 0.0, 0.01), in_place=True)
+        lat.init_equilibrium(u.repeat(1, rep, 1, 1))
+        start, f = lat.state_buffer().clone(), lat.populations()
+        lat.set_populations(f)
+        got.append((start.view(-1, ny, 27, nx), lat.state_buffer().view(-1, ny, 27, nx)))
+    for small, large in zip(*got):
+        assert torch.equal(small.repeat(m, 1, 1, 1), large)
