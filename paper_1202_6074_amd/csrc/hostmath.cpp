@@ -233,6 +233,10 @@ int cmhost_rule_adjoint_rows_pack(int64_t rows) { return cm::adjoint_rows_pack(r
 int cmhost_rule_adjoint_one_wave(int64_t rows) { return cm::adjoint_one_wave(rows); }
 int cmhost_rule_start_by_rows(int es, int nx, size_t bytes) { return cm::start_by_rows(es, nx, bytes); }
 int cmhost_rule_set_by_rows(int es, int nx, size_t bytes) { return cm::set_by_rows(es, nx, bytes); }
+int cmhost_rule_read_by_rows(int es, int nx, size_t bytes, int moments) { return cm::read_by_rows(es, nx, bytes, moments); }
+int cmhost_rule_read_non_temporal(int out, int nx, int64_t cells, int moments) {
+    return cm::read_non_temporal(out, nx, cells, moments);
+}
 unsigned cmhost_rule_xlds_reserve_f64(int width, size_t bytes) { return cm::xlds_reserve_f64(width, bytes); }
 
 }

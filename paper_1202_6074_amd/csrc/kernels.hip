@@ -1293,10 +1293,7 @@ __global__ void __launch_bounds__(ROWS ? 512 : 256) k_set_populations(typename S
 // ---------------------------------------------------------------- read-out
 // Canonical populations into out0 (27 planes), or, with MOMENTS, rho into out0
 // (1 plane) and u into out1 (3 planes), as OUT values. ROWS: the workgroup
-// covers the row and gathers through LDS. NT: non-temporal stores, for rows of
-// whole 32-byte sectors; others share sectors between waves (us, ordinary /
-// non-temporal: populations of 300 x 181 x 90 FP32 484 / 428, of 201 x 160 x 100
-// FP64 313 / 343).
+// covers the row and gathers through LDS. NT: non-temporal stores (read_non_temporal).
 template <int S, bool WALLS, bool FFIELD, bool MOMENTS, bool ROWS, bool NT, typename OUT>
 __global__ void __launch_bounds__(ROWS ? 512 : 256) k_read(const typename Store<S>::T* __restrict__ src,
                                               const typename Store<S>::R* __restrict__ force, OUT* __restrict__ out0,
@@ -2036,26 +2033,19 @@ static hipError_t setpop_t(const LaunchArgs& a, void* dst, const void* f, int dt
     return hipGetLastError();
 }
 
-// Rows that the read-outs gather through LDS: two-buffer lattices past the L2s
-// (as whole_rows; below, the extra barriers show: populations of 20 x 50 x 50
-// FP32 8.7 us by lane, 10.6 by row), 16 to 512 cells (FP64: 256, by its LDS).
+// Rows that the read-outs gather through LDS (read_by_rows): of two-buffer lattices.
 // us by lane / by row: rho and u of 256^3 FP32 440 / 383, of 300 x 181 x 90
 // FP32-shifted 160 / 118, of 201 x 160 x 100 FP64 165 / 141; populations of
 // 256^3 FP32 1,014 / 857, of 300 x 181 x 90 429 / 375.
-template <int S>
-static bool read_rows(const Geom& g) {
-    return g.aa == 0 && g.nx >= 16 && g.nx <= (S == 0 ? 256 : 512) && past_l2<S>(g);
-}
-
 template <int S, bool W, bool FF, bool MOMENTS, typename OUT>
 static hipError_t read_o(const LaunchArgs& a, const void* src, void* out0, void* out1) {
     using T = typename Store<S>::T;
     using R = typename Store<S>::R;
     hipStream_t st = (hipStream_t)a.stream;
-    const bool nt = (size_t)a.g.nx * sizeof(OUT) % 32 == 0;
+    const bool nt = read_non_temporal((int)sizeof(OUT), a.g.nx, a.g.N, MOMENTS);
     auto launch = [&](auto n) {
         constexpr bool NT = decltype(n)::value;
-        if (read_rows<S>(a.g)) {
+        if (a.g.aa == 0 && read_by_rows((int)sizeof(T), a.g.nx, state_bytes<S>(a.g), MOMENTS)) {
             k_read<S, W, FF, MOMENTS, true, NT, OUT><<<dim3(1, a.g.ny, a.g.nz), row_lanes(a.g), row_lds<T>(a.g), st>>>(
                 (const T*)src, (const R*)a.force_field, (OUT*)out0, (OUT*)out1, a.g, make_launch<R>(a));
         } else {

@@ -175,4 +175,24 @@ inline bool set_by_rows(int es, int nx, size_t state_bytes) {
     return nx >= 48 || (nx * es % 16 == 0 && nx * es >= 64) || (es == 8 && nx < 40);
 }
 
+// Whether the read-outs of a two-buffer lattice go by whole rows through LDS: past the L2s (below,
+// the extra barriers show: populations of 20 x 50 x 50 FP32 8.7 us by lane, 10.6 by
+// row), rows of up to 512 cells (FP64: 256, by its LDS). Populations from 5 cells on, whose many stores
+// want the loads out of the caches' way (us, lanes / rows: 5 x 200 x 300 FP32 96.7 / 84.6, 15 x 129 x 129 38.0 /
+// 30.6, 11 x 200 x 200 80.0 / 57.8, FP64 98.3 / 57.2; 3 x 200 x 300 76.7 / 82.5), density and
+// velocity from 16 (8 x 200 x 200 21.9 / 23.2, 15 x 258 x 258 45.1 / 43.1).
+inline bool read_by_rows(int es, int nx, size_t state_bytes, bool moments) {
+    return nx >= (moments ? 16 : 5) && nx <= (es == 8 ? 256 : 512) && state_bytes >= (size_t)16 << 20;
+}
+
+// Non-temporal stores of the read-outs (out bytes a value): of rows of whole 32-byte sectors;
+// others share sectors between waves (populations of 201 x 160 x 100 FP64 313 us ordinary, 343
+// non-temporal). Populations also from 320 MiB of output and 64 cells a row on: less stays in
+// the Infinity Cache and is completed there (us, ordinary / non-temporal: 100^3 FP32 (216 MB) 58 / 83, 128 x 128 x
+// 64 (226 MB) 55.5 / 66.4, 128^3 (453 MB) 144 / 140, 100 x 100 x 200 (432 MB) 172 / 168, 300 x 181 x 90 484 / 428;
+// 20 x 400 x 400 380 / 444).
+inline bool read_non_temporal(int out, int nx, int64_t cells, bool moments) {
+    return (int64_t)nx * out % 32 == 0 && (moments || (nx >= 64 && 27 * cells * out >= (int64_t)320 << 20));
+}
+
 }  // namespace cm

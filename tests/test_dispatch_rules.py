@@ -108,3 +108,16 @@ def test_states_set_by_rows(rules, es, nx, cells, start, set_):
     nbytes = ctypes.c_size_t(27 * es * cells)
     assert rules.cmhost_rule_start_by_rows(es, nx, nbytes) == start
     assert rules.cmhost_rule_set_by_rows(es, nx, nbytes) == set_
+
+
+@pytest.mark.parametrize("es,nx,ny,nz,pop_rows,mom_rows,pop_nt,mom_nt", [
+    (4, 15, 104, 155, 1, 0, 0, 0), (4, 9, 200, 200, 1, 0, 0, 0), (4, 3, 200, 300, 0, 0, 0, 0), (4, 100, 100, 100, 1, 1, 0, 1), (4, 20, 400, 400, 1, 1, 0, 1),
+    (4, 128, 128, 128, 1, 1, 1, 1), (4, 300, 181, 90, 1, 1, 1, 1), (8, 201, 160, 100, 1, 1, 0, 0), (8, 300, 100, 100, 0, 0, 1, 1),
+    (4, 20, 50, 50, 0, 0, 0, 1), (4, 700, 40, 40, 0, 0, 0, 1)])
+def test_read_outs(rules, es, nx, ny, nz, pop_rows, mom_rows, pop_nt, mom_nt):
+    """FP64 values read out."""
+    cells = nx * ny * nz
+    nbytes = ctypes.c_size_t(27 * es * cells)
+    got = [rules.cmhost_rule_read_by_rows(es, nx, nbytes, m) for m in (0, 1)]
+    got += [rules.cmhost_rule_read_non_temporal(8, nx, ctypes.c_int64(cells), m) for m in (0, 1)]
+    assert got == [pop_rows, mom_rows, pop_nt, mom_nt]

@@ -341,3 +341,25 @@ def test_large_in_place_lattices_start_as_small_ones(storage, nx, walls):
         got.append((start.view(-1, ny, 27, nx), lat.state_buffer().view(-1, ny, 27, nx)))
     for small, large in zip(*got):
         assert torch.equal(small.repeat(m, 1, 1, 1), large)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("nx", [4, 5, 8, 9, 15, 16])
+def test_short_rows_read_by_rows(storage, nx):
+    """Populations and moments of short rows past 16 MiB against those of a small lattice
+    with the same fields, repeated along z."""
+    torch = _torch()
+    from paper_1202_6074_amd.lattice import Lattice
+    es, nz = ELEM[storage], 3
+    ny = (5 << 20) // (27 * es * nx * nz)
+    m = -(-(17 << 20) // (27 * es * nx * ny * nz))
+    g = torch.Generator().manual_seed(nx)
+    u = (0.05 * torch.randn((3, nz, ny, nx), generator=g, dtype=torch.float64)).cuda()
+    got = []
+    for rep in (1, m):
+        lat = Lattice((nx, ny, nz * rep), storage=storage, walls=True, wall_u_hi=(-0.03, 0.0, 0.01))
+        lat.init_equilibrium(u.repeat(1, rep, 1, 1))
+        got.append((lat.populations(), lat.populations(torch.float32), lat.moments()))
+    (f, f32, mom), big = got
+    assert torch.equal(f.repeat(1, m, 1, 1), big[0]) and torch.equal(f32.repeat(1, m, 1, 1), big[1])
+    assert torch.equal(mom[0].repeat(m, 1, 1), big[2][0]) and torch.equal(mom[1].repeat(1, m, 1, 1), big[2][1])
