@@ -237,6 +237,9 @@ int cmhost_rule_read_by_rows(int es, int nx, size_t bytes, int moments) { return
 int cmhost_rule_read_non_temporal(int out, int nx, int64_t cells, int moments) {
     return cm::read_non_temporal(out, nx, cells, moments);
 }
+int cmhost_rule_chunks_pay(int nz, int64_t per_plane, int adjoint) {
+    return cm::chunks_pay(nz, per_plane, adjoint ? cm::kMinAdjointChunk : cm::kMinStepChunk);
+}
 unsigned cmhost_rule_xlds_reserve_f64(int width, size_t bytes) { return cm::xlds_reserve_f64(width, bytes); }
 
 }

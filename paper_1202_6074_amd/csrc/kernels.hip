@@ -1745,11 +1745,10 @@ constexpr unsigned kLdsTwoPerCu = 60000, kLdsThreePerCu = 50000, kLdsPairCap = 4
 // but 9,578 / 10,113 on another), the in-place kernels (256^3: 653 / 656 us) and
 // the D2Q9 step (8192^2: 869 us in one launch, 875-927 us in chunks of 4096-512
 // rows). The FP32 sub-grid-force step with one workgroup per row gains 1.1 %
-// (769.4 / 761.2 us at 256^3).
-constexpr int kZChunk = 128;
+// (769.4 / 761.2 us at 256^3). Only where a chunk fills the chip many times over (chunks_pay).
 template <typename Launch1>
-static hipError_t launch_z_chunks(const Geom& g, const dim3& grid, bool chunked, Launch1&& launch) {
-    const int chunk = chunked && !g.one_launch && g.nz > kZChunk ? kZChunk : g.nz;
+static hipError_t launch_z_chunks(const Geom& g, const dim3& grid, bool chunked, Launch1&& launch, int64_t min_chunk = kMinStepChunk) {
+    const int chunk = chunked && !g.one_launch && chunks_pay(g.nz, (int64_t)grid.x * grid.y, min_chunk) ? kZChunk : g.nz;
     for (int z0 = 0; z0 < g.nz; z0 += chunk) {
         Geom gg = g;
         gg.zbase = z0;
@@ -2108,8 +2107,7 @@ static hipError_t adjoint_k(const LaunchArgs& a, const void* state, const void* 
     return launch_z_chunks(a.g, grid, true, [&](const dim3& gq, const Geom& gg) {
         k_adjoint<S, FF, W, LES, VAR, false><<<gq, bx, 0, (hipStream_t)a.stream>>>((const T*)state, (const R*)lam_in, (R*)lam_out,
                                                                             (R*)grad_F, (const R*)a.force_field, gg, L);
-    });
-
+    }, kMinAdjointChunk);
 }
 template <int S, bool FF, bool W>
 static hipError_t adjoint_w(const LaunchArgs& a, const void* state, const void* lam_in, void* lam_out, void* grad_F) {

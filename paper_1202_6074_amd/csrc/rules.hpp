@@ -195,4 +195,14 @@ inline bool read_non_temporal(int out, int nx, int64_t cells, bool moments) {
     return (int64_t)nx * out % 32 == 0 && (moments || (nx >= 64 && 27 * cells * out >= (int64_t)320 << 20));
 }
 
+// Launches over chunks of kZChunk z-planes: where a chunk has at least min_chunk workgroups (per
+// plane of them given). Every launch ends with a partly empty chip, and thin planes made chunks
+// of a few microseconds (us per step, chunks / one launch: FP32 256 x 128 x 512 588 / 597,
+// 256 x 64 x 1024 606 / 595, 200 x 100 x 400 316 / 304, 256 x 32 x 1024 318 / 295, 300 x 32 x 512 213 / 195, 256 x
+// 8 x 2048 187 / 147, 64 x 64 x 1000 166 / 147, 100 x 1 x 4000 162 / 13; adjoint 256 x 128 x 512 986 / 1,008, 200 x
+// 100 x 400 592 / 608, 256 x 64 x 1024 1,006 / 1,008, 128 x 64 x 1024 530 / 497, 256 x 32 x 1024 532 / 493).
+constexpr int kZChunk = 128;
+constexpr int64_t kMinStepChunk = 16384, kMinAdjointChunk = 12288;
+inline bool chunks_pay(int nz, int64_t per_plane, int64_t min_chunk) { return nz > kZChunk && per_plane * kZChunk >= min_chunk; }
+
 }  // namespace cm

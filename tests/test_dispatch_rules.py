@@ -121,3 +121,10 @@ def test_read_outs(rules, es, nx, ny, nz, pop_rows, mom_rows, pop_nt, mom_nt):
     got = [rules.cmhost_rule_read_by_rows(es, nx, nbytes, m) for m in (0, 1)]
     got += [rules.cmhost_rule_read_non_temporal(8, nx, ctypes.c_int64(cells), m) for m in (0, 1)]
     assert got == [pop_rows, mom_rows, pop_nt, mom_nt]
+
+
+@pytest.mark.parametrize("nz,rows,adjoint,want", [
+    (128, 256, 0, 0), (256, 256, 0, 1), (512, 128, 0, 1), (1024, 64, 0, 0), (400, 100, 0, 0), (4000, 1, 0, 0), (1500, 3, 0, 0),
+    (400, 100, 1, 1), (1024, 64, 1, 0), (256, 256, 1, 1), (128, 128, 1, 0)])
+def test_chunks_of_planes(rules, nz, rows, adjoint, want):
+    assert rules.cmhost_rule_chunks_pay(nz, ctypes.c_int64(rows), adjoint) == want
