@@ -1719,7 +1719,7 @@ static bool pair_rows(const Geom& g, const void* src, const void* dst, const voi
 // Occupancy caps by LDS reservation: with 60,000 bytes of the CU's 160 KB of
 // LDS reserved per workgroup, at most two workgroups share a CU, with 50,000
 // three; with 40,960 bytes, three for a kernel that holds 9 KB of its own. The
-// reserved LDS itself is not used. Fewer resident rows per CU make the DRAM
+// reserved LDS itself is not used (the per-lane two-buffer kernels hold none: 40,960 bytes are four there). Fewer resident rows per CU make the DRAM
 // traffic of these kernels more efficient. The per-lane in-place pair with 4-byte
 // populations on rows of at most 512 cells: two workgroups where they are full
 // 256-lane ones, three where rows leave lanes idle or take 192 (us per step, two /
@@ -1834,8 +1834,12 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
             });
         });
     }
-    if (var) k_step<S, W, LES, FF, true, false, 0><<<grid, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
-    else k_step<S, W, LES, FF, false, false, 0><<<grid, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
+    // per-lane rows of 257 to 512 cells with 4-byte values, which the hints and small lattices take:
+    // four workgroups on a CU (300 x 200 x 100 FP32 380 us per step without,
+    // 341 with; with the row loop 436 and 386; 512 x 512 x 128 1,323 and 1,299)
+    const unsigned cap = sizeof(T) == 4 && a.g.nx > 256 && a.g.nx <= 512 ? kLdsPairCap : 0u;
+    if (var) k_step<S, W, LES, FF, true, false, 0><<<grid, bx, cap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
+    else k_step<S, W, LES, FF, false, false, 0><<<grid, bx, cap, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L);
     return hipGetLastError();
 }
 
