@@ -240,6 +240,9 @@ int cmhost_rule_read_non_temporal(int out, int nx, int64_t cells, int moments) {
 int cmhost_rule_chunks_pay(int nz, int64_t per_plane, int adjoint) {
     return cm::chunks_pay(nz, per_plane, adjoint ? cm::kMinAdjointChunk : cm::kMinStepChunk);
 }
+int cmhost_rule_d2q9_non_temporal(int es, int nx, int64_t cells, int field, int sgs) {
+    return cm::d2q9_non_temporal(es, nx, cells, field, sgs);
+}
 unsigned cmhost_rule_xlds_reserve_f64(int width, size_t bytes) { return cm::xlds_reserve_f64(width, bytes); }
 
 }

@@ -364,21 +364,11 @@ static Launch<R> make_launch(const LaunchArgs& a) {
     return L;
 }
 
-// Non-temporal stores of the step (f gets them as a compile-time constant): rows
-// of whole cache lines of buffers two of which are well beyond the 256 MB Infinity
-// Cache. Smaller ones are found there again by the next step, and rows that share
-// lines would write them in parts, which in FP64 costs less than what ordinary
-// stores evict up to 384 MiB (us per step, ordinary / non-temporal: 4096^2 FP32 230 /
-// 211, FP16 155 / 151; 2048 x 1400 FP64 82 / 69; 2048^2 FP32 49.8 / 52.4; sharing
-// lines 4001^2 FP32 249 / 292, FP16 160 / 171, 2429 x 2067 FP32-shifted between walls
-// 64 / 79, FP16 51.7 / 54.3; FP64 3000 x 500 38 / 42, 1500^2 60 / 64, 2501 x 1001 78 /
-// 73, 2000 x 1501 89 / 75, 3179 x 951 95 / 91, 1801^2 103 / 97, 4001 x 2001 243 / 257;
-// 1500^2 with the sub-grid force 47 / 52).
+// The step's stores (f gets whether they are non-temporal as a compile-time constant).
 template <typename T, typename F>
-static void with_stores(const Geom& g, F&& f) {
-    const size_t bytes = 9 * (size_t)g.N * sizeof(T);
-    const bool lines = (size_t)g.nx * sizeof(T) % 128 == 0 || (sizeof(T) == 8 && bytes < ((size_t)384 << 20));
-    if (lines && bytes >= ((size_t)168 << 20)) f(std::true_type());
+static void with_stores(const LaunchArgs& a, F&& f) {
+    const bool nt = cm::d2q9_non_temporal((int)sizeof(T), a.g.nx, a.g.N, a.force_field != nullptr, (a.flags & 4u) != 0);
+    if (nt) f(std::true_type());
     else f(std::false_type());
 }
 
@@ -389,7 +379,7 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
     int bx;
     const dim3 grid = grid_for(a.g, bx, a.g.rowloop != 0);
     const bool var = (a.flags & 3u) != 0;
-    with_stores<T>(a.g, [&](auto n) {
+    with_stores<T>(a, [&](auto n) {
         constexpr bool NT = decltype(n)::value;
         if (var) k2_step<S, W, LES, FF, true, false, NT><<<grid, bx, 0, (hipStream_t)a.stream>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, make_launch<R>(a));
         else k2_step<S, W, LES, FF, false, false, NT><<<grid, bx, 0, (hipStream_t)a.stream>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, make_launch<R>(a));
@@ -409,7 +399,7 @@ static hipError_t step_sgs_t(const LaunchArgs& a, const void* src, void* dst) {
     const R* rp = (const R*)a.stress_prev;
     R* rn = (R*)a.stress_next;
     const bool var = (a.flags & 3u) != 0;
-    with_stores<T>(a.g, [&](auto n) {
+    with_stores<T>(a, [&](auto n) {
         constexpr bool NT = decltype(n)::value;
         if (var) k2_step<S, false, false, FF, true, true, NT><<<grid, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L, rp, rn);
         else k2_step<S, false, false, FF, false, true, NT><<<grid, bx, 0, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, a.g, L, rp, rn);

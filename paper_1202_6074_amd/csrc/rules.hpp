@@ -205,4 +205,30 @@ constexpr int kZChunk = 128;
 constexpr int64_t kMinStepChunk = 16384, kMinAdjointChunk = 12288;
 inline bool chunks_pay(int nz, int64_t per_plane, int64_t min_chunk) { return nz > kZChunk && per_plane * kZChunk >= min_chunk; }
 
+// Non-temporal stores of the D2Q9 step (es bytes a population). `moved`: the two population
+// buffers, the force field and one set of the sub-grid stress. Up to about 360 MiB the next step finds
+// much of what this one stored in the 256 MB Infinity Cache, more of it without a field (us per
+// step, ordinary / non-temporal, at moved MB: FP32 with a field 2048^2 335 49.5 / 52.1, 2176^2 379 68.7 / 60.7,
+// 4096^2 1,342 229 / 210; FP64 1536 x 1400 344 52.5 / 55.7, 1536^2 377 62.7 / 59.9, 2048^2 671 119 / 99; FP16 2560^2
+// 288 56.9 / 59.2, 3072^2 415 87.4 / 83.7; without FP32 2304^2 382 63.7 / 67.7, 2432^2 426 78.2 / 75.1, FP64 2301 x
+// 1501 497 91.4 / 89.6, 2001 x 1301 375 67.0 / 73.3; sub-grid force 1920^2 339 71.2 / 74.3, 2048^2 385 79.6 / 73.3;
+// against the line's side FP64 1600 x 1104 283 48.7 / 47.3 and 1664 x 1152 307 52.6 / 51.2). Rows that share
+// cache lines write them in parts, which costs more the more of the state is in memory anyway: FP16
+// and, without a field, 4-byte values keep ordinary stores (4001 x 2001 FP16 75.2 / 78.4, 4001^2 152 / 161;
+// 3179 x 1951 FP32 84.7 / 86.2, 2429 x 2067 63.1 / 72.0), the others from 720 MB on (FP32 2429 x 2067 402
+// 78.1 / 74.0, 3001 x 2701 648 122 / 118, 3401 x 2701 735 145.6 / 144.3, 4001^2 1,281 242 / 279; FP64 1500 x 1501 360
+// 57.0 / 58.6, 2501 x 1001 401 73.9 / 67.3, 2601 x 1701 708 134 / 126, 2429 x 2067 802 156.0 / 156.2, 3179 x 1951
+// 992 184 / 194). Rows of less than a wave are stored by one-wave workgroups: non-temporal, FP64 from 48 MiB
+// a buffer (50 x 4000 FP32 6.64 / 6.26, FP16 6.13 / 5.64, FP64 7.1 / 8.0; 50 x 40000 FP32 32.8 / 30.5, FP64 58.8 / 53.0).
+inline bool d2q9_non_temporal(int es, int nx, int64_t cells, bool field, bool sgs) {
+    constexpr int64_t M = (int64_t)1 << 20;
+    const int64_t pop = 9 * cells * es, real = cells * (es == 8 ? 8 : 4);
+    const int64_t moved = 2 * pop + (field ? 2 * real : 0) + (sgs ? 3 * real : 0);
+    if (nx < 64 && (es != 8 || pop >= 48 * M)) return true;
+    if (moved < (field ? 356 : 386) * M) return false;
+    if ((int64_t)nx * es % 128 == 0) return true;
+    if (es == 2 || (es == 4 && !field)) return false;
+    return moved < 687 * M;
+}
+
 }  // namespace cm

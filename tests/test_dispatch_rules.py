@@ -128,3 +128,16 @@ def test_read_outs(rules, es, nx, ny, nz, pop_rows, mom_rows, pop_nt, mom_nt):
     (400, 100, 1, 1), (1024, 64, 1, 0), (256, 256, 1, 1), (128, 128, 1, 0)])
 def test_chunks_of_planes(rules, nz, rows, adjoint, want):
     assert rules.cmhost_rule_chunks_pay(nz, ctypes.c_int64(rows), adjoint) == want
+
+
+@pytest.mark.parametrize("es,nx,ny,field,sgs,want", [
+    (4, 2048, 2048, 1, 0, 0), (4, 2176, 2176, 1, 0, 1), (4, 4096, 4096, 1, 0, 1), (4, 8192, 8192, 1, 0, 1), (4, 2304, 2304, 0, 0, 0), (4, 2432, 2432, 0, 0, 1),
+    (8, 1536, 1400, 1, 0, 0), (8, 1536, 1536, 1, 0, 1), (8, 2048, 2048, 0, 0, 1), (2, 2560, 2560, 1, 0, 0), (2, 3072, 3072, 1, 0, 1),
+    (4, 1500, 1500, 1, 1, 0), (4, 2048, 2048, 1, 1, 1),
+    # rows that share cache lines
+    (4, 2429, 2067, 1, 0, 1), (4, 2429, 2067, 0, 0, 0), (4, 4001, 4001, 1, 0, 0), (2, 2429, 2067, 1, 0, 0), (2, 4001, 4001, 1, 0, 0),
+    (8, 1500, 1501, 1, 0, 0), (8, 3179, 951, 1, 0, 1), (8, 2001, 1301, 0, 0, 0), (8, 3179, 1951, 1, 0, 0),
+    # rows of less than a wave
+    (4, 50, 4000, 1, 0, 1), (2, 50, 4000, 1, 0, 1), (8, 50, 4000, 1, 0, 0), (8, 50, 40000, 1, 0, 1), (4, 100, 100, 1, 0, 0)])
+def test_d2q9_stores(rules, es, nx, ny, field, sgs, want):
+    assert rules.cmhost_rule_d2q9_non_temporal(es, nx, ctypes.c_int64(nx * ny), field, sgs) == want

@@ -344,3 +344,37 @@ def test_sgs_force_step_matches_oracle(storage, fact, rc):
     assert np.abs(to_np(ug)[:, 0] - uo).max() < 40 * TOL[storage]
     red, ref = lat.reduce(), sim.reduce()
     assert abs(red["ke"] - ref["ke"]) < 1e-6 * ref["ke"] + 40 * TOL[storage]
+
+
+@pytest.mark.parametrize("storage,nx,m,ny,opts", [
+    ("f64", 41, 61, 1001, {}),                                              # rows that share cache lines
+    ("f64", 64, 32, 2048, dict(walls=True, uniform=True)),
+    ("f64", 10, 5, 40000, {}),                                              # rows of less than a wave
+    ("f32", 50, 2, 4000, dict(walls=True)),                                 # (here the small one)
+    ("f32", 347, 7, 2067, dict(walls=True, flags=dict(factorized=True, reduced_compressibility=True))),
+    ("f32s", 32, 68, 2176, {}),
+    ("f32s", 38, 64, 2432, dict(uniform=True, walls=True)),
+    ("f16s", 64, 48, 3072, dict(walls=True)),
+    ("f32", 32, 64, 2048, dict(flags=dict(sgs_force=True))),
+    ("f64", 16, 96, 1536, dict(flags=dict(sgs_force=True, reduced_compressibility=True)))])
+def test_non_temporal_steps_as_ordinary_ones(storage, nx, m, ny, opts):
+    """Steps whose results are stored non-temporally against steps with ordinary stores of a
+    lattice whose fields are the same, repeated along x: bitwise the same."""
+    torch = _torch()
+    from paper_1202_6074_amd.lattice import Lattice
+    g = torch.Generator().manual_seed(nx)
+    u = (0.05 * torch.randn((2, 1, ny, nx), generator=g, dtype=torch.float64)).cuda()
+    F = (1e-3 * torch.randn((2, 1, ny, nx), generator=g, dtype=torch.float64)).cuda()
+    got = []
+    for rep in (1, m):
+        lat = Lattice((nx * rep, ny), storage=storage, lattice="d2q9", walls=opts.get("walls", False), wall_u_hi=(0.02, 0.0, 0.0))
+        lat.set_relaxation(1.7, cs_smag=0.12, **opts.get("flags", {}))
+        if opts.get("uniform"):
+            lat.set_force((1e-4, 2e-4, 0.0))
+        else:
+            lat.set_force((0.0, 0.0, 0.0), F.repeat(1, 1, 1, rep))
+        lat.init_equilibrium(u.repeat(1, 1, 1, rep))
+        lat.step(3)
+        got.append(lat.state_buffer().view(ny, 9, nx * rep).clone())
+        lat.close()
+    assert torch.equal(got[0].repeat(1, 1, m), got[1])
