@@ -138,7 +138,8 @@ typedef struct {
                                order of the step kernel: 0 library default,
                                by storage and row length, 1 plain, 2 XCD-aware
                                (each XCD takes a contiguous range of rows;
-                               as 3 where the workgroups are no multiple of 8), 3
+                               as 3 where the workgroups are no multiple of 8
+                               and the state has 16 MiB or more), 3
                                runs of 32 consecutive workgroups per XCD in
                                turn (the workgroups after the last full round
                                in the plain order); steps with several rows

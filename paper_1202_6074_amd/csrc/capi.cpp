@@ -208,6 +208,7 @@ cmlbm_status cmlbm_create(const cmlbm_desc* d, void* buf_a, void* buf_b, size_t 
         if (order == 0u)
             a.g.xcd = cm::default_order(d->lattice, d->storage, d->nx, a.g.rowloop != 0, (d->walls & 1u) != 0, inplace,
                                         a.g.lanegather != 0);
+        if (a.g.xcd == 1 && need < cm::kSmallState) a.g.xcd = -1;
         a.xcd_default = order == 0u ? 1 : 0;
         a.g.aa = inplace ? 1 : 0;
         a.g.ybase = 0;

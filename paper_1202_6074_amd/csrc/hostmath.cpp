@@ -229,8 +229,7 @@ int cmhost_rule_wide_rows(int es, int ny, int64_t rows, int walls, int sgs) { re
 int cmhost_rule_inplace_rows_fill(int es, int nx, int ny, int64_t rows, int walls) {
     return cm::inplace_rows_fill(es, nx, ny, rows, walls);
 }
-int cmhost_rule_adjoint_rows_pack(int64_t rows) { return cm::adjoint_rows_pack(rows); }
-int cmhost_rule_adjoint_one_wave(int64_t rows) { return cm::adjoint_one_wave(rows); }
+int cmhost_rule_adjoint_one_wave(int nx, int64_t rows) { return cm::adjoint_one_wave(nx, rows); }
 int cmhost_rule_start_by_rows(int es, int nx, size_t bytes) { return cm::start_by_rows(es, nx, bytes); }
 int cmhost_rule_set_by_rows(int es, int nx, size_t bytes) { return cm::set_by_rows(es, nx, bytes); }
 int cmhost_rule_read_by_rows(int es, int nx, size_t bytes, int moments) { return cm::read_by_rows(es, nx, bytes, moments); }

@@ -2076,17 +2076,17 @@ static hipError_t read_t(const LaunchArgs& a, const void* src, void* out0, void*
 // 22.8 / 14.8; 96^3 FP32 51.0 / 52.1, 128^3 119 / 137); and, one row in a workgroup, 4-byte rows
 // that are not whole 32-byte sectors, for the ordinary stores, which share
 // sectors between rows (150^3 269 / 234, 250 x 100 x 100 188 / 171, 101 x 90 x 80 52.9 / 46.7; of
-// whole sectors 120 x 100 x 100 74 / 82, 256 x 256 x 128 497 / 549). Not over 64 cells on few rows
-// (adjoint_rows_pack).
+// whole sectors 120 x 100 x 100 74 / 82, 256 x 256 x 128 497 / 549), but not where one-wave workgroups spread better
+// (adjoint_one_wave).
 template <int S>
 static bool packed_adjoint(const Geom& g) {
     if (g.nx < 8 || g.nx > 256) return false;
     if (g.nx <= 64) return true;
-    if (!adjoint_rows_pack((int64_t)g.ny * g.nz)) return false;
-    if (sizeof(typename Store<S>::R) == 4 && g.nx % 8 != 0) return true;
-    if (g.nx > 128) return false;
-    const int lanes = pack_lanes(g), fill = lanes / g.nx * g.nx;
-    return fill * ((g.nx + 63) / 64 * 64) * 10 >= 12 * g.nx * lanes;
+    if (g.nx <= 128) {
+        const int lanes = pack_lanes(g), fill = lanes / g.nx * g.nx;
+        if (fill * ((g.nx + 63) / 64 * 64) * 10 >= 12 * g.nx * lanes) return true;
+    }
+    return sizeof(typename Store<S>::R) == 4 && g.nx % 8 != 0 && !adjoint_one_wave(g.nx, (int64_t)g.ny * g.nz);
 }
 
 template <int S, bool FF, bool W, bool LES, bool VAR>
@@ -2095,7 +2095,7 @@ static hipError_t adjoint_k(const LaunchArgs& a, const void* state, const void* 
     using R = typename Store<S>::R;
     int bx;
     dim3 grid = grid_for(a.g, bx);
-    if (a.g.nx <= 256 && adjoint_one_wave((int64_t)a.g.ny * a.g.nz)) {
+    if (adjoint_one_wave(a.g.nx, (int64_t)a.g.ny * a.g.nz)) {
         bx = 64;
         grid.x = (a.g.nx + 63) / 64;
     }

@@ -23,10 +23,17 @@ namespace cm {
 // 32 there (us per step, plain / eighths of unequal length / runs of 32: D2Q9 3179 x
 // 951 FP64 83.4 / 90.8 / 82.7, 4001^2 FP32 274 / 249 / 242, D3Q27 600 x 101 x 75 FP64
 // 351 / 376 / 358, 300 x 201 x 101 FP64 641 / 593 / 554, 1000 x 101 x 51 FP16 153 / 162 /
-// 145, 700 x 101 x 99 FP32 461 / 445 / 434).
+// 145, 700 x 101 x 99 FP32 461 / 445 / 434, 429 x 31 x 18 FP64 26.5 / 26.6 / 25.2). order -1: as 1, in
+// unequal eighths then, for states that fit the L2s, where neighbours find each other's rows
+// (kSmallState; 352 x 15 x 11 FP64 9.8 / 7.5 / 8.4, 600 x 15 x 11 FP32 8.1 / 6.7 / 7.7, D2Q9 1280 x 333 FP32
+// 7.9 / 7.0 / 7.5, 1001 x 101 5.1 / 4.7 / 5.1).
+constexpr size_t kSmallState = (size_t)16 << 20;
 CM_RULE uint32_t ordered_block(uint32_t lin, uint32_t total, int order) {
     if (order == 0) return lin;
-    if (order == 1 && (total & 7u) == 0u) return (lin & 7u) * (total >> 3) + (lin >> 3);
+    if (order == -1 || (order == 1 && (total & 7u) == 0u)) {
+        const uint32_t k = lin & 7u, rest = total & 7u;   // the first `rest` eighths are one longer
+        return k * (total >> 3) + (k < rest ? k : rest) + (lin >> 3);
+    }
     const uint32_t run = order == 1 ? 32u : (uint32_t)order, round = lin / (8u * run), k = lin % (8u * run);
     return (round + 1u) * 8u * run <= total ? round * 8u * run + (k & 7u) * run + (k >> 3) : lin;
 }
@@ -144,13 +151,14 @@ inline bool inplace_rows_fill(int es, int nx, int ny, int64_t rows, bool walls) 
     return rows >= (es == 8 ? 16384 : (nx > 256 ? 1024 : 4096));
 }
 
-// Adjoint rows of 65 to 256 cells: packed, or one row in a workgroup with ordinary stores,
-// from 2,048 rows on (us, packed / by row: 75 x 32 x 32 FP32 11.1 / 9.6, 89 x 5 x 56 8.5 / 8.3, 250 x
-// 5 x 56 10.9 / 9.8; of more rows 101 x 90 x 80 46.7 / 52.9); and below 512 rows one wave a
-// workgroup, which spreads them over the CUs (89 x 5 x 56 7.1 in one-wave workgroups, 8.3 in two-wave
-// ones).
-inline bool adjoint_rows_pack(int64_t rows) { return rows >= 2048; }
-inline bool adjoint_one_wave(int64_t rows) { return rows < 512; }
+// Adjoint rows of 65 to 256 cells: one wave a workgroup where one workgroup a row would be
+// little more than one for each of the 256 CUs, a few of which then take two (us, one workgroup
+// a row / one-wave ones: 280 rows 89 wide FP32 8.5 / 7.0, 150 wide 9.4 / 8.5, FP64 14.8 / 10.4, 250 wide FP32 10.8 /
+// 9.6; 480 rows 101 wide 9.9 / 8.4, FP64 10.6 / 10.2, 201 wide 11.1 / 11.4, FP64 17.2 / 19.3; 256 rows 150 wide
+// 7.7 / 8.2, FP64 9.2 / 9.9; 1,024 rows 250 wide 17.9 / 19.9).
+inline bool adjoint_one_wave(int nx, int64_t rows) {
+    return nx > 64 && nx <= 256 && rows > 256 && rows < (nx <= 128 ? 512 : 384);
+}
 
 // Whether init_equilibrium goes by whole rows through LDS or by lanes, whose scattered
 // partial lines cost nothing where a state stays in the 256 MB Infinity Cache: from 192 MiB on, and on

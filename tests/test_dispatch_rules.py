@@ -18,19 +18,20 @@ def rules():
     return ctypes.CDLL(HOSTLIB)
 
 
-@pytest.mark.parametrize("order", [0, 1, 2, 32, 256])
+@pytest.mark.parametrize("order", [-1, 0, 1, 2, 32, 256])
 @pytest.mark.parametrize("total", [1, 7, 8, 9, 255, 256, 257, 1000, 1001, 4096, 10002])
 def test_workgroup_orders(rules, order, total):
     """Every order visits every place once. Contiguous eighths only where the count
-    has them; else whole runs of 32 go to one XCD (workgroups k, k + 8, ...)."""
+    has them, or for small states; else whole runs of 32 go to one XCD (workgroups k, k + 8, ...)."""
     at = [rules.cmhost_rule_ordered_block(k, total, order) for k in range(total)]
     assert sorted(at) == list(range(total))
     run = 32 if order == 1 and total % 8 else order
     if order == 0:
         assert at == list(range(total))
-    elif order == 1 and total % 8 == 0:
+    elif order == -1 or (order == 1 and total % 8 == 0):
+        ends = [sum(total // 8 + (k < total % 8) for k in range(xcd)) for xcd in range(9)]
         for xcd in range(8):
-            assert at[xcd::8] == list(range(xcd * total // 8, (xcd + 1) * total // 8))
+            assert at[xcd::8] == list(range(ends[xcd], ends[xcd + 1]))
     else:
         full = total // (8 * run) * 8 * run
         for xcd in range(8):
@@ -92,11 +93,10 @@ def test_in_place_rows_by_row_from_enough_rows(rules, es, nx, ny, nz, walls, wan
     assert rules.cmhost_rule_inplace_rows_fill(es, nx, ny, ctypes.c_int64(ny * nz), walls) == want
 
 
-@pytest.mark.parametrize("ny,nz,pack,one_wave", [(5, 56, 0, 1), (16, 16, 0, 1), (32, 32, 0, 0), (90, 80, 1, 0)])
-def test_adjoint_rows_of_few_and_many(rules, ny, nz, pack, one_wave):
-    rows = ctypes.c_int64(ny * nz)
-    assert rules.cmhost_rule_adjoint_rows_pack(rows) == pack
-    assert rules.cmhost_rule_adjoint_one_wave(rows) == one_wave
+@pytest.mark.parametrize("nx,ny,nz,want", [(89, 5, 56, 1), (250, 5, 56, 1), (128, 20, 24, 1), (201, 20, 24, 0), (150, 16, 16, 0), (250, 32, 32, 0),
+                                           (64, 5, 56, 0), (300, 5, 56, 0)])
+def test_adjoint_rows_in_one_wave_workgroups(rules, nx, ny, nz, want):
+    assert rules.cmhost_rule_adjoint_one_wave(nx, ctypes.c_int64(ny * nz)) == want
 
 
 @pytest.mark.parametrize("es,nx,cells,start,set_", [
