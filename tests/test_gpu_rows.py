@@ -363,3 +363,45 @@ def test_short_rows_read_by_rows(storage, nx):
     (f, f32, mom), big = got
     assert torch.equal(f.repeat(1, m, 1, 1), big[0]) and torch.equal(f32.repeat(1, m, 1, 1), big[1])
     assert torch.equal(mom[0].repeat(m, 1, 1), big[2][0]) and torch.equal(mom[1].repeat(1, m, 1, 1), big[2][1])
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("nx,ny,nz", [(9, 33, 40), (32, 33, 40), (64, 9, 5), (187, 151, 24), (250, 151, 24), (300, 33, 21), (384, 33, 21), (700, 5, 3)])
+@pytest.mark.parametrize("walls", [False, True])
+def test_states_off_vector_boundaries(storage, nx, ny, nz, walls):
+    """Steps between buffers that start at any element of a 16-byte vector: the same bits
+    as between aligned ones, and nothing written beside them."""
+    torch = _torch()
+    from paper_1202_6074_amd.lattice import Lattice
+    lat = Lattice((nx, ny, nz), storage=storage, walls=walls, wall_u_hi=(0.02, 0.0, 0.01))
+    lat.set_relaxation(1.7, cs_smag=0.12)
+    g = torch.Generator().manual_seed(nx)
+    lat.init_equilibrium((0.05 * torch.randn((3, nz, ny, nx), generator=g, dtype=torch.float64)).cuda())
+    src = lat.state_buffer().clone()
+    want = torch.empty_like(src)
+    lat.step_from(src, want)
+    n, v = src.numel(), 16 // ELEM[storage]
+    for a, b in ((1, 0), (0, 1), (v - 1, 1), (v // 2, v - 1)):
+        room = torch.full((2, n + 2 * v), 77.0, dtype=src.dtype, device="cuda")
+        s, d = room[0][a:a + n], room[1][b:b + n]
+        s.copy_(src.flatten())
+        lat.step_from(s, d)
+        assert torch.equal(d, want.flatten()), (a, b)
+        assert bool((room[1][:b] == 77).all()) and bool((room[1][b + n:] == 77).all())
+
+
+def test_more_lattices_than_shared_result_slots():
+    """Reductions of 70 lattices at a time (64 share a page of host memory), and of new ones
+    after some are gone."""
+    torch = _torch()
+    from paper_1202_6074_amd.lattice import Lattice
+    lats = []
+    for k in range(70):
+        lats.append(Lattice((8, 4, 3), storage="f64"))
+        lats[-1].init_equilibrium(torch.zeros((3, 3, 4, 8), device="cuda"), torch.full((3, 4, 8), 1.0 + k, device="cuda"))
+    assert all(abs(lat.reduce()["mass"] - 96 * (1 + k)) < 1e-9 for k, lat in enumerate(lats))
+    for k in range(0, 70, 3):
+        lats[k].close()
+        lats[k] = Lattice((8, 4, 3), storage="f64")
+        lats[k].init_equilibrium(torch.zeros((3, 3, 4, 8), device="cuda"), torch.full((3, 4, 8), 2.0 + k, device="cuda"))
+    assert all(abs(lat.reduce()["mass"] - 96 * (1 + k + (k % 3 == 0))) < 1e-9 for k, lat in enumerate(lats))
