@@ -271,18 +271,18 @@ __device__ __forceinline__ void add_wall_terms(const Geom& g, int y, const Launc
 // y and z are uniform across a block, so the 27 source rows are uniform
 // pointers (scalar registers); only the x offset (x - 1, x, x + 1 with wrap)
 // varies across lanes, as a 32-bit byte offset.
-// NTX: non-temporal loads also for the x-shifted rows (ex != 0). When a row is
-// split between workgroups, the cache lines at the split are read by two of
-// them, and ordinary loads keep those lines for the second reader (measured
-// +4 % for FP32 at 512^3); the step kernel takes ordinary loads there, and
-// gather_xlds when one workgroup covers a row. The read-out kernels keep the
-// default.
+// The rows read at x, once, take non-temporal loads; the x-shifted rows ordinary ones,
+// since the neighbouring wave, and at the split of a row between workgroups another
+// workgroup, reads their cache lines too (non-temporal +4 % for FP32 at 512^3; reductions of
+// 512 x 512 x 128 FP16 531 us non-temporal, 458 ordinary; the aligned rows of the odd in-place gather
+// non-temporal: 1024 x 512 x 512 FP32 10,930 -> 10,832 us, FP16 shifted 6,038 -> 5,957 us per pair).
+// gather_xlds, where one workgroup covers a row, reads every line once.
 // WALLS: a group from a wall reads other rows and is not shifted; y is uniform, so
 // these are scalar selects, and the wall terms are added at the end (a branch
 // for each population kept the loads from being in flight together: the adjoint
 // of 128^3 FP32 with the eddy viscosity between walls 175 us, now 119, periodic
 // 118).
-template <int S, bool WALLS, int MODE = 0, bool NTX = true, bool SB = false, typename R = typename Store<S>::R>
+template <int S, bool WALLS, int MODE = 0, bool SB = false, typename R = typename Store<S>::R>
 __device__ __forceinline__ void gather(const typename Store<S>::T* src, const Geom g, int x, int y, int z,
                                        const Launch<R>& L, R (&h)[27]) {
     using T = typename Store<S>::T;
@@ -310,25 +310,18 @@ __device__ __forceinline__ void gather(const typename Store<S>::T* src, const Ge
         const bool rev = (MODE == 2) != wall;
         const T* grp = src + row_base(g, rev ? 24 - 3 * q : 3 * q, wall ? y : ys[iy], wall ? z : zs[iz]);
         const auto p = row_at<SB>(grp, xo[wall ? 1 : ix] + (uint32_t)(rev ? 2 - ix : ix) * rb);
-        // rows read at x once: non-temporal; x-shifted rows: non-temporal only with
-        // NTX and not in the odd in-place gather (whose shifted reads share lines
-        // with the neighbouring wave; its aligned rows non-temporal: 1024 x 512 x
-        // 512 FP32 10,930 -> 10,832 us, FP16 shifted 6,038 -> 5,957 us per pair)
-        if (ix == 1 || (MODE != 2 && NTX)) h[i] = load_dev<S, true>(p, i, L.P.rho0);   // w_i = w_{26-i}
-        else h[i] = load_dev<S, false>(p, i, L.P.rho0);
+        h[i] = ix == 1 ? load_dev<S, true>(p, i, L.P.rho0) : load_dev<S, false>(p, i, L.P.rho0);   // w_i = w_{26-i}
     }
     if constexpr (WALLS) add_wall_terms(g, y, L, h);
 }
 
-// Gather in the mode the geometry's streaming state asks for (read-out kernels;
-// ordinary loads of the x-shifted rows, whose lines the neighbouring wave reads
-// too: reductions of 512 x 512 x 128 FP16 531 us non-temporal, 458 ordinary).
+// Gather in the mode the geometry's streaming state asks for (read-out kernels).
 template <int S, bool WALLS, typename R = typename Store<S>::R>
 __device__ __forceinline__ void gather_any(const typename Store<S>::T* src, const Geom g, int x, int y, int z,
                                            const Launch<R>& L, R (&h)[27]) {
-    if (g.aa == 0) gather<S, WALLS, 0, false>(src, g, x, y, z, L, h);
-    else if (g.aa == 1) gather<S, WALLS, 1, false>(src, g, x, y, z, L, h);
-    else gather<S, WALLS, 2, false>(src, g, x, y, z, L, h);
+    if (g.aa == 0) gather<S, WALLS, 0>(src, g, x, y, z, L, h);
+    else if (g.aa == 1) gather<S, WALLS, 1>(src, g, x, y, z, L, h);
+    else gather<S, WALLS, 2>(src, g, x, y, z, L, h);
 }
 
 // Gather of the two-buffer pull scheme when one workgroup covers a whole grid
@@ -709,7 +702,7 @@ __global__ void __launch_bounds__(256, (S == 3 && !SGS) ? 5 : 1) k_step(const ty
                     R acc[3], F[3];
                     if constexpr (SGS) sgs_accel<R, true>(rs_prev, g, x, y, z, acc);
                     R h[27], ls[9], ld[9];
-                    gather<S, WALLS, 0, false, true>(src, g, x, y, z, L, h);
+                    gather<S, WALLS, 0, true>(src, g, x, y, z, L, h);
                     row_force<R, FFIELD, true>(force, g, L, x, y, z, F);
                     zline_sums(h, ls, ld);
                     finish_cell<S, LES, VAR, SGS, true>(dst, g, L, x, y, z, h, ls, ld, F, acc, rs_next);
@@ -721,7 +714,7 @@ __global__ void __launch_bounds__(256, (S == 3 && !SGS) ? 5 : 1) k_step(const ty
             R acc[3], F[3];
             if constexpr (SGS) sgs_accel(rs_prev, g, x, y, z, acc);
             R h[27], ls[9], ld[9];
-            gather<S, WALLS, 0, false>(src, g, x, y, z, L, h);
+            gather<S, WALLS, 0>(src, g, x, y, z, L, h);
             row_force<R, FFIELD>(force, g, L, x, y, z, F);
             zline_sums(h, ls, ld);
             finish_cell<S, LES, VAR, SGS>(dst, g, L, x, y, z, h, ls, ld, F, acc, rs_next);
@@ -1384,7 +1377,7 @@ __global__ void __launch_bounds__(256) k_adjoint(const typename Store<S>::T* __r
         gather_packed<-1, WALLS, false>(state, g, x, y, z, t);
         stored_devs<S, WALLS>(t, g, y, L, h);
     } else {
-        gather<S, WALLS, 0, false>(state, g, x, y, z, L, h);
+        gather<S, WALLS, 0>(state, g, x, y, z, L, h);
     }
     // lambda at x + e_i: the rows (y + ey, z + ez) are block-uniform (scalar
     // registers); only the x offset (x - 1, x, x + 1 with wrap) is per lane.
@@ -1445,7 +1438,7 @@ __global__ void __launch_bounds__(256) k_energy_seed(const typename Store<S>::T*
     if (x >= g.nx) return;
     const int c = x + g.nx * (y + g.ny * z);
     R h[27];
-    gather<S, WALLS, 0, false>(state, g, x, y, z, L, h);
+    gather<S, WALLS, 0>(state, g, x, y, z, L, h);
     R Fx, Fy, Fz;
     cell_force<R, FFIELD>(force, g, c, L, Fx, Fy, Fz);
     R drho, jx, jy, jz;
@@ -1767,8 +1760,10 @@ static void launch_packed(const LaunchArgs& a, F&& launch) {
     Geom gp = a.g;
     int lanes = pack_lanes(a.g);
     const dim3 gq = pack_rows(gp, lanes);
-    if ((size_t)gp.nx * es % 128 == 0) launch(gq, lanes, 0u, gp, std::true_type());
-    else launch(gq, lanes, (unsigned)(((size_t)gp.pack * 27 * gp.nx * es + 47) / 16 * 16), gp, std::false_type());
+    if constexpr (es != 2) {   // (FP16 rows of whole lines fill their waves and are not packed)
+        if ((size_t)gp.nx * es % 128 == 0) return launch(gq, lanes, 0u, gp, std::true_type());
+    }
+    launch(gq, lanes, (unsigned)(((size_t)gp.pack * 27 * gp.nx * es + 47) / 16 * 16), gp, std::false_type());
 }
 
 template <int S, bool W, bool LES, bool FF>
@@ -1818,9 +1813,10 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
                 k_step_row<S, W, LES, FF, decltype(v)::value, false, decltype(d)::value>
                     <<<gq, row_lanes(gg), row_lds<T>(gg), st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L);
             };
-            if (var && direct) launch(std::true_type(), std::true_type());
-            else if (var) launch(std::true_type(), std::false_type());
-            else if (direct) launch(std::false_type(), std::true_type());
+            if constexpr (S != 0) {   // (FP64 rows that start on cache lines do not come here)
+                if (direct) return var ? launch(std::true_type(), std::true_type()) : launch(std::false_type(), std::true_type());
+            }
+            if (var) launch(std::true_type(), std::false_type());
             else launch(std::false_type(), std::false_type());
         });
     }
@@ -1939,8 +1935,6 @@ static hipError_t step_sgs_t(const LaunchArgs& a, const void* src, void* dst) {
     // over runs of rows per XCD (measured 768 against 784 us at 256^3)
     Geom g = a.g;
     if (a.xcd_default && g.xcd >= 2) g.xcd = 0;
-    // FP32 rows of one workgroup in chunks of planes, as the step without the
-    // stress force (256^3: 769.4 -> 761.2 us)
     if (packed_rows<S>(g)) {
         launch_packed<S>(a, [&](const dim3& gq, int lanes, unsigned lds, const Geom& gp, auto d) {
             constexpr bool D = decltype(d)::value;
@@ -1956,12 +1950,15 @@ static hipError_t step_sgs_t(const LaunchArgs& a, const void* src, void* dst) {
                 k_step_row<S, false, false, FF, decltype(v)::value, true, decltype(d)::value>
                     <<<gq, row_lanes(gg), row_lds<T>(gg), st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gg, L, rp, rn);
             };
-            if (var && direct) launch(std::true_type(), std::true_type());
-            else if (var) launch(std::true_type(), std::false_type());
-            else if (direct) launch(std::false_type(), std::true_type());
+            if constexpr (S != 0) {
+                if (direct) return var ? launch(std::true_type(), std::true_type()) : launch(std::false_type(), std::true_type());
+            }
+            if (var) launch(std::true_type(), std::false_type());
             else launch(std::false_type(), std::false_type());
         });
     }
+    // FP32 rows of one workgroup in chunks of planes, as the step without the
+    // stress force (256^3: 769.4 -> 761.2 us)
     return launch_z_chunks(g, grid, sizeof(T) == 4 && xl, [&](const dim3& gq, const Geom& gg) {
         if (xl) {
             with_row_width(bx, [&](auto w) {
