@@ -193,10 +193,15 @@ typedef struct {
  * Eq. cascadedstreaming1. buf_a and buf_b are two device buffers of
  * bytes_each >= Q*N*element bytes (Q = 27 for D3Q27, 9 for D2Q9; element 8,
  * 4, 4, 2 bytes for the storage modes), caller-owned and borrowed for the
- * handle's lifetime; hip_stream is a hipStream_t (may be null for the default
+ * handle's lifetime; they may start at any element. Population buffers are
+ * read in whole 16-byte vectors: up to 15 bytes before and after one, in the
+ * vectors its ends lie in, may be read (and are not used), never written.
+ * hip_stream is a hipStream_t (may be null for the default
  * stream). Every description field is validated on the host (CMLBM_EINVAL,
- * nothing allocated); then a small device scratch area for the reductions is
- * allocated (CMLBM_EHIP on failure). Relaxation defaults to omega_shear = 1
+ * nothing allocated); then a device scratch area for the reductions
+ * (65,536 bytes) is allocated, and with the first handle a page of pinned host
+ * memory for their results, which 64 handles at a time share and the process keeps
+ * (each further one allocates 64 bytes of its own; CMLBM_EHIP on failure). Relaxation defaults to omega_shear = 1
  * and all other rates 1, no eddy viscosity, F = 0. The state is undefined
  * until cmlbm_init_equilibrium or cmlbm_set_populations. */
 cmlbm_status cmlbm_create(const cmlbm_desc* desc /* [host] */, void* buf_a, void* buf_b, size_t bytes_each,
@@ -249,9 +254,11 @@ cmlbm_status cmlbm_step_from(cmlbm_handle h, const void* src, void* dst);
 
 /* nsteps >= 1 steps of cmlbm_step_from in one call, from src into dst, with the
  * handle's own two buffers in between: neither src nor dst may be one of
- * them (CMLBM_EINVAL, as what cmlbm_step_from refuses), and the handle's
+ * them (CMLBM_EINVAL), and the handle's
  * state is undefined afterwards until a state is set or copied into
- * cmlbm_state_buffer. */
+ * cmlbm_state_buffer. src and dst may be the same buffer for nsteps >= 2 (for one step
+ * CMLBM_EINVAL); null buffers, the sub-grid force and in-place streaming are refused
+ * as by cmlbm_step_from. */
 cmlbm_status cmlbm_steps_between(cmlbm_handle h, const void* src, void* dst, int64_t nsteps);
 
 /* nsteps >= 0 steps of cmlbm_step_from in one call, every state kept: step k

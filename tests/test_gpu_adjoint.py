@@ -395,3 +395,20 @@ def test_energy_of_lattices_without_an_adjoint(kind):
             E.append(float(EnergyAdjoint.apply(F, lat, lat.state_buffer().clone(), 5, 2)))
             assert lat.reduce()["ke"] == E[0]
     assert E[0] == E[1]
+
+
+@pytest.mark.parametrize("n", [2, 5])
+def test_steps_between_back_into_the_same_buffer(n):
+    torch = _torch()
+    from paper_1202_6074_amd import _lib
+    from paper_1202_6074_amd.lattice import Lattice
+    g = torch.Generator().manual_seed(n)
+    lat = Lattice((12, 7, 5), storage="f32")
+    lat.init_equilibrium((0.05 * torch.randn((3, 5, 7, 12), generator=g)).cuda())
+    a = lat.state_buffer().clone()
+    b = torch.empty_like(a)
+    lat.steps_between(a, b, n)
+    lat.steps_between(a, a, n)
+    assert torch.equal(a, b)
+    with pytest.raises(_lib.CmlbmError):
+        lat.steps_between(a, a, 1)
