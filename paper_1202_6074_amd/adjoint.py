@@ -29,10 +29,11 @@ from .lattice import Lattice
 def _on_stream_of(lat: Lattice, *inputs: torch.Tensor):
     """torch's work inside runs on the lattice's stream, where its kernels run:
     after what the caller queued so far, and before what the caller queues next.
-    inputs: the caller's tensors that are read inside."""
+    inputs: the caller's tensors that are read inside. Gives the caller's stream, or None
+    where it is the lattice's."""
     caller = torch.cuda.current_stream(lat.device)
     if caller == lat.stream:
-        yield caller
+        yield None
         return
     lat.stream.wait_stream(caller)
     lat._after_use(*[t for t in inputs if t.device == lat.device])
@@ -137,7 +138,8 @@ class EnergyAdjoint(torch.autograd.Function):
     def backward(ctx, gE):
         with _on_stream_of(ctx.lat) as caller:
             gF = _backward(ctx.lat, ctx.F, ctx.ckpts, ctx.final, ctx.nsteps, ctx.K)
-            gF.record_stream(caller)   # used there from now on
+            if caller is not None:
+                gF.record_stream(caller)   # used there from now on
         ctx.ckpts = ctx.final = None
         return (gE.to(gF.dtype) * gF), None, None, None, None
 

@@ -161,25 +161,30 @@ inline bool adjoint_one_wave(int nx, int64_t rows) {
 }
 
 // Whether init_equilibrium goes by whole rows through LDS or by lanes, whose scattered
-// partial lines cost nothing where a state stays in the 256 MB Infinity Cache: from 192 MiB on, and on
+// partial lines cost little where a state stays in the 256 MB Infinity Cache: from 192 MiB on, and on
 // rows of 64 cells or more or of whole 16-byte vectors (others are written with most of their
 // ends value by value). us, lanes / rows: 3M cells FP16 (162 MB) 256 wide 37 / 42, 187
 // wide 41 / 58; 187 x 151 x 133 (203 MB) 82 / 69; 1M cells FP32 (108 MB) 300 wide 24.5 / 29.2, 128^3
 // (226 MB) 56 / 42; 3M cells FP32 33 wide 126 / 163, 43 121 / 164, 50 114 / 122, 16 145 / 153, 20 137 /
 // 123, 24 x 418 x 418 204 / 144, 75 wide 135 / 117; FP64 43 wide 245 / 251, 24 x 296 x 296 186 / 104.
+// 4- and 8-byte rows of whole cache lines from 16 MiB on (into buffers that no cache holds 256 x 62 x 62 FP32
+// 23.4 / 20.7, 64 x 125 x 125 22.7 / 22.4, FP64 256 x 34 x 34 21.7 / 20.2; into one that the last call
+// filled 21.1 / 21.8, 21.2 / 22.0).
 inline bool start_by_rows(int es, int nx, size_t state_bytes) {
-    if (nx < 16 || nx > 512 || state_bytes < (size_t)192 << 20) return false;
-    return nx >= 64 || (nx * es % 16 == 0 && nx * es >= 80);
+    if (nx < 16 || nx > 512 || state_bytes < (size_t)16 << 20) return false;
+    if (es != 2 && nx >= 64 && nx * es % 128 == 0) return true;
+    return state_bytes >= (size_t)192 << 20 && (nx >= 64 || (nx * es % 16 == 0 && nx * es >= 80));
 }
 
-// The same of set_populations, which reads 8 or 4 bytes a value besides: past the L2s, FP16 from
-// 96 MiB on; rows under 48 cells of whole vectors of 64 bytes or more, and FP64 ones under 40 (us,
-// lanes / rows of FP64 values: 1M cells FP16 64 wide 39.4 / 40.0, 43 wide 53.9 / 59.7, 3M cells 64 wide 151 / 145, 20
-// wide 247 / 264, 33 wide 186 / 202, 40 x 229 x 229 124 / 115; FP32 1M cells 16 wide 97 / 65, 33 wide 66.4 / 67.3, 43
-// wide 65 / 67, 50 wide 59.9 / 59.5, 300 wide 69 / 52; FP64 33 wide 99 / 81, 3M cells 43 wide 304 / 321, 50 wide
-// 272 / 259).
+// The same of set_populations, which reads 8 or 4 bytes a value besides: from 48 MiB on; rows under
+// 48 cells of whole vectors of 64 bytes or more, and FP64 ones under 40 (us, lanes / rows of FP64
+// values: 300,000 cells FP32 (32 MB) 64 wide 15.1 / 16.4, 256 wide 15.9 / 17.7, 1M cells 256 wide 55 / 47,
+// FP16 (54 MB) 128 wide 41.7 / 39.9, 256 wide 38.7 / 39.5, 43 wide 53.9 / 59.7; 3M cells FP16 64 wide 151 /
+// 145, 20 wide 247 / 264, 33 wide 186 / 202, 40 x 229 x 229 124 / 115; 1M cells FP32 16 wide 97 / 65, 33 wide
+// 66.4 / 67.3, 43 wide 65 / 67, 50 wide 59.9 / 59.5, 300 wide 69 / 52; FP64 33 wide 99 / 81, 3M cells 43
+// wide 304 / 321, 50 wide 272 / 259).
 inline bool set_by_rows(int es, int nx, size_t state_bytes) {
-    if (nx < 16 || nx > 512 || state_bytes < (size_t)(es == 2 ? 96 : 16) << 20) return false;
+    if (nx < 16 || nx > 512 || state_bytes < (size_t)48 << 20) return false;
     return nx >= 48 || (nx * es % 16 == 0 && nx * es >= 64) || (es == 8 && nx < 40);
 }
 

@@ -101,8 +101,8 @@ def test_adjoint_rows_in_one_wave_workgroups(rules, nx, ny, nz, want):
 
 @pytest.mark.parametrize("es,nx,cells,start,set_", [
     (4, 43, 3_800_000, 0, 0), (4, 33, 8_000_000, 0, 0), (4, 20, 3_000_000, 1, 1), (4, 16, 3_000_000, 0, 1), (4, 300, 1_000_000, 0, 1),
-    (4, 256, 256 ** 3, 1, 1), (4, 300, 300 * 181 * 90, 1, 1), (4, 20, 20 * 50 * 50, 0, 0), (4, 513, 8_000_000, 0, 0),
-    (2, 187, 187 * 151 * 133, 1, 1), (2, 256, 3_000_000, 0, 1), (2, 64, 1_000_000, 0, 0), (2, 20, 8_000_000, 0, 0), (2, 40, 8_000_000, 1, 1),
+    (4, 256, 256 ** 3, 1, 1), (4, 300, 300 * 181 * 90, 1, 1), (4, 64, 64 * 64 * 128, 1, 1), (4, 256, 300_000, 1, 0), (8, 256, 300_000, 1, 1), (4, 20, 20 * 50 * 50, 0, 0), (4, 513, 8_000_000, 0, 0),
+    (2, 187, 187 * 151 * 133, 1, 1), (2, 256, 3_000_000, 0, 1), (2, 64, 1_000_000, 0, 1), (2, 64, 500_000, 0, 0), (2, 20, 8_000_000, 0, 0), (2, 40, 8_000_000, 1, 1),
     (8, 33, 3_000_000, 0, 1), (8, 43, 3_000_000, 0, 0), (8, 24, 3_000_000, 1, 1), (8, 201, 201 * 160 * 100, 1, 1)])
 def test_states_set_by_rows(rules, es, nx, cells, start, set_):
     nbytes = ctypes.c_size_t(27 * es * cells)
