@@ -1711,8 +1711,8 @@ static bool pair_rows(const Geom& g, const void* src, const void* dst, const voi
 
 // Occupancy caps by LDS reservation: with 60,000 bytes of the CU's 160 KB of
 // LDS reserved per workgroup, at most two workgroups share a CU, with 50,000
-// three; with 40,960 bytes, three for a kernel that holds 9 KB of its own. The
-// reserved LDS itself is not used (the per-lane two-buffer kernels hold none: 40,960 bytes are four there). Fewer resident rows per CU make the DRAM
+// three; with 40,960 bytes, three for a kernel that holds 9 KB of its own and four
+// for one without. The reserved LDS itself is not used. Fewer resident rows per CU make the DRAM
 // traffic of these kernels more efficient. The per-lane in-place pair with 4-byte
 // populations on rows of at most 512 cells: two workgroups where they are full
 // 256-lane ones, three where rows leave lanes idle or take 192 (us per step, two /
@@ -1779,9 +1779,10 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
         if (pair_rows(a.g, src, dst, a.force_field)) {
             const dim3 gp(1, a.g.yrows, a.g.nz);
             // one lane per pair; at most three workgroups per CU (with the
-            // kernel's own 9 KB of LDS) for the longest rows only (512 x 512 x
-            // 128: 688 us per step without, 663 with the cap; 400 x 200 x 200:
-            // 335 and 343, in 256 lanes for all widths and the cap 381)
+            // kernel's own 9 KB of LDS) for the longest rows only (us per step without / with
+            // the cap: 512 x 512 x 128 688 / 663, 512 x 400 x 200 830 / 811, 510 940 / 923, 464
+            // 814 / 806, 450 822 / 811, but 480 799 / 799, 496 893 / 897, 448 724 / 740, 432 757 / 766, 400 x
+            // 200 x 200 335 / 343; few rows 512 x 100 x 100 96.2 / 97.3)
             const int bp = (a.g.nx / 2 + 63) / 64 * 64;
             const unsigned pcap = a.g.nx > 448 ? kLdsPairCap : 0u;
             // past 2^25 cells in chunks of planes, in the plain order (us per step, one
