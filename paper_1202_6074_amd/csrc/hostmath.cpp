@@ -242,6 +242,7 @@ int cmhost_rule_chunks_pay(int nz, int64_t per_plane, int adjoint) {
 int cmhost_rule_d2q9_non_temporal(int es, int nx, int64_t cells, int field, int sgs) {
     return cm::d2q9_non_temporal(es, nx, cells, field, sgs);
 }
+int cmhost_rule_packing_pays(int es, int64_t rows, int walls) { return cm::packing_pays(es, rows, walls); }
 unsigned cmhost_rule_xlds_reserve_f64(int width, size_t bytes) { return cm::xlds_reserve_f64(width, bytes); }
 
 }

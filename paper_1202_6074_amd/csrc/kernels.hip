@@ -1670,7 +1670,7 @@ static dim3 pack_rows(Geom& g, int& lanes) {
 // 42.0 / 28.1, FP64 107 / 94; 70 x 200 x 100 FP16 43.7 / 33.3, FP32 57.9 / 56.7; with
 // less to fill 45 x 60 x 80 FP32 12.2 / 13.0, 96^3 36.4 / 38.5, 128^3 75.7 / 83.1. But FP32
 // rows of whole cache lines of lattices inside the L2s, where launches and
-// latency count (32^3 4.7 / 4.9).
+// latency count (32^3 4.7 / 4.9), and not on few rows (packing_pays).
 // In place (us per step, row / packed): 20 x 200 x 200 FP32 45.6 / 32.2, FP16 46.5 / 21.8,
 // FP64 77.2 / 57.3; 32 x 200 x 200 FP32 51.2 / 44.5; 70 x 200 x 100 FP32 62.5 / 53.2, FP16
 // 47.6 / 31.6; 32^3 FP32 6.2 / 4.7.
@@ -1684,9 +1684,11 @@ static bool packed_fill(const Geom& g) {
 }
 
 template <int S>
-static bool packed_rows(const Geom& g) {
-    if (sizeof(typename Store<S>::T) == 4 && g.nx % 32 == 0 && !past_l2<S>(g)) return false;
-    return packed_fill<S>(g);
+static bool packed_rows(const LaunchArgs& a) {
+    constexpr size_t es = sizeof(typename Store<S>::T);
+    const Geom& g = a.g;
+    if (es == 4 && g.nx % 32 == 0 && !past_l2<S>(g)) return false;
+    return packing_pays((int)es, (int64_t)g.ny * g.nz, a.walls != 0) && packed_fill<S>(g);
 }
 
 // Calls f with the row width XL of the LDS-exchange kernel as a compile-time
@@ -1795,7 +1797,7 @@ static hipError_t step_t(const LaunchArgs& a, const void* src, void* dst) {
             });
         }
     }
-    if (packed_rows<S>(a.g)) {
+    if (packed_rows<S>(a)) {
         launch_packed<S>(a, [&](const dim3& gq, int lanes, unsigned lds, const Geom& gp, auto d) {
             constexpr bool D = decltype(d)::value;
             if (var) k_step_packed<S, W, LES, FF, true, false, D><<<gq, lanes, lds, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gp, L);
@@ -1936,7 +1938,7 @@ static hipError_t step_sgs_t(const LaunchArgs& a, const void* src, void* dst) {
     // over runs of rows per XCD (measured 768 against 784 us at 256^3)
     Geom g = a.g;
     if (a.xcd_default && g.xcd >= 2) g.xcd = 0;
-    if (packed_rows<S>(g)) {
+    if (packed_rows<S>(a)) {
         launch_packed<S>(a, [&](const dim3& gq, int lanes, unsigned lds, const Geom& gp, auto d) {
             constexpr bool D = decltype(d)::value;
             if (var) k_step_packed<S, false, false, FF, true, true, D><<<gq, lanes, lds, st>>>((const T*)src, (T*)dst, (const R*)a.force_field, gp, L, rp, rn);
@@ -1988,7 +1990,7 @@ hipError_t step_w(const LaunchArgs& a, const void* src, void* dst) {
         return a.force_field ? step_sgs_t<S, true>(a, src, dst) : step_sgs_t<S, false>(a, src, dst);
     }
     const bool pairs = S == 3 && a.walls && walled_pairs(a.g.nx, (int64_t)a.g.ny * a.g.nz) && pair_rows(a.g, src, dst, a.force_field);
-    if (!pairs && (packed_rows<S>(a.g) || whole_rows<S>(a) || one_block_per_row(a.g)))
+    if (!pairs && (packed_rows<S>(a) || whole_rows<S>(a) || one_block_per_row(a.g)))
         return a.walls ? step_les<S, true>(a, src, dst) : step_les<S, false>(a, src, dst);
     return split_wall_rows(a, [&](const LaunchArgs& b, bool w) {
         return w ? step_les<S, true>(b, src, dst) : step_les<S, false>(b, src, dst);

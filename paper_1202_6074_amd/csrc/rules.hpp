@@ -151,6 +151,15 @@ inline bool inplace_rows_fill(int es, int nx, int ny, int64_t rows, bool walls) 
     return rows >= (es == 8 ? 16384 : (nx > 256 ? 1024 : 4096));
 }
 
+// Two-buffer rows are packed from 1,280 rows on (FP64 512): fewer leave CUs idle, and a lane's
+// own row costs the packed kernel its uniform addresses (us per step, packed / by row, periodic: 256 rows 17 wide
+// FP32 5.9 / 5.5, 85 wide 6.0 / 5.4, FP64 17 wide 7.0 / 6.0, 33 wide 6.7 / 5.8; 529 rows 33 wide FP32 6.0 / 5.5, 85
+// wide 6.0 / 6.4, FP64 75 wide 6.8 / 8.2, 17 wide 6.9 / 6.5; 1,024 rows 17 wide FP32 6.2 / 5.7, 75 wide 7.6 / 7.0, FP64
+// 20 wide 6.7 / 7.3, 30 wide 6.3 / 7.6; 1,521 rows 12 wide FP32 6.3 / 6.3, 24 wide 6.1 / 6.4, FP16 75 wide 7.1 / 7.9;
+// 2,070 rows 70 wide FP32 7.7 / 10.1, FP16 7.1 / 8.6). Between walls packed at any size: the rows' own
+// kernel is the slower one there (524 rows 30 wide 5.5 / 6.2).
+inline bool packing_pays(int es, int64_t rows, bool walls) { return walls || rows >= (es == 8 ? 512 : 1280); }
+
 // Adjoint rows of 65 to 256 cells: one wave a workgroup where one workgroup a row would be
 // little more than one for each of the 256 CUs, a few of which then take two (us, one workgroup
 // a row / one-wave ones: 280 rows 89 wide FP32 8.5 / 7.0, 150 wide 9.4 / 8.5, FP64 14.8 / 10.4, 250 wide FP32 10.8 /

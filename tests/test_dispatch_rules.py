@@ -141,3 +141,10 @@ def test_chunks_of_planes(rules, nz, rows, adjoint, want):
     (4, 50, 4000, 1, 0, 1), (2, 50, 4000, 1, 0, 1), (8, 50, 4000, 1, 0, 0), (8, 50, 40000, 1, 0, 1), (4, 100, 100, 1, 0, 0)])
 def test_d2q9_stores(rules, es, nx, ny, field, sgs, want):
     assert rules.cmhost_rule_d2q9_non_temporal(es, nx, ctypes.c_int64(nx * ny), field, sgs) == want
+
+
+@pytest.mark.parametrize("es,ny,nz,walls,want", [
+    (4, 16, 16, 0, 0), (4, 32, 32, 0, 0), (4, 46, 45, 0, 1), (2, 262, 2, 0, 0), (2, 33, 40, 0, 1), (4, 16, 16, 1, 1),
+    (8, 16, 16, 0, 0), (8, 23, 23, 0, 1), (8, 32, 32, 0, 1)])
+def test_packing_from_enough_rows(rules, es, ny, nz, walls, want):
+    assert rules.cmhost_rule_packing_pays(es, ctypes.c_int64(ny * nz), walls) == want
