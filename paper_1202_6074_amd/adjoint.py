@@ -18,28 +18,27 @@ HIP kernels, a segment's steps in one call each (``cmlbm_steps_between``, ``cmlb
 """
 from __future__ import annotations
 
-from contextlib import contextmanager
-
 import torch
 
 from .lattice import Lattice
 
 
-@contextmanager
-def _on_stream_of(lat: Lattice, *inputs: torch.Tensor):
-    """torch's work inside runs on the lattice's stream, where its kernels run:
-    after what the caller queued so far, and before what the caller queues next.
-    inputs: the caller's tensors that are read inside. Gives the caller's stream, or None
-    where it is the lattice's."""
-    caller = torch.cuda.current_stream(lat.device)
-    if caller == lat.stream:
-        yield None
-        return
+def _on_stream_of(lat: Lattice, caller, work, *inputs: torch.Tensor):
+    """work() with torch's part of it on the lattice's stream, where its kernels run: after
+    what the caller queued so far, and before what the caller queues next. caller: the
+    caller's current stream, or None where it is the lattice's; work returns
+    (something for the caller to use, or None; the rest); inputs: the caller's
+    tensors that it reads."""
+    if caller is None:
+        return work()
     lat.stream.wait_stream(caller)
     lat._after_use(*[t for t in inputs if t.device == lat.device])
     with torch.cuda.stream(lat.stream):
-        yield caller
+        out = work()
+        if out[0] is not None:
+            out[0].record_stream(caller)
     caller.wait_stream(lat.stream)
+    return out
 
 
 def _keep_all(nsteps: int, K: int) -> bool:
@@ -127,19 +126,22 @@ class EnergyAdjoint(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, F, lat, f0_state, nsteps, K):
-        with _on_stream_of(lat, F, f0_state):
+        def work():
             Fs = F.detach().to(device=lat.device, dtype=lat.dtype).clone()
-            E, ckpts, final = _forward(lat, Fs, f0_state, int(nsteps), int(K))
+            return (None, Fs) + _forward(lat, Fs, f0_state, int(nsteps), int(K))
+
+        caller = torch.cuda.current_stream(lat.device.index)
+        ctx.caller = None if caller == lat.stream else caller
+        _, Fs, E, ckpts, final = _on_stream_of(lat, ctx.caller, work, F, f0_state)
         ctx.lat, ctx.F, ctx.ckpts, ctx.final = lat, Fs, ckpts, final
         ctx.nsteps, ctx.K = int(nsteps), int(K)
         return torch.tensor(E, dtype=torch.float64, device=F.device)
 
     @staticmethod
     def backward(ctx, gE):
-        with _on_stream_of(ctx.lat) as caller:
-            gF = _backward(ctx.lat, ctx.F, ctx.ckpts, ctx.final, ctx.nsteps, ctx.K)
-            if caller is not None:
-                gF.record_stream(caller)   # used there from now on
+        # (autograd makes the forward pass's stream the current one)
+        gF, = _on_stream_of(ctx.lat, ctx.caller,
+                            lambda: (_backward(ctx.lat, ctx.F, ctx.ckpts, ctx.final, ctx.nsteps, ctx.K),))
         ctx.ckpts = ctx.final = None
         return (gE.to(gF.dtype) * gF), None, None, None, None
 
