@@ -1937,7 +1937,7 @@ static hipError_t step_sgs_t(const LaunchArgs& a, const void* src, void* dst) {
     // the stress planes read by the y-neighbour rows favour the plain order
     // over runs of rows per XCD (measured 768 against 784 us at 256^3)
     Geom g = a.g;
-    if (a.xcd_default && g.xcd >= 2) g.xcd = 0;
+    if (a.xcd_default && g.xcd == kXcdRun) g.xcd = 0;
     if (packed_rows<S>(a)) {
         launch_packed<S>(a, [&](const dim3& gq, int lanes, unsigned lds, const Geom& gp, auto d) {
             constexpr bool D = decltype(d)::value;

@@ -14,7 +14,7 @@ struct Geom {
     int pairs_off;    // step kernel: 1 = one cell per lane also for FP16 rows (no two-cell kernel)
     int one_launch;   // step kernel: 1 = all z-planes in one launch (no chunks of planes)
     int xcd;       // step kernel workgroup order: 0 plain, 1 XCD-aware (contiguous eighths; -1 also
-                   // unequal ones), R >= 2 runs of R workgroups per XCD in turn (ordered_block)
+                   // unequal ones), kXcdRun runs of 32 workgroups per XCD in turn (ordered_block)
     int aa;        // streaming: 0 two buffers (pull); in place: 1 even parity (natural), 2 odd parity
     // rows of a step launch: y = ybase + ystride * (row index), yrows of them
     // (all rows by default; the interior and the two wall rows are launched

@@ -18,14 +18,13 @@ def rules():
     return ctypes.CDLL(HOSTLIB)
 
 
-@pytest.mark.parametrize("order", [-1, 0, 1, 2, 32, 256])
+@pytest.mark.parametrize("order", [-1, 0, 1, 32])
 @pytest.mark.parametrize("total", [1, 7, 8, 9, 255, 256, 257, 1000, 1001, 4096, 10002])
 def test_workgroup_orders(rules, order, total):
     """Every order visits every place once. Contiguous eighths only where the count
     has them, or for small states; else whole runs of 32 go to one XCD (workgroups k, k + 8, ...)."""
     at = [rules.cmhost_rule_ordered_block(k, total, order) for k in range(total)]
     assert sorted(at) == list(range(total))
-    run = 32 if order == 1 and total % 8 else order
     if order == 0:
         assert at == list(range(total))
     elif order == -1 or (order == 1 and total % 8 == 0):
@@ -33,9 +32,9 @@ def test_workgroup_orders(rules, order, total):
         for xcd in range(8):
             assert at[xcd::8] == list(range(ends[xcd], ends[xcd + 1]))
     else:
-        full = total // (8 * run) * 8 * run
+        full = total // 256 * 256
         for xcd in range(8):
-            assert all(p // run % 8 == xcd for p in at[xcd:full:8])
+            assert all(p // 32 % 8 == xcd for p in at[xcd:full:8])
         assert at[full:] == list(range(full, total))
 
 
